@@ -232,6 +232,7 @@ struct PairPartArgs {
   uint2* part;                 // [n] (new id or -1, vertex - band start)
   uint32_t* table;             // [nb][tiles]
   int32_t* status;
+  int32_t* new2old;            // nullable: receives the ids with kRepBit, at their group's new id
   SortBuffers sort;
   int32_t from_sort;
 };
@@ -265,9 +266,11 @@ static __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartAr
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i) {
     const int64_t k = base + int64_t(i) * kPairBlock + tid;
-    const bool ok = p[i].x <= last && p[i].y <= last;
+    const uint32_t id = p[i].y & ~kRepBit;
+    const bool ok = p[i].x <= last && id <= last;
     if (k < a.n && !ok) bad = true;  // only after a failed wait
-    vtx[i] = k < a.n && ok ? p[i].y : 0xFFFFFFFFu;
+    vtx[i] = k < a.n && ok ? id : 0xFFFFFFFFu;
+    if (a.new2old && k < a.n && ok && (p[i].y & kRepBit) && uint32_t(val[i]) <= last) a.new2old[val[i]] = int32_t(id);
   }
   if (bad) atomicMax(a.status, kBandErrInternal);
   uint32_t r[kPairItems];

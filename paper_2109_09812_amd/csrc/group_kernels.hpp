@@ -19,8 +19,8 @@
 // k, its k-th used group's element goes to slot span start + k of the
 // element buffer. Names stay below N and need no count of earlier chunks, so
 // the chunks never wait for each other; the chunks' counts go to per-run
-// sums, and k_group_compact_hist adds those up and packs the used groups'
-// elements densely while counting their key digits.
+// sums, from which the kernels that order the used groups (split_kernels.hpp)
+// find the elements.
 //
 // A batch groups by (mesh id, record): every mesh owns a range of buckets,
 // so its vertices end up at the sorted positions of its own vertex range,
@@ -28,10 +28,8 @@
 // lies in that range (the name tells the group's mesh).
 //
 // A bucket that does not fit the LDS window (many copies of one value, or an
-// unlucky hash) makes the call take the plain path instead: the same key
-// sort then runs on all N hash-ordered elements, followed by Section 2's
-// run-head flags and scans. Both paths give the identical result; which one
-// runs is decided on the device (Control::path).
+// unlucky hash) is grouped by the same workgroup through a table of chains in
+// global memory (group_big_bucket), whatever its size.
 #pragma once
 
 #include "device_common.hpp"
@@ -63,19 +61,18 @@ struct GroupShape {
   static_assert(TS * 3 >= WIN * 4, "table load");
 };
 
-// Per-chunk record of k_group: span start, used groups, groups, 1 if the
-// chunk's last bucket did not fit the window.
+// Per-chunk record of k_group: span start, used groups.
 struct GroupArgs {
   const uint32_t* elems;   // [n][K+1] elements in (hash bucket, id) order
   int64_t n;
   uint32_t bucket_mask;    // bucket of a record = hash & bucket_mask
-  uint2* pairs;            // [n] (group name, original id) per position
-  int32_t* rep;            // [n] smallest original id of each group, by name
+  uint2* pairs;            // [n] (group name, original id | kRepBit) per position
+  uint32_t* rep;           // [n] scratch of group_big_bucket: smallest id of a group, by name
   int32_t* cmap;           // [n] -1 for unused groups (used ones are set by the key sort's finalisation)
   uint32_t* uelems;        // [n][K+1] (record, group name) of every used group, in its span's slots
-  uint4* chunks;           // [chunks] (span start, used groups, groups, overflow)
-  uint32_t* range_sums;    // [3][ranges] zeroed: used groups, groups and overflow of each run of
-                           // chunks k_group_compact_hist takes (spread over many addresses: atomics
+  uint2* chunks;           // [chunks] (span start, used groups)
+  uint32_t* range_sums;    // [ranges] zeroed: used groups of each run of chunks
+                           // k_group_compact_hist takes (spread over many addresses: atomics
                            // on one address from every chunk would serialise)
   int64_t ranges;          // that kernel's grid (group_compact_ranges)
   int32_t* status;
@@ -124,6 +121,157 @@ constexpr int group_min_waves() {
                         : GroupShape<MESH ? K + 1 : K>::MIN_WAVES_PER_SIMD;
 }
 
+// Groups one bucket of any size that starts at position b0 (the last one of
+// a chunk, running past its window). The distinct records of the bucket hang
+// in chains off a table in `uelems`, of which the bucket's positions own two
+// words each (head of a chain, next of a node) until its elements are written
+// there; a node is the position of some copy and names its group. The record
+// at b0 is the likeliest one to have thousands of copies: its copies are told
+// by a comparison in registers and touch no table. Everything the
+// workgroup's waves tell each other through memory goes by agent-scope
+// atomics (L2), ordered by fences. Chains are only ever prepended to, so a
+// failed insertion re-reads what was added and retries. Bound: one
+// workgroup's streaming rate, about 2,000 elements per 2 microseconds; a
+// value needs over a million copies before that is felt in a call. Returns
+// the number of used groups; their elements start at slot `upre`.
+template <int K, bool MESH, int BLOCK>
+__device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t upre, uint32_t* s_x) {
+  constexpr int S = K + 1;
+  constexpr int U = 4;  // elements in flight per thread
+  constexpr uint32_t kNone = 0xFFFFFFFFu, kUsedBit = 0x80000000u;
+  constexpr int32_t kUsedMark = -2;
+  const int tid = threadIdx.x;
+  const int64_t n = a.n;
+  uint32_t mesh = 0;
+  if constexpr (MESH) mesh = mesh_of(a.mesh_off, a.nmesh, b0, a.mesh_tab);
+  // bucket and hash of the element at a position (all of one mesh: buckets
+  // belong to meshes, and a mesh's positions are its vertex range)
+  auto hash_of = [&](const uint32_t(&e)[S]) {
+    if constexpr (MESH) return hash_mesh_words<K>(mesh, e);
+    else return hash_words<K>(e);
+  };
+  const int64_t lim = MESH ? min(n, a.mesh_off[mesh + 1]) : n;
+  auto bucket_of = [&](uint32_t h) {
+    if constexpr (MESH) return mesh_bucket(a.mesh_buckets, mesh, h);
+    else return h & a.bucket_mask;
+  };
+  uint32_t hot[S];
+  load_words<S>(a.elems + b0 * S, hot);
+  const uint32_t bucket = bucket_of(hash_of(hot));
+  // ---- end of the bucket
+  if (tid == 0) s_x[0] = kNone;
+  __syncthreads();
+  int64_t b1 = lim;
+  for (int64_t base = b0 + 1; base < lim; base += BLOCK * U) {
+    uint32_t first = kNone;
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t p = base + r * BLOCK + tid;
+      if (p < lim) {
+        uint32_t e[S];
+        load_words<S>(a.elems + p * S, e);
+        if (bucket_of(hash_of(e)) != bucket) first = min(first, uint32_t(p));
+      }
+    }
+    if (first != kNone) atomicMin(&s_x[0], first);
+    __syncthreads();
+    const uint32_t end = s_x[0];
+    __syncthreads();
+    if (end != kNone) {
+      b1 = end;
+      break;
+    }
+  }
+  const uint32_t cnt = uint32_t(b1 - b0);
+  uint32_t* const table = a.uelems + b0 * S;  // head of chain h: [h * S], next of node b0 + i: [i * S + 1]
+  for (uint32_t i = tid; i < cnt; i += BLOCK) lb_store(table + int64_t(i) * S, kNone);
+  if (tid == 0) {
+    lb_store(reinterpret_cast<uint32_t*>(a.cmap) + b0, uint32_t(-1));
+    s_x[1] = 0;                      // the hot group is used
+    s_x[2] = hot[K] & 0x7FFFFFFFu;   // its smallest id
+    s_x[3] = 0;                      // used groups
+  }
+  __threadfence();
+  __syncthreads();
+  uint32_t* const rep = a.rep;
+  uint32_t* const cm = reinterpret_cast<uint32_t*>(a.cmap);
+  // ---- every element finds or becomes its group's node
+  for (int64_t base = b0; base < b1; base += BLOCK * U) {
+    uint32_t e[U][S];
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t p = base + r * BLOCK + tid;
+      if (p < b1) load_words<S>(a.elems + p * S, e[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t p = base + r * BLOCK + tid;
+      if (p >= b1) continue;
+      const uint32_t id = e[r][K] & 0x7FFFFFFFu;
+      bool is_hot = true;
+#pragma unroll
+      for (int w = 0; w < K; ++w) is_hot = is_hot && e[r][w] == hot[w];
+      uint32_t node = uint32_t(b0);
+      if (is_hot) {
+        if ((e[r][K] & kUsedBit) && s_x[1] == 0u) s_x[1] = 1u;
+        if (id < s_x[2]) atomicMin(&s_x[2], id);
+      } else {
+        const uint32_t h = uint32_t((uint64_t(hash_of(e[r]) * 0x9E3779B1u) * cnt) >> 32);
+        uint32_t* const head = table + int64_t(h) * S;
+        uint32_t seen = kNone;  // nodes from here on are known not to match
+        uint32_t cur = lb_load(head);
+        node = kNone;
+        while (node == kNone) {
+          for (uint32_t q = cur; q != seen && q != kNone; q = lb_load(table + (int64_t(q) - b0) * S + 1)) {
+            bool eq = true;
+#pragma unroll
+            for (int w = 0; w < K; ++w) eq = eq && a.elems[int64_t(q) * S + w] == e[r][w];
+            if (eq) {
+              node = q;
+              break;
+            }
+          }
+          if (node != kNone) break;
+          seen = cur;
+          lb_store(table + (p - b0) * S + 1, cur);
+          lb_store(rep + p, id);
+          lb_store(cm + p, uint32_t(-1));
+          __threadfence();
+          const uint32_t was = atomicCAS(head, cur, uint32_t(p));
+          if (was == cur) node = uint32_t(p);
+          else cur = was;
+        }
+        if (lb_load(rep + node) > id) atomicMin(rep + node, id);
+        if ((e[r][K] & kUsedBit) && lb_load(cm + node) != uint32_t(kUsedMark)) lb_store(cm + node, uint32_t(kUsedMark));
+      }
+      a.pairs[p] = make_uint2(node, id);
+    }
+  }
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) {
+    lb_store(rep + b0, s_x[2]);
+    if (s_x[1]) lb_store(cm + b0, uint32_t(kUsedMark));
+    __threadfence();
+  }
+  __syncthreads();
+  // ---- representatives, and one element per used group (the table is no
+  // longer needed)
+  for (int64_t p = b0 + tid; p < b1; p += BLOCK) {
+    const uint2 pr = a.pairs[p];  // written by this thread
+    if (lb_load(cm + pr.x) != uint32_t(kUsedMark)) continue;
+    if (lb_load(rep + pr.x) == pr.y) a.pairs[p].y = pr.y | kRepBit;
+    if (pr.x != uint32_t(p)) continue;
+    const int64_t u = upre + atomicAdd(&s_x[3], 1u);
+    uint32_t e[S];
+    load_words<S>(a.elems + p * S, e);
+    e[K] = uint32_t(p);
+    store_words<S>(a.uelems + u * S, e);
+  }
+  __syncthreads();
+  return s_x[3];
+}
+
 template <int K, bool MESH>
 __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_waves<K, MESH>())) void k_group(
     GroupArgs a) {
@@ -141,13 +289,15 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
   __shared__ uint32_t s_keys[KW * WIN];     // window keys, word-major
   __shared__ uint32_t s_scratch[kScratch];  // buckets of the window, then the table
   __shared__ uint32_t s_cnt[2][IPT][WAVES];
-  __shared__ uint32_t s_sq, s_eq;
+  __shared__ uint32_t s_sq, s_eq, s_lq;
+  __shared__ uint32_t s_big[4];
 
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int64_t n = a.n;
   if (tid == 0) {
     s_sq = WIN;
     s_eq = WIN;
+    s_lq = 0;
   }
   const uint32_t tile = blockIdx.x;
   const int64_t c0 = int64_t(tile) * CHUNK;
@@ -204,8 +354,8 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
   }
   __syncthreads();
 
-  // ---- bucket starts: the first in the chunk (sq) and the first at or after
-  // position c1 (eq; position n counts as one)
+  // ---- bucket starts: the first (sq) and last (lq) in the chunk and the first
+  // at or after position c1 (eq; position n counts as one)
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const int q = i * BLOCK + tid;
@@ -213,14 +363,19 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
     if (q == 0 || pos > n) continue;
     const bool start = pos == 0 || pos == n || s_scratch[q] != s_scratch[q - 1];
     if (!start) continue;
-    if (q < qc1) atomicMin(&s_sq, uint32_t(q));
-    else atomicMin(&s_eq, uint32_t(q));
+    if (q < qc1) {
+      atomicMin(&s_sq, uint32_t(q));
+      atomicMax(&s_lq, uint32_t(q));
+    } else {
+      atomicMin(&s_eq, uint32_t(q));
+    }
   }
   __syncthreads();
-  const int sq = int(s_sq), eq = int(s_eq);
-  const bool owns = sq < qc1;
-  const bool over = owns && eq >= WIN;  // the chunk's last bucket runs past the window
-  const bool active = owns && !over;
+  const int sq = int(s_sq);
+  const bool active = sq < qc1;
+  // the chunk's last bucket runs past the window: it is grouped by itself below
+  const bool over = active && int(s_eq) >= WIN;
+  const int eq = over ? int(s_lq) : int(s_eq);
   for (int i = tid; i < TS; i += BLOCK) s_scratch[i] = kEmpty;  // buckets are no longer needed
   __syncthreads();
 
@@ -303,23 +458,9 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
     if (h) s_scratch[slot[i]] = (MESH ? q : gb) | (ub << 16);
   }
 
-  // ---- the chunk's record and its share of its run's sums; names start at
-  // the span's first position (batches: the first copy's position)
-  const uint32_t span0 = owns ? uint32_t(c0 - 1 + sq) : 0u;
-  if (tid == 0) {
-    const uint32_t u_own = active ? ut : 0u, g_own = active ? gt : 0u;
-    a.chunks[tile] = make_uint4(span0, u_own, g_own, over ? 1u : 0u);
-    // run of this chunk: the last w whose first chunk is at most `tile`
-    const int64_t T = int64_t(gridDim.x);
-    int64_t w = int64_t(tile) * a.ranges / T;
-    while (w + 1 < a.ranges && group_range_start(w + 1, T, a.ranges) <= tile) ++w;
-    while (w > 0 && group_range_start(w, T, a.ranges) > tile) --w;
-    if (u_own) atomicAdd(&a.range_sums[w], u_own);
-    if (g_own) atomicAdd(&a.range_sums[a.ranges + w], g_own);
-    if (over) atomicOr(&a.range_sums[2 * a.ranges + w], 1u);
-  }
+  // names start at the span's first position (batches: the first copy's position)
+  const uint32_t span0 = active ? uint32_t(c0 - 1 + sq) : 0u;
   __syncthreads();  // the ranks the heads left in the table are read below
-  if (!active) return;
   const uint32_t gpre = span0, upre = span0;
 
   // ---- outputs of the owned span
@@ -335,9 +476,8 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
       atomicMax(a.status, 7 /* MRX_ERR_INTERNAL */);
       continue;
     }
-    a.pairs[pos] = make_uint2(g, org);
+    a.pairs[pos] = make_uint2(g, org | ((uheadm >> i) & 1u ? kRepBit : 0u));
     if (!((headm >> i) & 1u)) continue;
-    a.rep[g] = int32_t(org);
     if ((uheadm >> i) & 1u) {
       const uint32_t u = upre + (ranks >> 16);
       if (int64_t(u) >= n) {
@@ -353,26 +493,38 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
       a.cmap[g] = -1;
     }
   }
+  uint32_t u_own = active ? ut : 0u;
+  if (over) u_own += group_big_bucket<K, MESH, BLOCK>(a, c0 - 1 + int(s_lq), int64_t(upre) + ut, s_big);
+  // ---- the chunk's record and its share of its run's sum
+  if (tid == 0) {
+    a.chunks[tile] = make_uint2(span0, u_own);
+    // run of this chunk: the last w whose first chunk is at most `tile`
+    const int64_t T = int64_t(gridDim.x);
+    int64_t w = int64_t(tile) * a.ranges / T;
+    while (w + 1 < a.ranges && group_range_start(w + 1, T, a.ranges) <= tile) ++w;
+    while (w > 0 && group_range_start(w, T, a.ranges) > tile) --w;
+    if (u_own) atomicAdd(&a.range_sums[w], u_own);
+  }
 }
 
-// Totals of the grouping (every workgroup adds up the runs' sums; workgroup 0
-// stores them: U, G, Control::path = some bucket did not fit, and the
-// element counts of the key sort). Then, on the grouping path, packs the used
-// groups' elements (slots span start + k of each chunk) densely into `dense`
-// at the chunk's used-group offset, and adds every key digit of them to the
-// LDS histograms (flushed once per workgroup). A workgroup takes a run of consecutive chunks, whose elements
+// Where there are too many vertices for the sample sort (split_kernels.hpp):
+// totals of the grouping (every workgroup adds up the runs' sums; workgroup 0
+// stores U), then the used groups' elements (slots span start + k of each
+// chunk) packed densely into `dense` at the chunk's used-group offset, with
+// every key digit of them added to the LDS histograms (flushed once per
+// workgroup). A workgroup takes a run of consecutive chunks, whose elements
 // are one contiguous stretch of `dense`; each thread maps its dense positions
 // back to (chunk, slot) with a search over the run's offsets in LDS.
 struct GroupCompactArgs {
   const uint32_t* sparse;     // [n][K+1]
-  const uint4* chunks;
-  const uint32_t* range_sums; // [3][ranges] (k_group)
+  const uint2* chunks;
+  const uint32_t* range_sums; // [ranges] (k_group)
   int64_t tiles;
   int64_t ranges;             // the grid
   int64_t n;
   uint32_t* dense;            // [U][K+1]
   uint32_t* hist;             // [P][2^D] global histograms
-  Control* ctl;               // totals of the grouping, set here by workgroup 0
+  Control* ctl;               // num_used, set here by workgroup 0
 };
 
 template <int K, int D, int BLOCK>
@@ -392,28 +544,17 @@ __global__ __launch_bounds__(BLOCK) void k_group_compact_hist(GroupCompactArgs a
   __shared__ uint32_t s_wave[BLOCK / kWave];
   const int tid = threadIdx.x;
   const int64_t w = blockIdx.x;
-  // totals, and the used groups of the runs before this one
-  uint32_t used = 0, before = 0, groups = 0, over = 0;
+  // the used groups of all runs, and of those before this one
+  uint32_t used = 0, before = 0;
   for (int64_t r = tid; r < a.ranges; r += BLOCK) {
     const uint32_t ur = a.range_sums[r];
     used += ur;
     before += r < w ? ur : 0u;
-    groups += a.range_sums[a.ranges + r];
-    over |= a.range_sums[2 * a.ranges + r];
   }
-  uint32_t total_used, first, total_groups;
+  uint32_t total_used, first;
   (void)block_exclusive_scan<BLOCK>(used, s_wave, &total_used);
   (void)block_exclusive_scan<BLOCK>(before, s_wave, &first);
-  (void)block_exclusive_scan<BLOCK>(groups, s_wave, &total_groups);
-  const bool fallback = __syncthreads_or(over != 0u) != 0;
-  if (w == 0 && tid == 0) {
-    a.ctl->num_used = int64_t(total_used);
-    a.ctl->num_groups = int64_t(total_groups);
-    a.ctl->path = fallback ? 1 : 0;
-    a.ctl->sort_count = fallback ? a.n : int64_t(total_used);
-    a.ctl->all_count = fallback ? a.n : 0;
-  }
-  if (fallback) return;  // the same in every workgroup
+  if (w == 0 && tid == 0) a.ctl->num_used = int64_t(total_used);
   const int64_t t0 = group_range_start(w, a.tiles, a.ranges);
   const int64_t t1 = group_range_start(w + 1, a.tiles, a.ranges);
   const int nc = int(t1 - t0);  // <= kCompactMaxChunks (group_compact_ranges)
@@ -422,7 +563,7 @@ __global__ __launch_bounds__(BLOCK) void k_group_compact_hist(GroupCompactArgs a
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int i = tid * PER + j;
-    uint4 c = make_uint4(0, 0, 0, 0);
+    uint2 c = make_uint2(0, 0);
     if (i < nc) c = a.chunks[t0 + i];
     cnt[j] = c.y;
     sum += c.y;
@@ -475,13 +616,11 @@ __global__ __launch_bounds__(BLOCK) void k_group_compact_hist(GroupCompactArgs a
   flush_histograms<WORDS, BLOCK>(s_h, a.hist);
 }
 
-// Plan of the key sort that follows the grouping: it reads buf[0], which
-// holds the packed used groups' elements when the grouping succeeded, else
-// all N hash-ordered elements; passes whose digit is the same for every
-// element (dead, from the bucket scan) are skipped. One thread.
-static __global__ void k_group_sort_plan(SortBuffers b, const Control* ctl) {
+// Plan of the LSD key sort that follows the packing: it reads buf[0], which
+// holds the packed elements; passes whose digit is the same for every element
+// (dead, from the bucket scan) are skipped. One thread.
+static __global__ void k_group_sort_plan(SortBuffers b) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  (void)ctl;
   const uint32_t* dead = b.plan + b.passes + 1;
   uint32_t in = 0u;
   for (int p = 0; p < b.passes; ++p) {
@@ -492,16 +631,13 @@ static __global__ void k_group_sort_plan(SortBuffers b, const Control* ctl) {
   b.plan[b.passes] = in;
 }
 
-// After the key sort of the used groups: sorted position c is output vertex
-// c (Section 2, Step 3 compacts the sorted array). Writes the record, the
-// representative, cmap[group] = c, and U. Runs only when the grouping
-// succeeded.
+// After an LSD key sort of the used groups: sorted position c is output
+// vertex c (Section 2, Step 3 compacts the sorted array). Writes the record,
+// cmap[group] = c, and U.
 struct FinalizeArgs {
-  SortBuffers bufs;        // sorted(): [U][K+1] (record, group id)
-  const int32_t* rep;      // [G]
-  int32_t* cmap;           // [G]
+  SortBuffers bufs;        // sorted(): [U][K+1] (record, group name)
+  int32_t* cmap;           // [n]
   uint32_t* out_vtx;       // [U][K]
-  int32_t* new2old;        // [U], nullable
   int64_t* out_num;        // nullable
   int64_t cap;             // n
   Control* ctl;
@@ -511,7 +647,6 @@ struct FinalizeArgs {
 template <int K>
 __global__ __launch_bounds__(256) void k_group_finalize(FinalizeArgs a) {
   constexpr int S = K + 1;
-  if (gate_closed(kGateGrouped, a.ctl)) return;
   const int64_t u = a.ctl->num_used;
   if (blockIdx.x == 0 && threadIdx.x == 0 && a.out_num) *a.out_num = u;
   const uint32_t* sorted = a.bufs.sorted();
@@ -526,7 +661,6 @@ __global__ __launch_bounds__(256) void k_group_finalize(FinalizeArgs a) {
       atomicMax(a.status, 7 /* MRX_ERR_INTERNAL */);
       continue;
     }
-    if (a.new2old) a.new2old[c] = a.rep[g];
     a.cmap[g] = int32_t(c);
   }
 }

@@ -34,16 +34,15 @@ __global__ void k_fill_zero(uint4* __restrict__ p, int64_t n16, int32_t* status,
 // from cmap at the first sorted position of mesh b (a head, since heads
 // break at mesh starts).
 __global__ void k_batch_offsets(const int64_t* __restrict__ vtx_off, int32_t nmesh, SortBuffers bufs,
-                                const uint2* pairs_in, const int32_t* __restrict__ cmap, const Control* ctl,
-                                const int64_t* __restrict__ total_used, int64_t n, int32_t gate,
+                                const int32_t* __restrict__ cmap, const Control* ctl,
+                                const int64_t* __restrict__ total_used, int64_t n,
                                 int64_t* __restrict__ out_off) {
-  if (gate_closed(gate, ctl)) return;
   const int32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b > nmesh) return;
   const int64_t p = vtx_off[b];
   int64_t r = *total_used;
   if (b < nmesh && p >= 0 && p < n) {
-    const uint2* pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
+    const uint2* pairs = reinterpret_cast<const uint2*>(bufs.spare());
     const uint32_t g = pairs[p].x;
     if (int64_t(g) < ctl->num_groups) {
       const int32_t c = cmap[g];
@@ -53,16 +52,14 @@ __global__ void k_batch_offsets(const int64_t* __restrict__ vtx_off, int32_t nme
   out_off[b] = r;
 }
 
-// Output offsets of a batch after its hash grouping: the used groups'
-// elements (record, name), packed densely before the key sort, are in order
-// of their names, the sorted positions of the groups' first copies, which
-// lie in their mesh's vertex range; so mesh b's outputs start at the number
-// of packed elements whose name is below vtx_off[b] (a binary search per
-// mesh). The key sort by (mesh id, record) keeps the meshes in that order.
+// Output offsets of a batch after its hash grouping, from a list in mesh
+// order of group names, which lie in their mesh's vertex range (the last word
+// of every `stride`): those of the packed used groups before an LSD key sort,
+// or those of the output vertices. Mesh b's outputs start at the
+// number of entries below vtx_off[b] (a binary search per mesh).
 __global__ void k_batch_offsets_dense(const uint32_t* __restrict__ dense, int32_t stride, const Control* ctl,
                                       const int64_t* __restrict__ vtx_off, int32_t nmesh,
                                       int64_t* __restrict__ out_off) {
-  if (gate_closed(kGateGrouped, ctl)) return;
   const int32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b > nmesh) return;
   const int64_t u = ctl->num_used;
@@ -492,23 +489,163 @@ mrx_status validate_single(const void* vtx, int64_t num_vtx, int32_t vtx_bytes, 
   return MRX_OK;
 }
 
+// Order of the used groups by record after the grouping (for a batch by (mesh
+// id, record)): the sample sort, for up to kSplitMax vertices, else an LSD
+// sort of the packed elements. Both leave the output records, cmap and U.
+struct OrderArgs {
+  uint32_t* X;               // [n][K+1], free
+  uint32_t* C;               // [n][K+1], the used groups' elements in their chunks' slots
+  uint32_t* scratch;         // [n * K] words
+  const uint2* chunks;
+  const uint32_t* range_sums;
+  int64_t ranges;
+  int32_t* cmap;
+  uint32_t* out_vtx;
+  int64_t* out_num;          // nullable
+  Control* ctl;
+  int32_t* status;
+  uint32_t* hist;            // LSD sort: zeroed histograms, plan, look-back words, tile counters
+  uint32_t* plan;
+  uint64_t* lookback;
+  bool wide;
+  uint32_t* counter;         // nullable
+  int gp;                    // passes of the call so far
+  const int64_t* mesh_off;   // batches
+  const int32_t* mesh_tab;
+  int32_t nmesh;
+  int64_t* out_off;
+};
+
+// The sample sort's buckets and samples are sized for tens of millions of
+// used values: with kMaxBuckets buckets, 67M 12-byte values average two of
+// the sort kernel's capacities per bucket, where cutting buckets again still
+// costs less than twelve passes over the data.
+constexpr int64_t kSplitMax = int64_t(1) << 26;
+bool split_applies(const SortVariant& v, const Layout& L, int64_t n, int K) {
+  const int64_t runs = group_compact_ranges(L.tiles_group);
+  const SplitSort& sp = L.mesh_hash ? v.split_mesh : v.split;
+  return n <= kSplitMax && L.tiles_group <= runs * kSplitMaxChunks && sp.scratch(n, runs).words <= n * int64_t(K);
+}
+
+void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, const OrderArgs& o, hipStream_t s) {
+  const bool mesh = L.mesh_hash;
+  if (split_applies(v, L, n, K)) {
+    const SplitSort& sp = mesh ? v.split_mesh : v.split;
+    const SplitScratch at = sp.scratch(n, o.ranges);
+    SplitArgs a{};
+    a.sparse = o.C;
+    a.chunks = o.chunks;
+    a.range_sums = o.range_sums;
+    a.tiles = L.tiles_group;
+    a.runs = o.ranges;
+    a.n = n;
+    a.samples = o.scratch + at.samples;
+    a.splitters = o.scratch + at.splitters;
+    a.counts = o.scratch + at.counts;
+    a.starts = o.scratch + at.starts;
+    a.run_base = o.scratch + at.run_base;
+    a.digits = reinterpret_cast<uint16_t*>(o.scratch + at.digits);
+    a.dense = o.X;
+    a.cmap = o.cmap;
+    a.out_vtx = o.out_vtx;
+    a.order = o.C;  // free once scattered
+    a.out_num = o.out_num;
+    a.ctl = o.ctl;
+    a.mesh_off = o.mesh_off;
+    a.mesh_tab = o.mesh_tab;
+    a.nmesh = o.nmesh;
+    prof_mark("split_sample", s);
+    sp.sample(a, s);
+    if (sp.ranked(n)) {
+      prof_mark("split_rank", s);
+      sp.rank(a, s);
+    }
+    prof_mark("split_count", s);
+    sp.count(a, s);
+    prof_mark("split_scatter", s);
+    sp.scatter(a, s);
+    prof_mark("split_sort", s);
+    sp.sort(a, s);
+    if (mesh) {
+      prof_mark("batch_offsets", s);
+      hipLaunchKernelGGL(k_batch_offsets_dense, dim3((o.nmesh + 1 + 255) / 256), dim3(256), 0, s,
+                         static_cast<const uint32_t*>(a.order), 1, static_cast<const Control*>(o.ctl),
+                         o.mesh_off, o.nmesh, o.out_off);
+    }
+    return;
+  }
+  const int P = L.P_key + (mesh ? L.P_mesh : 0);
+  uint32_t* const lb32[2] = {reinterpret_cast<uint32_t*>(o.lookback),
+                             reinterpret_cast<uint32_t*>(o.lookback) + size_t(L.tiles_sort) * v.radix()};
+  const SortBuffers sb{{o.X, o.C}, o.plan, P};
+  const GroupCompactArgs gc{o.C, o.chunks, o.range_sums, L.tiles_group, o.ranges, n, o.X, o.hist, o.ctl};
+  prof_mark("compact_histogram", s);
+  v.group_compact_hist(gc, s);
+  if (mesh) {
+    prof_mark("batch_offsets", s);
+    hipLaunchKernelGGL(k_batch_offsets_dense, dim3((o.nmesh + 1 + 255) / 256), dim3(256), 0, s,
+                       static_cast<const uint32_t*>(o.X), int32_t(K + 1), static_cast<const Control*>(o.ctl),
+                       o.mesh_off, o.nmesh, o.out_off);
+    prof_mark("mesh_histogram", s);
+    v.mesh_hist(o.out_off, o.nmesh, L.P_mesh, o.hist + size_t(L.P_key) * v.radix(), s);
+  }
+  prof_mark("scan_buckets", s);
+  v.scan(o.hist, P, n, &o.ctl->num_used, o.plan + P + 1, s);
+  prof_mark("sort_plan", s);
+  hipLaunchKernelGGL(k_group_sort_plan, dim3(1), dim3(64), 0, s, sb);
+  int gp = o.gp;
+  for (int p = 0; p < P; ++p, ++gp) {
+    SortPassArgs a{};
+    a.bufs = sb;
+    a.pass = p;
+    a.bucket_base = o.hist + size_t(p) * v.radix();
+    a.lookback = o.wide ? static_cast<void*>(o.lookback) : static_cast<void*>(lb32[gp & 1]);
+    a.lookback_next = lb32[(gp + 1) & 1];
+    a.tile_counter = o.counter ? o.counter + p : nullptr;
+    a.ctl = o.ctl;
+    a.status = o.status;
+    a.n = n;
+    a.n_dev = &o.ctl->num_used;
+    a.mesh_off = o.mesh_off;
+    a.mesh_tab = o.mesh_tab;
+    a.nmesh = o.nmesh;
+    a.tag = uint32_t(gp + 1);
+    int mode = kPassKey;
+    if (p < L.P_key) {
+      set_digit(a, K, p * v.D);
+    } else {
+      a.shift = (p - L.P_key) * v.D;
+      mode = kPassMesh;
+    }
+    prof_mark(mode == kPassMesh ? "onesweep_mesh" : "onesweep", s);
+    v.pass(a, mode, o.wide, L.tiles_sort, s);
+  }
+  FinalizeArgs fa{};
+  fa.bufs = sb;
+  fa.cmap = o.cmap;
+  fa.out_vtx = o.out_vtx;
+  fa.out_num = o.out_num;
+  fa.cap = n;
+  fa.ctl = o.ctl;
+  fa.status = o.status;
+  prof_mark("finalize", s);
+  v.finalize(fa, grid_for(n, 256, 4096), s);
+}
+
 // The hash-grouping launch sequence of one mesh (see group_kernels.hpp):
 //   Step 1 (marking, by vertex bands or by scattered stores) with the
 //   hash-digit histograms; stable sort of (record, id | used << 31) by
-//   P_hash hash digits into X; grouping of each hash bucket in LDS (pairs
+//   P_hash hash digits into X; grouping of each hash bucket (pairs
 //   (group, id) into Y, one (record, group) element per used group into its
-//   chunk's slots of C); the totals and, on the grouping path, the used
-//   groups' elements packed into X with their key-digit histograms; key sort
-//   of X (the used groups, or, if a bucket did not fit, all N hash-ordered
-//   elements); then either the finalisation (output records,
-//   representatives, group -> new id) or, on the fallback path, Section 2's
-//   flag scan and compaction; Step 4 (old2new and the index remap, by
-//   vertex bands or by scattered accesses) is shared.
+//   chunk's slots of C); order of the used groups by record, with the output
+//   records and the map from group to new id (order_used_groups); Step 4
+//   (old2new, with new2old, and the index remap, by vertex bands or by
+//   scattered accesses).
 // Buffers: A and B hold the hash passes (X = the last one written, Y = the
 // other), C the used groups' slots (before the grouping: Step 1's index
-// partition when only the marking goes by bands); the key sort alternates
-// between X and C starting from X; by bands, Step 4 then partitions the
-// pairs into X and puts the index entries' new ids in C.
+// partition when only the marking goes by bands); the ordering works in X and
+// C; by bands, Step 4 then partitions the pairs into X and puts the index
+// entries' new ids in C.
 mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, int64_t num_vtx,
                        int32_t vtx_bytes, const int32_t* idx, int64_t num_elems, int32_t arity,
                        const int64_t* live_elems, void* out_vtx, int32_t* out_idx, int32_t* old2new,
@@ -527,8 +664,7 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   uint32_t* plan_hash = reinterpret_cast<uint32_t*>(ws + L.plan_hash);
   uint32_t* dead_hash = reinterpret_cast<uint32_t*>(ws + L.dead_hash);
   uint64_t* lookback = reinterpret_cast<uint64_t*>(ws + L.lookback);
-  uint64_t* scan_lookback = reinterpret_cast<uint64_t*>(ws + L.scan_lookback);
-  uint4* group_chunks = reinterpret_cast<uint4*>(ws + L.group_chunks);
+  uint2* group_chunks = reinterpret_cast<uint2*>(ws + L.group_chunks);
   uint32_t* group_range_sums = reinterpret_cast<uint32_t*>(ws + L.group_ranges);
   const int64_t group_ranges = group_compact_ranges(L.tiles_group);
   const bool wide = wide_lookback(n, tuning);
@@ -536,10 +672,8 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   uint32_t* const lb32[2] = {reinterpret_cast<uint32_t*>(lookback),
                              reinterpret_cast<uint32_t*>(lookback) + size_t(L.tiles_sort) * v.radix()};
   uint8_t* used_v = reinterpret_cast<uint8_t*>(ws + L.used_v);
-  uint8_t* used_g = reinterpret_cast<uint8_t*>(ws + L.used_g);
   uint32_t* buf[3] = {reinterpret_cast<uint32_t*>(ws + L.buf_a), reinterpret_cast<uint32_t*>(ws + L.buf_b),
                       reinterpret_cast<uint32_t*>(ws + L.buf_c)};
-  uint32_t* uniq = reinterpret_cast<uint32_t*>(ws + L.uniq);
   int32_t* rep = reinterpret_cast<int32_t*>(ws + L.rep);
   int32_t* cmap = reinterpret_cast<int32_t*>(ws + L.cmap);
   int32_t* status = dev_status;
@@ -618,7 +752,7 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
     g.n = n;
     g.bucket_mask = ph * v.D >= 32 ? 0xFFFFFFFFu : (1u << (ph * v.D)) - 1u;
     g.pairs = pairs;
-    g.rep = rep;
+    g.rep = reinterpret_cast<uint32_t*>(rep);
     g.cmap = cmap;
     g.uelems = buf[2];
     g.chunks = group_chunks;
@@ -628,89 +762,31 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
     prof_mark("group", s);
     v.group(g, L.tiles_group, s);
 
-    // key sort of X: the used groups' elements packed from C (or, on the
-    // fallback path, all N hash-ordered elements)
-    const SortBuffers sbk{{X, buf[2]}, plan, L.P_key};
-    const GroupCompactArgs gc{buf[2], group_chunks, group_range_sums, L.tiles_group, group_ranges, n, X, hist, ctl};
-    prof_mark("compact_histogram", s);
-    v.group_compact_hist(gc, s);
-    const HistArgs ha{{X, X}, nullptr, n, &ctl->all_count, hist};
-    prof_mark("histogram", s);
-    v.elem_hist(ha, s);
-    prof_mark("scan_buckets", s);
-    v.scan(hist, L.P_key, n, &ctl->sort_count, plan + L.P_key + 1, s);
-    prof_mark("sort_plan", s);
-    hipLaunchKernelGGL(k_group_sort_plan, dim3(1), dim3(64), 0, s, sbk, static_cast<const Control*>(ctl));
-    for (int p = 0; p < L.P_key; ++p, ++gp) {
-      SortPassArgs a{};
-      a.bufs = sbk;
-      a.pass = p;
-      a.bucket_base = hist + size_t(p) * v.radix();
-      a.lookback = wide ? static_cast<void*>(lookback) : static_cast<void*>(lb32[gp & 1]);
-      a.lookback_next = lb32[(gp + 1) & 1];
-      a.tile_counter = next_counter();
-      a.ctl = ctl;
-      a.status = status;
-      a.n = n;
-      a.n_dev = &ctl->sort_count;
-      set_digit(a, K, p * v.D);
-      a.tag = uint32_t(gp + 1);
-      prof_mark("onesweep", s);
-      v.pass(a, kPassKey, wide, L.tiles_sort, s);
-    }
-    // grouping path: sorted position = new id
-    FinalizeArgs fa{};
-    fa.bufs = sbk;
-    fa.rep = rep;
-    fa.cmap = cmap;
-    fa.out_vtx = static_cast<uint32_t*>(out_vtx);
-    fa.new2old = new2old;
-    fa.out_num = out_num_vtx;
-    fa.cap = n;
-    fa.ctl = ctl;
-    fa.status = status;
-    prof_mark("finalize", s);
-    v.finalize(fa, grid_for(n, 256, 4096), s);
-    // fallback path: Section 2's flags, scans and compaction over all of X
-    FlagScanArgs f{};
-    f.bufs = sbk;
-    f.n = n;
-    f.uniq = uniq;
-    f.rep = rep;
-    f.used_g = used_g;
-    f.lookback = scan_lookback;
-    f.tile_counter = next_counter();
-    f.ctl = ctl;
-    f.status = status;
-    f.tag = uint32_t(gp + 1);
-    f.pairs = pairs;
-    f.gate = kGateSortAll;
-    prof_mark("flag_scan", s);
-    v.flag_scan(f, false, L.tiles_scan, s);
-    CompactArgs c{};
-    c.used_g = used_g;
-    c.uniq = uniq;
-    c.rep = rep;
-    c.K = K;
-    c.out_vtx = static_cast<uint32_t*>(out_vtx);
-    c.new2old = new2old;
-    c.cmap = cmap;
-    c.out_num = out_num_vtx;
-    c.cap = n;
-    c.lookback = scan_lookback;
-    c.tile_counter = next_counter();
-    c.ctl = ctl;
-    c.status = status;
-    c.tag = uint32_t(gp + 2);
-    c.gate = kGateSortAll;
-    prof_mark("compact", s);
-    hipLaunchKernelGGL((k_compact<kScanBlock, kScanIpt>), dim3(L.tiles_scan), dim3(kScanBlock), 0, s, c);
-    // both paths: Step 4's map (and, by bands, the remap)
+    OrderArgs o{};
+    o.X = X;
+    o.C = buf[2];
+    o.scratch = reinterpret_cast<uint32_t*>(ws + L.uniq);
+    o.chunks = group_chunks;
+    o.range_sums = group_range_sums;
+    o.ranges = group_ranges;
+    o.cmap = cmap;
+    o.out_vtx = static_cast<uint32_t*>(out_vtx);
+    o.ctl = ctl;
+    o.status = status;
+    o.hist = hist;
+    o.plan = plan;
+    o.lookback = lookback;
+    o.wide = wide;
+    o.counter = claimed ? counters + counter : nullptr;
+    o.gp = gp;
+    o.out_num = out_num_vtx;
+    order_used_groups(v, L, n, K, o, s);
+    // Step 4's map (and, by bands, the remap)
     if (bp.mode == kMarkAndMap) {
       // X and C are free again: X takes the partitioned pairs, C the new ids
       // of the index entries
       const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
-                            reinterpret_cast<uint2*>(X), ptable, status};
+                            reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0};
       prof_mark("pair_partition", s);
       launch_pair_partition(pa, s);
       const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
@@ -726,7 +802,8 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
     }
     prof_mark("old2new", s);
     hipLaunchKernelGGL((k_scatter_old2new<false>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
-                       sbk, static_cast<const uint2*>(pairs), cmap, n, nullptr, nullptr, 0, nullptr, old2new);
+                       SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs), cmap, n, nullptr,
+                       nullptr, 0, nullptr, old2new, new2old);
   }
   // Step 4: remap the index array
   if (m > 0) {
@@ -910,7 +987,8 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
     }
     prof_mark("old2new", s);
     hipLaunchKernelGGL((k_scatter_old2new<false>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
-                       sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0, nullptr, old2new);
+                       sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0, nullptr, old2new,
+                       static_cast<int32_t*>(nullptr));
   }
   // Step 4: remap the index array
   if (m > 0) {
@@ -926,15 +1004,11 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
 // vertices told apart by (mesh id, record). The hash digits are those of a
 // bucket of the vertex's mesh (each mesh owns a range of buckets, in mesh
 // order), so the hash-ordered elements are grouped by mesh; the grouping
-// compares (mesh id, record) in LDS and names each group by the sorted
-// position of its first copy, which lies in its mesh's vertex range. The
-// packed used elements are thus in mesh order, which gives the output
-// offsets, and the key sort of the used values adds the mesh-id passes of
-// the batched sort-all path (the mesh of an element is that of its name).
-// New ids are numbered over the whole batch and made mesh-local by the
-// old2new scatter and the new2old pass. A bucket that does not fit makes the
-// device sort all N hash-ordered elements by (mesh id, record) instead and
-// finish with the batched flags, scans and compaction.
+// compares (mesh id, record) and names each group by a sorted position of
+// one of its copies, which lies in its mesh's vertex range; the used groups
+// are ordered by (mesh id, record), the mesh of an element being that of its
+// name. New ids are numbered over the whole batch and made mesh-local by the
+// old2new scatter.
 mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void* vtx, const int64_t* vtx_offsets,
                                int64_t n, int32_t vtx_bytes, const int32_t* idx, const int64_t* elem_offsets,
                                int64_t total_elems, int32_t arity, int32_t num_meshes, void* out_vtx,
@@ -943,7 +1017,6 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   const int K = vtx_bytes / 4;
   const int64_t m = total_elems * arity;
   const int ph = L.P_hash;
-  const int P = L.P_key + L.P_mesh;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream_);
   char* ws = static_cast<char*>(workspace);
   Control* ctl = reinterpret_cast<Control*>(ws + L.ctl);
@@ -954,8 +1027,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   uint32_t* plan_hash = reinterpret_cast<uint32_t*>(ws + L.plan_hash);
   uint32_t* dead_hash = reinterpret_cast<uint32_t*>(ws + L.dead_hash);
   uint64_t* lookback = reinterpret_cast<uint64_t*>(ws + L.lookback);
-  uint64_t* scan_lookback = reinterpret_cast<uint64_t*>(ws + L.scan_lookback);
-  uint4* group_chunks = reinterpret_cast<uint4*>(ws + L.group_chunks);
+  uint2* group_chunks = reinterpret_cast<uint2*>(ws + L.group_chunks);
   uint32_t* group_range_sums = reinterpret_cast<uint32_t*>(ws + L.group_ranges);
   const int64_t group_ranges = group_compact_ranges(L.tiles_group);
   const bool wide = wide_lookback(n, tuning);
@@ -963,10 +1035,8 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   uint32_t* const lb32[2] = {reinterpret_cast<uint32_t*>(lookback),
                              reinterpret_cast<uint32_t*>(lookback) + size_t(L.tiles_sort) * v.radix()};
   uint8_t* used_v = reinterpret_cast<uint8_t*>(ws + L.used_v);
-  uint8_t* used_g = reinterpret_cast<uint8_t*>(ws + L.used_g);
   uint32_t* buf[3] = {reinterpret_cast<uint32_t*>(ws + L.buf_a), reinterpret_cast<uint32_t*>(ws + L.buf_b),
                       reinterpret_cast<uint32_t*>(ws + L.buf_c)};
-  uint32_t* uniq = reinterpret_cast<uint32_t*>(ws + L.uniq);
   int32_t* rep = reinterpret_cast<int32_t*>(ws + L.rep);
   int32_t* cmap = reinterpret_cast<int32_t*>(ws + L.cmap);
   int32_t* vtab = reinterpret_cast<int32_t*>(ws + L.vtx_tab);
@@ -1038,7 +1108,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   g.elems = X;
   g.n = n;
   g.pairs = pairs;
-  g.rep = rep;
+  g.rep = reinterpret_cast<uint32_t*>(rep);
   g.cmap = cmap;
   g.uelems = buf[2];
   g.chunks = group_chunks;
@@ -1052,119 +1122,35 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   prof_mark("group", s);
   v.group_mesh(g, L.tiles_group, s);
 
-  // key sort of X by (mesh id, record): the used groups' (record, name)
-  // elements packed from C in name order (or, on the fallback path, all N
-  // hash-ordered (record, id) elements)
-  const SortBuffers sbk{{X, buf[2]}, plan, P};
-  const GroupCompactArgs gc{buf[2], group_chunks, group_range_sums, L.tiles_group, group_ranges, n, X, hist, ctl};
-  prof_mark("compact_histogram", s);
-  v.group_compact_hist(gc, s);
-  const HistArgs ha{{X, X}, nullptr, n, &ctl->all_count, hist};
-  prof_mark("histogram", s);
-  v.elem_hist(ha, s);
-  prof_mark("batch_offsets", s);
-  hipLaunchKernelGGL(k_batch_offsets_dense, dim3((num_meshes + 1 + 255) / 256), dim3(256), 0, s,
-                     static_cast<const uint32_t*>(X), int32_t(K + 1), static_cast<const Control*>(ctl), vtx_offsets,
-                     num_meshes, out_vtx_offsets);
-  prof_mark("mesh_histogram", s);
-  v.mesh_hist_path(out_vtx_offsets, vtx_offsets, ctl, num_meshes, L.P_mesh, hist + size_t(L.P_key) * v.radix(), s);
-  prof_mark("scan_buckets", s);
-  v.scan(hist, P, n, &ctl->sort_count, plan + P + 1, s);
-  prof_mark("sort_plan", s);
-  hipLaunchKernelGGL(k_group_sort_plan, dim3(1), dim3(64), 0, s, sbk, static_cast<const Control*>(ctl));
-  for (int p = 0; p < P; ++p, ++gp) {
-    SortPassArgs a{};
-    a.bufs = sbk;
-    a.pass = p;
-    a.bucket_base = hist + size_t(p) * v.radix();
-    a.lookback = wide ? static_cast<void*>(lookback) : static_cast<void*>(lb32[gp & 1]);
-    a.lookback_next = lb32[(gp + 1) & 1];
-    a.tile_counter = next_counter();
-    a.ctl = ctl;
-    a.status = status;
-    a.n = n;
-    a.n_dev = &ctl->sort_count;
-    a.mesh_off = vtx_offsets;
-    a.mesh_tab = vtab;
-    a.nmesh = num_meshes;
-    a.tag = uint32_t(gp + 1);
-    int mode = kPassKey;
-    if (p < L.P_key) {
-      set_digit(a, K, p * v.D);
-    } else {
-      a.shift = (p - L.P_key) * v.D;
-      mode = kPassMesh;
-    }
-    prof_mark(mode == kPassMesh ? "onesweep_mesh" : "onesweep", s);
-    v.pass(a, mode, wide, L.tiles_sort, s);
-  }
-  // grouping path: sorted position = new id over the whole batch
-  FinalizeArgs fa{};
-  fa.bufs = sbk;
-  fa.rep = rep;
-  fa.cmap = cmap;
-  fa.out_vtx = static_cast<uint32_t*>(out_vtx);
-  fa.new2old = new2old;
-  fa.out_num = nullptr;
-  fa.cap = n;
-  fa.ctl = ctl;
-  fa.status = status;
-  prof_mark("finalize", s);
-  v.finalize(fa, grid_for(n, 256, 4096), s);
-  // fallback path: the batched flags, scans and compaction over all of X
-  FlagScanArgs f{};
-  f.bufs = sbk;
-  f.n = n;
-  f.uniq = uniq;
-  f.rep = rep;
-  f.used_g = used_g;
-  f.lookback = scan_lookback;
-  f.tile_counter = next_counter();
-  f.ctl = ctl;
-  f.status = status;
-  f.mesh_off = vtx_offsets;
-  f.mesh_tab = vtab;
-  f.nmesh = num_meshes;
-  f.tag = uint32_t(gp + 1);
-  f.pairs = pairs;
-  f.gate = kGateSortAll;
-  prof_mark("flag_scan", s);
-  v.flag_scan(f, true, L.tiles_scan, s);
-  CompactArgs c{};
-  c.used_g = used_g;
-  c.uniq = uniq;
-  c.rep = rep;
-  c.K = K;
-  c.out_vtx = static_cast<uint32_t*>(out_vtx);
-  c.new2old = new2old;
-  c.cmap = cmap;
-  c.out_num = &ctl->num_used;
-  c.cap = n;
-  c.lookback = scan_lookback;
-  c.tile_counter = next_counter();
-  c.ctl = ctl;
-  c.status = status;
-  c.tag = uint32_t(gp + 2);
-  c.gate = kGateSortAll;
-  prof_mark("compact", s);
-  hipLaunchKernelGGL((k_compact<kScanBlock, kScanIpt>), dim3(L.tiles_scan), dim3(kScanBlock), 0, s, c);
-  prof_mark("batch_offsets", s);
-  hipLaunchKernelGGL(k_batch_offsets, dim3((num_meshes + 1 + 255) / 256), dim3(256), 0, s, vtx_offsets, num_meshes,
-                     sbk, static_cast<const uint2*>(pairs), static_cast<const int32_t*>(cmap),
-                     static_cast<const Control*>(ctl), static_cast<const int64_t*>(&ctl->num_used), n,
-                     int32_t(kGateSortAll), out_vtx_offsets);
+  OrderArgs o{};
+  o.X = X;
+  o.C = buf[2];
+  o.scratch = reinterpret_cast<uint32_t*>(ws + L.uniq);
+  o.chunks = group_chunks;
+  o.range_sums = group_range_sums;
+  o.ranges = group_ranges;
+  o.cmap = cmap;
+  o.out_vtx = static_cast<uint32_t*>(out_vtx);
+  o.ctl = ctl;
+  o.status = status;
+  o.hist = hist;
+  o.plan = plan;
+  o.lookback = lookback;
+  o.wide = wide;
+  o.counter = claimed ? counters + counter : nullptr;
+  o.gp = gp;
+  o.mesh_off = vtx_offsets;
+  o.mesh_tab = vtab;
+  o.nmesh = num_meshes;
+  o.out_off = out_vtx_offsets;
+  order_used_groups(v, L, n, K, o, s);
 
-  // both paths: Step 4's map made mesh-local, new2old made mesh-local, remap
+  // Step 4's map and new2old, both mesh-local, remap
   prof_mark("old2new", s);
   hipLaunchKernelGGL((k_scatter_old2new<true>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                      SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs), cmap, n,
                      vtx_offsets, static_cast<const int64_t*>(out_vtx_offsets), num_meshes,
-                     static_cast<const int32_t*>(vtab), old2new);
-  if (new2old) {
-    prof_mark("localize_new2old", s);
-    hipLaunchKernelGGL(k_localize_new2old, dim3(grid_for(n, 256)), dim3(256), 0, s, new2old, &ctl->num_used,
-                       vtx_offsets, num_meshes, static_cast<const int32_t*>(vtab));
-  }
+                     static_cast<const int32_t*>(vtab), old2new, new2old);
   if (m > 0) {
     prof_mark("remap", s);
     hipLaunchKernelGGL((k_remap<true>), dim3(rand_grid(m)), dim3(kRandBlock), 0, s, idx, m, arity, n, vtx_offsets,
@@ -1487,13 +1473,12 @@ mrx_status mrx_reindex_mesh_batched(const void* vtx, const int64_t* vtx_offsets,
     hipLaunchKernelGGL((k_compact<kScanBlock, kScanIpt>), dim3(L.tiles_scan), dim3(kScanBlock), 0, s, c);
     prof_mark("batch_offsets", s);
     hipLaunchKernelGGL(k_batch_offsets, dim3((num_meshes + 1 + 255) / 256), dim3(256), 0, s, vtx_offsets,
-                       num_meshes, sb, static_cast<const uint2*>(nullptr), static_cast<const int32_t*>(cmap),
-                       static_cast<const Control*>(ctl), static_cast<const int64_t*>(&ctl->num_used), n,
-                       int32_t(kGateAlways), out_vtx_offsets);
+                       num_meshes, sb, static_cast<const int32_t*>(cmap), static_cast<const Control*>(ctl),
+                       static_cast<const int64_t*>(&ctl->num_used), n, out_vtx_offsets);
     prof_mark("old2new", s);
     hipLaunchKernelGGL((k_scatter_old2new<true>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                        sb, static_cast<const uint2*>(nullptr), cmap, n, vtx_offsets, out_vtx_offsets, num_meshes,
-                       static_cast<const int32_t*>(vtab), old2new);
+                       static_cast<const int32_t*>(vtab), old2new, static_cast<int32_t*>(nullptr));
     if (new2old) {
       prof_mark("localize_new2old", s);
       hipLaunchKernelGGL(k_localize_new2old, dim3(grid_for(n, 256)), dim3(256), 0, s, new2old,
@@ -1502,9 +1487,9 @@ mrx_status mrx_reindex_mesh_batched(const void* vtx, const int64_t* vtx_offsets,
   } else {
     prof_mark("batch_offsets", s);
     hipLaunchKernelGGL(k_batch_offsets, dim3((num_meshes + 1 + 255) / 256), dim3(256), 0, s, vtx_offsets,
-                       num_meshes, SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(nullptr),
-                       static_cast<const int32_t*>(cmap), static_cast<const Control*>(ctl),
-                       static_cast<const int64_t*>(&ctl->num_used), n, int32_t(kGateAlways), out_vtx_offsets);
+                       num_meshes, SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const int32_t*>(cmap),
+                       static_cast<const Control*>(ctl), static_cast<const int64_t*>(&ctl->num_used), n,
+                       out_vtx_offsets);
   }
   if (m > 0) {
     prof_mark("remap", s);

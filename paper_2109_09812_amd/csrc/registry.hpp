@@ -10,6 +10,7 @@
 #include "group_kernels.hpp"
 #include "scan_kernels.hpp"
 #include "sort_kernels.hpp"
+#include "split_kernels.hpp"
 
 namespace mrx {
 
@@ -46,6 +47,16 @@ __global__ __launch_bounds__(BLOCK) void k_mark_histogram(MarkArgs ma, const uin
   }
 }
 
+struct SplitSort {
+  SplitScratch (*scratch)(int64_t n, int64_t runs) = nullptr;
+  bool (*ranked)(int64_t n) = nullptr;  // several blocks of samples are possible
+  void (*sample)(const SplitArgs&, hipStream_t) = nullptr;
+  void (*rank)(const SplitArgs&, hipStream_t) = nullptr;
+  void (*count)(const SplitArgs&, hipStream_t) = nullptr;
+  void (*scatter)(const SplitArgs&, hipStream_t) = nullptr;
+  void (*sort)(const SplitArgs&, hipStream_t) = nullptr;
+};
+
 struct SortVariant {
   int K = 0, D = 0, block = 0, ipt = 0;
   // one LSD pass over `grid` tiles; `wide` selects 64-bit tagged look-back
@@ -68,11 +79,9 @@ struct SortVariant {
                hipStream_t) = nullptr;
   // run-head flags + prefix sum + scatters over the sorted elements
   void (*flag_scan)(const FlagScanArgs&, bool batched, int64_t grid, hipStream_t) = nullptr;
-  // hash grouping: key-digit histograms of sort elements (buffer and count
-  // read on the device), hash-digit histograms of the records for `ph`
+  // hash grouping: hash-digit histograms of the records for `ph`
   // passes (with Step 1's marking when `mark` is given), the grouping kernel
-  // and the finalisation after the key sort of the used groups
-  void (*elem_hist)(const HistArgs&, hipStream_t) = nullptr;
+  // and the finalisation after an LSD key sort of the used groups
   void (*hash_hist)(const MarkArgs* mark, const uint32_t* vtx, int64_t n, int ph, uint32_t* hist,
                     hipStream_t) = nullptr;
   // Step 1's band marking (small bands, 256-thread blocks) in one launch
@@ -80,22 +89,22 @@ struct SortVariant {
   void (*band_mark_hash_hist)(const BandArgs& ba, const uint32_t* vtx, int64_t n, int ph, uint32_t* hist,
                               hipStream_t) = nullptr;
   void (*group)(const GroupArgs&, int64_t grid, hipStream_t) = nullptr;
-  // grouping path: dense copy of the used groups' elements + their key-digit
-  // histograms
+  // dense copy of the used groups' elements + their key-digit histograms
+  // (for the LSD key sort)
   void (*group_compact_hist)(const GroupCompactArgs&, hipStream_t) = nullptr;
   void (*finalize)(const FinalizeArgs&, int64_t grid, hipStream_t) = nullptr;
   int group_chunk = 0;           // sorted positions per grouping workgroup
   int group_target_bucket = 0;   // average bucket size the hash passes aim for
-  // hash grouping of a batch: bucket-digit histograms of (mesh id,
-  // record), the grouping by (mesh id, record), and the mesh-id digit
-  // histograms of the key sort that follows (k_mesh_histogram_path)
+  // sample sort of the used groups (split_kernels.hpp), by record or, for a
+  // batch, by (mesh id, record); `n` sizes the grids
+  SplitSort split, split_mesh;
+  // hash grouping of a batch: bucket-digit histograms of (mesh id, record)
+  // and the grouping by (mesh id, record)
   // (with Step 1's marking of the batch in the same launch when `mark` is given)
   void (*hash_mesh_hist)(const MarkArgs* mark, const uint32_t* vtx, int64_t n, const int64_t* off, int32_t nmesh,
                          const int32_t* tab, const uint2* mesh_buckets, int ph, uint32_t* hist,
                          hipStream_t) = nullptr;
   void (*group_mesh)(const GroupArgs&, int64_t grid, hipStream_t) = nullptr;
-  void (*mesh_hist_path)(const int64_t* off_grouped, const int64_t* off_all, const Control* ctl, int32_t nmesh,
-                         int32_t passes, uint32_t* hist, hipStream_t) = nullptr;
   int group_mesh_chunk = 0;
   int group_mesh_target_bucket = 0;
 

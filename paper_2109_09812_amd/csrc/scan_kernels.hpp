@@ -90,8 +90,6 @@ struct FlagScanArgs {
   const int32_t* mesh_tab; // batched: bucket table of mesh_off (mesh_of)
   int32_t nmesh;
   uint32_t tag;
-  uint2* pairs;            // nullable: receives the pairs instead of bufs.spare()
-  int32_t gate;            // Gate: run always, or only on one path of the hash grouping
 };
 
 template <int K, int BLOCK, int IPT, bool BATCHED>
@@ -104,13 +102,12 @@ __global__ __launch_bounds__(BLOCK) void k_flag_scan(FlagScanArgs a) {
   __shared__ uint32_t s_prefix;
 
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  if (gate_closed(a.gate, a.ctl)) return;  // the same for every workgroup
   const uint32_t fin = a.bufs.entry(a.bufs.passes);  // requested before the barrier
   const uint32_t tile = claim_tile(a.tile_counter, &s_tile);
   const int64_t n = a.n;
   const int64_t wave_base = int64_t(tile) * TILE + int64_t(wave) * (kWave * IPT) + lane;
   const uint32_t* sorted = a.bufs.buf[fin & 1u];
-  uint2* pairs = a.pairs ? a.pairs : reinterpret_cast<uint2*>(a.bufs.buf[(fin & 1u) ^ 1u]);
+  uint2* pairs = reinterpret_cast<uint2*>(a.bufs.buf[(fin & 1u) ^ 1u]);
 
   uint32_t id[IPT];
   uint32_t incl[IPT];   // heads at or before this element within the wave's (j, lane) order
@@ -228,7 +225,6 @@ struct CompactArgs {
   Control* ctl;
   int32_t* status;
   uint32_t tag;
-  int32_t gate;            // Gate: run always, or only on one path of the hash grouping
 };
 
 template <int BLOCK, int IPT>
@@ -240,7 +236,6 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
   __shared__ uint32_t s_prefix;
 
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  if (gate_closed(a.gate, a.ctl)) return;  // the same for every workgroup
   const uint32_t tile = claim_tile(a.tile_counter, &s_tile);
   const int64_t G = a.ctl->num_groups;
   if (int64_t(tile) * TILE >= G) return;  // whole block: tile is uniform
@@ -307,14 +302,16 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
 // output offset. A batch's pairs are in mesh order, mesh b's at positions
 // [vtx_off[b], vtx_off[b+1]) (sorted by (mesh id, record), or hash-ordered
 // with per-mesh bucket ranges), so the mesh of an element is that of its
-// position: one lookup for a tile inside one mesh.
+// position: one lookup for a tile inside one mesh. `new2old` (nullable)
+// receives the ids with kRepBit at their group's new id.
 template <bool BATCHED>
 __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs, const uint2* pairs_in,
                                                                 const int32_t* __restrict__ cmap, int64_t n,
                                                                 const int64_t* __restrict__ vtx_off,
                                                                 const int64_t* __restrict__ out_off,
                                                                 int32_t nmesh, const int32_t* __restrict__ vtx_tab,
-                                                                int32_t* __restrict__ old2new) {
+                                                                int32_t* __restrict__ old2new,
+                                                                int32_t* __restrict__ new2old) {
   constexpr int TILE = kRandBlock * kScatterItems;
   const uint2* __restrict__ pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
   __shared__ int32_t s_cmap[TILE];
@@ -354,23 +351,38 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
 #pragma unroll
   for (int it = 0; it < kScatterItems; ++it) {
     const int64_t off = int64_t(p[it].x) - int64_t(g0);
-    if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) c[it] = -1;
+    if (int64_t(p[it].x) >= n) c[it] = -1;
     else c[it] = (off >= 0 && off < span) ? s_cmap[off] : cmap[p[it].x];  // outside: only after a failed wait
   }
-  int64_t tile_off = 0;  // output offset of the tile's mesh, if it has one
+  int64_t tile_off = 0, tile_vtx = 0;  // output and vertex offsets of the tile's mesh, if it has one
   const bool one_mesh = BATCHED && s_mesh[0] == s_mesh[1];
   if constexpr (BATCHED) {
-    if (one_mesh) tile_off = out_off[s_mesh[0]];
+    if (one_mesh) {
+      tile_off = out_off[s_mesh[0]];
+      tile_vtx = vtx_off[s_mesh[0]];
+    }
   }
 #pragma unroll
   for (int it = 0; it < kScatterItems; ++it) {
-    if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) continue;  // past the end (or a failed wait)
+    const uint32_t id = p[it].y & ~kRepBit;
+    if (int64_t(p[it].x) >= n || int64_t(id) >= n) continue;  // past the end (or a failed wait)
     int32_t cc = c[it] < 0 ? -1 : c[it];
+    const bool rep = new2old && (p[it].y & kRepBit) && cc >= 0 && cc < n;
     if constexpr (BATCHED) {
-      if (cc >= 0)
-        cc -= int32_t(one_mesh ? tile_off : out_off[mesh_of(vtx_off, nmesh, base + it * kRandBlock, vtx_tab)]);
+      if (cc >= 0) {
+        int64_t off = tile_off, first = tile_vtx;
+        if (!one_mesh) {
+          const uint32_t b = mesh_of(vtx_off, nmesh, base + it * kRandBlock, vtx_tab);
+          off = out_off[b];
+          first = vtx_off[b];
+        }
+        if (rep) new2old[cc] = int32_t(int64_t(id) - first);
+        cc -= int32_t(off);
+      }
+    } else {
+      if (rep) new2old[cc] = int32_t(id);
     }
-    old2new[p[it].y] = cc;
+    old2new[id] = cc;
   }
 }
 

@@ -69,22 +69,11 @@ void launch_hist(const uint32_t* vtx, int64_t n, uint32_t* hist, hipStream_t s) 
     hipLaunchKernelGGL((k_histogram<KeyDigits<K, D>, K, D, K, B, GROUPS>), dim3(grid), dim3(B), 0, s, a);
 }
 
-// Key-digit histograms of sort elements (K + 1 words) whose buffer and count
-// are read on the device. The grid covers a.n (the capacity), capped at two
-// workgroups per CU: each workgroup then walks several chunks before it adds
-// its LDS histograms to the global ones once (with one chunk per workgroup
-// those additions, one per nonzero bin, cost more than the counting).
+// Grid cap of histograms whose workgroups walk several chunks before they
+// add their LDS histograms to the global ones once (with one chunk per
+// workgroup those additions, one per nonzero bin, cost more than the
+// counting): two workgroups per CU.
 constexpr int64_t kElemHistGrid = 512;
-
-template <int D>
-void launch_elem_hist(const HistArgs& a, hipStream_t s) {
-  constexpr int B = 256, GROUPS = kHistGroups;
-  constexpr int R = items_per_group(K + 1);
-  const int64_t per_block = int64_t(B) * GROUPS * R;
-  const int64_t grid = std::min<int64_t>((a.n + per_block - 1) / per_block, kElemHistGrid);
-  if (grid > 0)
-    hipLaunchKernelGGL((k_histogram<KeyDigits<K, D>, K, D, K + 1, B, GROUPS>), dim3(grid), dim3(B), 0, s, a);
-}
 
 // Hash-digit histograms of the records for ph passes, with Step 1's marking
 // in the same launch when there is something to mark.
@@ -230,15 +219,32 @@ void launch_group_mesh(const GroupArgs& a, int64_t grid, hipStream_t s) {
   if (grid > 0) hipLaunchKernelGGL((k_group<K, true>), dim3(grid), dim3(GroupShape<K + 1>::BLOCK), 0, s, a);
 }
 
-// Mesh-id digit histograms of a batch's key sort after its hash grouping:
-// per-mesh counts from the used values' offsets (grouping path) or the
-// vertex offsets (everything sorted).
-template <int D>
-void launch_mesh_hist_path(const int64_t* off_grouped, const int64_t* off_all, const Control* ctl, int32_t nmesh,
-                           int32_t passes, uint32_t* hist, hipStream_t s) {
-  if (nmesh <= 0 || passes <= 0) return;
-  hipLaunchKernelGGL((k_mesh_histogram_path<D>), dim3((nmesh + 255) / 256), dim3(256), 0, s, off_grouped, off_all,
-                     ctl, nmesh, passes, hist);
+// The sample sort of the used groups, grids sized for n of them.
+template <bool MESH>
+SplitSort make_split() {
+  constexpr int KW = K + (MESH ? 1 : 0);
+  using SH = SplitShape<KW>;
+  SplitSort p;
+  p.scratch = &split_scratch<KW>;
+  p.ranked = [](int64_t n) { return split_plan<KW>(n).samples > uint32_t(SH::SCAP); };
+  p.sample = [](const SplitArgs& a, hipStream_t s) {
+    const int64_t blocks = (int64_t(split_plan<KW>(a.n).samples) + SH::SCAP - 1) / SH::SCAP;
+    hipLaunchKernelGGL((k_split_sample<K, MESH>), dim3(std::max<int64_t>(1, blocks)), dim3(SH::BLOCK), 0, s, a);
+  };
+  p.rank = [](const SplitArgs& a, hipStream_t s) {
+    const int64_t grid = (int64_t(split_plan<KW>(a.n).samples) + 7) / 8;
+    if (grid > 0) hipLaunchKernelGGL((k_split_rank<K, MESH>), dim3(grid), dim3(256), 0, s, a);
+  };
+  p.count = [](const SplitArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((k_split_count<K, MESH>), dim3(a.runs), dim3(kSplitRunBlock), 0, s, a);
+  };
+  p.scatter = [](const SplitArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((k_split_scatter<K, MESH>), dim3(a.runs), dim3(kSplitRunBlock), 0, s, a);
+  };
+  p.sort = [](const SplitArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((k_split_sort<K, MESH>), dim3(split_plan<KW>(a.n).buckets), dim3(SH::BLOCK), 0, s, a);
+  };
+  return p;
 }
 
 void launch_finalize(const FinalizeArgs& a, int64_t grid, hipStream_t s) {
@@ -315,7 +321,6 @@ SortVariant make() {
   v.mesh_hist = &launch_mesh_hist<D>;
   v.scan = &launch_scan<D>;
   v.flag_scan = &launch_flag_scan;
-  v.elem_hist = &launch_elem_hist<D>;
   v.hash_hist = &launch_hash_hist<D>;
   v.band_mark_hash_hist = &launch_band_mark_hash_hist<D>;
   v.group = &launch_group;
@@ -324,7 +329,8 @@ SortVariant make() {
   v.group_chunk = GroupShape<K>::CHUNK;
   v.group_target_bucket = GroupShape<K>::TARGET_BUCKET;
   v.hash_mesh_hist = &launch_hash_mesh_hist<D>;
-  v.mesh_hist_path = &launch_mesh_hist_path<D>;
+  v.split = make_split<false>();
+  v.split_mesh = make_split<true>();
   v.group_mesh = &launch_group_mesh;
   v.group_mesh_chunk = GroupShape<K + 1>::CHUNK;
   v.group_mesh_target_bucket = GroupShape<K + 1>::TARGET_BUCKET;

@@ -318,23 +318,6 @@ __global__ void k_mesh_histogram(const int64_t* __restrict__ off, int32_t nmesh,
     atomicAdd(&hist[q * RADIX + ((uint32_t(b) >> (q * D)) & (RADIX - 1))], cnt);
 }
 
-// The same for the key sort of a batch after its hash grouping, which sorts
-// the used values (grouping path: per-mesh counts from their offsets
-// off_grouped) or every vertex (Control::path = 1: from off_all).
-template <int D>
-__global__ void k_mesh_histogram_path(const int64_t* __restrict__ off_grouped, const int64_t* __restrict__ off_all,
-                                      const Control* ctl, int32_t nmesh, int32_t mesh_passes,
-                                      uint32_t* __restrict__ hist) {
-  constexpr int RADIX = 1 << D;
-  const int32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nmesh) return;
-  const int64_t* off = __builtin_amdgcn_readfirstlane(ctl->path) == 0 ? off_grouped : off_all;
-  const uint32_t cnt = uint32_t(off[b + 1] - off[b]);
-  if (cnt == 0) return;
-  for (int q = 0; q < mesh_passes; ++q)
-    atomicAdd(&hist[q * RADIX + ((uint32_t(b) >> (q * D)) & (RADIX - 1))], cnt);
-}
-
 // Exclusive scan of each pass's RADIX counts, in place (one block per pass),
 // and dead[p] = 1 if one digit holds all n elements in pass p.
 template <int D, int BLOCK>
