@@ -9,6 +9,7 @@
 #include "band_kernels.hpp"
 #include "group_kernels.hpp"
 #include "scan_kernels.hpp"
+#include "small_kernels.hpp"
 #include "sort_kernels.hpp"
 #include "split_kernels.hpp"
 
@@ -95,6 +96,10 @@ struct SortVariant {
   void (*finalize)(const FinalizeArgs&, int64_t grid, hipStream_t) = nullptr;
   int group_chunk = 0;           // sorted positions per grouping workgroup
   int group_target_bucket = 0;   // average bucket size the hash passes aim for
+  // the whole re-index of a mesh of at most small_vertices vertices and
+  // small_entries index entries in one workgroup (small_kernels.hpp)
+  void (*small)(const SmallArgs&, hipStream_t) = nullptr;
+  int small_vertices = 0, small_entries = 0;
   // sample sort of the used groups (split_kernels.hpp), by record or, for a
   // batch, by (mesh id, record); `n` sizes the grids
   SplitSort split, split_mesh;

@@ -307,6 +307,10 @@ void launch_flag_scan(const FlagScanArgs& a, bool batched, int64_t grid, hipStre
     hipLaunchKernelGGL((k_flag_scan<K, kScanBlock, kScanIpt, false>), dim3(grid), dim3(kScanBlock), 0, s, a);
 }
 
+void launch_small(const SmallArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_small<K>), dim3(1), dim3(SmallShape<K>::BLOCK), 0, s, a);
+}
+
 template <int D, int BLOCK, int IPT>
 SortVariant make() {
   SortVariant v;
@@ -329,6 +333,9 @@ SortVariant make() {
   v.group_chunk = GroupShape<K>::CHUNK;
   v.group_target_bucket = GroupShape<K>::TARGET_BUCKET;
   v.hash_mesh_hist = &launch_hash_mesh_hist<D>;
+  v.small = &launch_small;
+  v.small_vertices = SmallShape<K>::CAP;
+  v.small_entries = SmallShape<K>::MAX_ENTRIES;
   v.split = make_split<false>();
   v.split_mesh = make_split<true>();
   v.group_mesh = &launch_group_mesh;
