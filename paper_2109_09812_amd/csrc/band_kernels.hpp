@@ -41,7 +41,13 @@ constexpr int kMaxBands = 1024;
 constexpr int kPairBlock = 512;
 constexpr int kPairItems = 32;
 constexpr int kPairTile = kPairBlock * kPairItems;  // 16384 pairs (128 KB staged)
+// Up to some million entries, tiles of a quarter of that: the partitions and
+// the remap of 4.2M entries would otherwise run on 128 workgroups, half the
+// GPU, one to a CU (index partition of 4.2M entries 44 -> 23 us).
+constexpr int kFineIdxItems = 16, kFineBandTile = kIdxPartBlock * kFineIdxItems;
+constexpr int kFinePairItems = 8, kFinePairTile = kPairBlock * kFinePairItems;
 constexpr int kMinBandShift = 12;                   // bands start 16-byte aligned
+constexpr int kMinFineShift = 8;
 constexpr int kMaxMarkShift = 19;                   // a band's bitmap: at most 64 KB
 constexpr int kMaxMapShift = 15;                    // a band's old2new slice: 128 KB
 constexpr int kPosShift = 17;                       // entry = pos << 17 | vertex - band start
@@ -58,7 +64,8 @@ struct BandArgs {
   int32_t nb;                  // ceil(n / 2^shift) <= kMaxBands
   int32_t vec;                 // idx is 16-byte aligned
   int32_t keep_pos;            // entries carry their position in the tile (shift <= kPosShift)
-  int64_t tiles;               // ceil(m / kBandTile)
+  int64_t tiles;               // ceil(m / tile size)
+  int32_t fine;                // tiles of kFineBandTile entries instead of kBandTile
   uint32_t* part;              // [m]
   uint32_t* table;             // [nb][tiles]
   uint32_t* tile_valid;        // [tiles], nullable: valid entries of each tile
@@ -70,8 +77,9 @@ __device__ __forceinline__ int64_t live_entries(const int64_t* live_elems, int64
   return live_elems ? min(m, *live_elems * arity) : m;
 }
 
-static __global__ __launch_bounds__(kIdxPartBlock) void k_band_partition(BandArgs a) {
-  constexpr int B = kIdxPartBlock, ITEMS = kIdxPartItems;
+template <int ITEMS>
+__global__ __launch_bounds__(kIdxPartBlock) void k_band_partition(BandArgs a) {
+  constexpr int B = kIdxPartBlock, kBandTile = B * ITEMS;
   static_assert(ITEMS % 4 == 0, "entries are loaded four at a time");
   static_assert(kBandTile <= (1 << (32 - kPosShift)), "positions fit above the vertex offset");
   __shared__ uint32_t s_cnt[kMaxBands];
@@ -150,41 +158,80 @@ __device__ __forceinline__ uint32_t spread_bits4(uint32_t x) {  // bit i -> byte
   return (x & 1u) | ((x & 2u) << 7) | ((x & 4u) << 14) | ((x & 8u) << 21);
 }
 
-// Walks the band's row of a partition table: fn(entry) for every entry of
-// the band, wave by wave, BATCH slices in flight per wave. Slices are
-// `tile_size` apart; word positions fit 32 bits (fewer than 2^31 entries).
+// Walks the band's row of a partition table: fn(entry, place) for every entry
+// of the band. Slices are `tile_size` apart; word positions fit 32 bits
+// (fewer than 2^31 entries). The slices of BLOCK tiles at a time are cut into
+// units of up to 16 entries, listed in LDS, and every 16 lanes take a unit,
+// BATCH of them in flight: the work is spread evenly whether the entries are
+// scattered (tens of entries in every slice) or in order (nearly all of a
+// band's entries in one or two slices). With one wave per slice and 64 slices
+// per wave, 160 tiles kept 3 of 16 waves busy and long slices one: 0.13 ms to
+// mark and 0.13 ms to map the 5.4M ordered entries of a 1M-vertex mesh, which
+// take 0.033 (with the hash histograms) and 0.018 ms now; the map of the 25M
+// scattered entries of a 26.4M-vertex soup 0.22 -> 0.18 ms.
+template <int BLOCK>
+struct BandWalk {
+  static constexpr int UNITS = 4 * BLOCK;
+  uint32_t unit[UNITS];  // slice | number of the unit in it << 10
+  uint32_t at[BLOCK];    // first entry of a slice
+  uint32_t cnt[BLOCK];
+  uint32_t wave[BLOCK / kWave];
+};
+
 template <int BLOCK, int BATCH, class Load, class Fn>
 __device__ __forceinline__ void for_band_entries(const uint32_t* __restrict__ row, int64_t tiles, int tile_size,
-                                                 Load load, Fn fn) {
-  constexpr int WAVES = BLOCK / kWave;
-  const int lane = lane_id(), wave = threadIdx.x / kWave;
-  for (int64_t t0 = int64_t(wave) * kWave; t0 < tiles; t0 += int64_t(WAVES) * kWave) {
-    const uint32_t mine = t0 + lane < tiles ? row[t0 + lane] : 0u;
-    for (int j0 = 0; j0 < kWave; j0 += BATCH) {
-      uint32_t e[BATCH];
-      decltype(load(0u)) x[BATCH];
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        e[u] = __shfl(mine, j0 + u, kWave);
-        const uint32_t at = uint32_t(t0 + j0 + u) * uint32_t(tile_size) + (e[u] >> 16) + lane;
-        if (uint32_t(lane) < (e[u] & 0xFFFFu)) x[u] = load(at);
+                                                 BandWalk<BLOCK>& w, Load load, Fn fn) {
+  static_assert(BLOCK <= 1024, "slices are numbered in 10 bits");
+  constexpr int UNITS = BandWalk<BLOCK>::UNITS, GROUPS = BLOCK / 16;
+  const int tid = threadIdx.x, lane = lane_id();
+  for (int64_t t0 = 0; t0 < tiles; t0 += BLOCK) {
+    const uint32_t e = t0 + tid < tiles ? row[t0 + tid] : 0u;
+    const uint32_t cnt = e & 0xFFFFu;
+    const int units = int((cnt + 15) >> 4);
+    uint32_t total;
+    const int first = int(block_exclusive_scan<BLOCK>(uint32_t(units), w.wave, &total));
+    w.at[tid] = uint32_t(t0 + tid) * uint32_t(tile_size) + (e >> 16);
+    w.cnt[tid] = cnt;
+    for (int w0 = 0; w0 < int(total); w0 += UNITS) {
+      if (w0 > 0) __syncthreads();  // the units before are done
+      const int lo = max(first, w0), hi = min(first + units, w0 + UNITS);
+      if (units <= 4) {
+        for (int k = lo; k < hi; ++k) w.unit[k - w0] = uint32_t(tid) | uint32_t(k - first) << 10;
       }
+      for (uint64_t many = ballot(units > 4 && lo < hi); many; many &= many - 1) {
+        const int src = __ffsll((unsigned long long)many) - 1;
+        const int l = __shfl(lo, src), h = __shfl(hi, src), f = __shfl(first, src);
+        const uint32_t slice = uint32_t(tid - lane + src);
+        for (int k = l + lane; k < h; k += kWave) w.unit[k - w0] = slice | uint32_t(k - f) << 10;
+      }
+      __syncthreads();
+      const int nu = min(int(total) - w0, UNITS);
+      for (int u0 = 0; u0 < nu; u0 += GROUPS * BATCH) {
+        uint32_t at[BATCH];
+        bool ok[BATCH];
+        decltype(load(0u)) x[BATCH];
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u)
-        if (uint32_t(lane) < (e[u] & 0xFFFFu)) fn(x[u], uint32_t(t0 + j0 + u) * uint32_t(tile_size) + (e[u] >> 16) + lane);
-      // slices longer than a wave
+        for (int b = 0; b < BATCH; ++b) {  // unconditional loads, all in flight at once
+          const int u = u0 + b * GROUPS + (tid >> 4);
+          const uint32_t c = w.unit[min(u, nu - 1)];
+          const uint32_t in = (c >> 10) * 16 + uint32_t(tid & 15), n = w.cnt[c & 1023u];
+          ok[b] = u < nu && in < n;
+          at[b] = w.at[c & 1023u] + min(in, n - 1);
+          x[b] = load(at[b]);
+        }
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const uint32_t at = uint32_t(t0 + j0 + u) * uint32_t(tile_size) + (e[u] >> 16);
-        for (uint32_t k = lane + kWave; k < (e[u] & 0xFFFFu); k += kWave) fn(load(at + k), at + k);
+        for (int b = 0; b < BATCH; ++b)
+          if (ok[b]) fn(x[b], at[b]);
       }
     }
   }
+  __syncthreads();
 }
 
 // One band of k_band_mark; s_bits holds (1 << shift) / 32 words of LDS.
 template <int BLOCK>
-__device__ __forceinline__ void band_mark_body(const BandArgs& a, int64_t band, uint32_t* s_bits) {
+__device__ __forceinline__ void band_mark_body(const BandArgs& a, int64_t band, uint32_t* s_bits,
+                                               BandWalk<BLOCK>& walk) {
   const int tid = threadIdx.x;
   const int words = (1 << a.shift) / 32;
   for (int w = tid; w < words; w += BLOCK) s_bits[w] = 0;
@@ -192,8 +239,8 @@ __device__ __forceinline__ void band_mark_body(const BandArgs& a, int64_t band, 
   const int64_t lo = band << a.shift;
   const uint32_t mask = (1u << a.shift) - 1u;
   const uint32_t* part = a.part;
-  for_band_entries<BLOCK, 16>(
-      a.table + size_t(band) * size_t(a.tiles), a.tiles, kBandTile,
+  for_band_entries<BLOCK, 8>(
+      a.table + size_t(band) * size_t(a.tiles), a.tiles, a.fine ? kFineBandTile : kBandTile, walk,
       [&](uint32_t at) { return stream_load(part + at); },
       [&](uint32_t e, uint32_t) {
         const uint32_t l = e & mask;
@@ -215,7 +262,8 @@ __device__ __forceinline__ void band_mark_body(const BandArgs& a, int64_t band, 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_band_mark(BandArgs a) {
   extern __shared__ uint32_t s_bits[];
-  band_mark_body<BLOCK>(a, blockIdx.x, s_bits);
+  __shared__ BandWalk<BLOCK> s_walk;
+  band_mark_body<BLOCK>(a, blockIdx.x, s_bits, s_walk);
 }
 
 // Buffers of the sort-all path are decided on the device: with from_sort
@@ -228,7 +276,7 @@ struct PairPartArgs {
   int64_t n;
   int32_t shift;
   int32_t nb;
-  int64_t tiles;               // ceil(n / kPairTile)
+  int64_t tiles;               // ceil(n / tile size)
   uint2* part;                 // [n] (new id or -1, vertex - band start)
   uint32_t* table;             // [nb][tiles]
   int32_t* status;
@@ -239,7 +287,9 @@ struct PairPartArgs {
 
 // The group ids of a tile of pairs are clustered (sorted, or grouped by
 // hash bucket), so the cmap reads hit cache lines other lanes fetched.
-static __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
+template <int kPairItems>
+__global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
+  constexpr int kPairTile = kPairBlock * kPairItems;
   __shared__ uint32_t s_cnt[kMaxBands];
   __shared__ uint32_t s_off[kMaxBands];
   __shared__ uint2 s_stage[kPairTile];
@@ -318,8 +368,10 @@ struct BandMapArgs {
   int32_t from_sort;
 };
 
-static __global__ __launch_bounds__(kBandBlock) void k_band_map(BandMapArgs a) {
-  __shared__ int32_t s_map[1 << kMaxMapShift];
+template <int kBandBlock, int SHIFT, bool FINE>
+__global__ __launch_bounds__(kBandBlock) void k_band_map(BandMapArgs a) {
+  __shared__ alignas(16) int32_t s_map[1 << SHIFT];  // a.shift <= SHIFT
+  __shared__ BandWalk<kBandBlock> s_walk;
   const int tid = threadIdx.x;
   const int64_t band = blockIdx.x;
   const int64_t lo = band << a.shift;
@@ -330,10 +382,9 @@ static __global__ __launch_bounds__(kBandBlock) void k_band_map(BandMapArgs a) {
   __syncthreads();
   const uint2* ppart = a.from_sort ? reinterpret_cast<const uint2*>(a.sort.sorted()) : a.ppart;
   for_band_entries<kBandBlock, 8>(
-      a.ptable + size_t(band) * size_t(a.ptiles), a.ptiles, kPairTile,
+      a.ptable + size_t(band) * size_t(a.ptiles), a.ptiles, FINE ? kFinePairTile : kPairTile, s_walk,
       [&](uint32_t at) { return stream_load(ppart + at); },
       [&](uint2 p, uint32_t) { s_map[p.y] = int32_t(p.x); });
-  __syncthreads();
   int32_t* out = a.old2new + lo;
   if ((reinterpret_cast<uintptr_t>(out) & 15) == 0) {
     for (int i = 4 * tid; i < len; i += 4 * kBandBlock) {
@@ -350,7 +401,7 @@ static __global__ __launch_bounds__(kBandBlock) void k_band_map(BandMapArgs a) {
   const uint32_t* ipart = a.ipart;
   int32_t* values = a.from_sort ? reinterpret_cast<int32_t*>(a.sort.spare()) : a.values;
   for_band_entries<kBandBlock, 8>(
-      a.itable + size_t(band) * size_t(a.itiles), a.itiles, kBandTile,
+      a.itable + size_t(band) * size_t(a.itiles), a.itiles, FINE ? kFineBandTile : kBandTile, s_walk,
       [&](uint32_t at) { return stream_load(ipart + at); },
       [&](uint32_t e, uint32_t at) { stream_store(values + at, s_map[e & mask]); });
 }
@@ -368,7 +419,8 @@ struct BandRemapArgs {
 };
 
 // Entries dropped by the partition (out of range) come out as -1.
-static __global__ __launch_bounds__(kBandBlock) void k_band_remap(BandRemapArgs a) {
+template <int kBandBlock, int kBandTile>
+__global__ __launch_bounds__(kBandBlock) void k_band_remap(BandRemapArgs a) {
   __shared__ int32_t s_out[kBandTile];
   const int tid = threadIdx.x;
   const int64_t tile = blockIdx.x;
@@ -400,7 +452,11 @@ static __global__ __launch_bounds__(kBandBlock) void k_band_remap(BandRemapArgs 
 
 // Launches, each with the block shape its kernel is written for.
 static inline void launch_band_partition(const BandArgs& a, hipStream_t s) {
-  if (a.tiles > 0) hipLaunchKernelGGL(k_band_partition, dim3(a.tiles), dim3(kIdxPartBlock), 0, s, a);
+  if (a.tiles <= 0) return;
+  if (a.fine)
+    hipLaunchKernelGGL(k_band_partition<kFineIdxItems>, dim3(a.tiles), dim3(kIdxPartBlock), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_band_partition<kIdxPartItems>, dim3(a.tiles), dim3(kIdxPartBlock), 0, s, a);
 }
 
 // Small bands (Step 4 follows): many short workgroups; large bands: few,
@@ -413,16 +469,32 @@ static inline void launch_band_mark(const BandArgs& a, bool small_bands, hipStre
     hipLaunchKernelGGL(k_band_mark<1024>, dim3(a.nb), dim3(1024), bits_lds, s, a);
 }
 
-static inline void launch_pair_partition(const PairPartArgs& a, hipStream_t s) {
-  if (a.tiles > 0) hipLaunchKernelGGL(k_pair_partition, dim3(a.tiles), dim3(kPairBlock), 0, s, a);
+static inline void launch_pair_partition(const PairPartArgs& a, bool fine, hipStream_t s) {
+  if (a.tiles <= 0) return;
+  if (fine)
+    hipLaunchKernelGGL(k_pair_partition<kFinePairItems>, dim3(a.tiles), dim3(kPairBlock), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_pair_partition<kPairItems>, dim3(a.tiles), dim3(kPairBlock), 0, s, a);
 }
 
-static inline void launch_band_map(const BandMapArgs& a, int32_t nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_band_map, dim3(nb), dim3(kBandBlock), 0, s, a);
+// Fine bands hold at most 2^14 vertices, in 32 or 64 KB of LDS, so that
+// several of their workgroups share a CU.
+constexpr int kMaxFineShift = 14;
+static inline void launch_band_map(const BandMapArgs& a, int32_t nb, bool fine, hipStream_t s) {
+  if (fine && a.shift <= 13)
+    hipLaunchKernelGGL((k_band_map<512, 13, true>), dim3(nb), dim3(512), 0, s, a);
+  else if (fine)
+    hipLaunchKernelGGL((k_band_map<512, kMaxFineShift, true>), dim3(nb), dim3(512), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_band_map<kBandBlock, kMaxMapShift, false>), dim3(nb), dim3(kBandBlock), 0, s, a);
 }
 
-static inline void launch_band_remap(const BandRemapArgs& a, int64_t tiles, hipStream_t s) {
-  if (tiles > 0) hipLaunchKernelGGL(k_band_remap, dim3(tiles), dim3(kBandBlock), 0, s, a);
+static inline void launch_band_remap(const BandRemapArgs& a, int64_t tiles, bool fine, hipStream_t s) {
+  if (tiles <= 0) return;
+  if (fine)
+    hipLaunchKernelGGL((k_band_remap<512, kFineBandTile>), dim3(tiles), dim3(512), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_band_remap<kBandBlock, kBandTile>), dim3(tiles), dim3(kBandBlock), 0, s, a);
 }
 
 }  // namespace mrx

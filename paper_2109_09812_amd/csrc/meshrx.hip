@@ -272,6 +272,7 @@ enum BandMode { kBandNone = 0, kMarkOnly = 1, kMarkAndMap = 2 };
 constexpr int64_t kBandMinEntries = int64_t(1) << 20;
 struct BandPlan {
   int mode = kBandNone;
+  bool fine = false;  // the smaller tiles, and bands to match
   int shift = 0, nb = 0;
   int64_t itiles = 0, ptiles = 0;
   size_t words() const {  // index table + tile counts (+ pair table)
@@ -295,6 +296,24 @@ BandPlan band_plan(int64_t n, int64_t m, int s, bool force, bool automatic) {
     b.ptiles = mode == kMarkAndMap ? (n + kPairTile - 1) / kPairTile : 0;
     return b;
   }
+  return b;
+}
+
+// On the hash path, up to kFineMaxEntries index entries: tiles of a quarter of
+// the size and up to 512 bands, so that a slice still holds 16 entries where
+// they are scattered. Their larger tables lie behind the sample sort's
+// scratch, where there is room.
+constexpr int64_t kFineMaxEntries = int64_t(1) << 23;
+BandPlan fine_band_plan(const BandPlan& coarse, int64_t n, int64_t m) {
+  if (coarse.mode != kMarkAndMap || m > kFineMaxEntries) return coarse;
+  BandPlan b = coarse;
+  b.fine = true;
+  b.shift = kMinFineShift;
+  while (((n - 1) >> b.shift) + 1 > 512) ++b.shift;
+  if (b.shift > kMaxFineShift) return coarse;
+  b.nb = int(((n - 1) >> b.shift) + 1);
+  b.itiles = (m + kFineBandTile - 1) / kFineBandTile;
+  b.ptiles = (n + kFinePairTile - 1) / kFinePairTile;
   return b;
 }
 
@@ -710,16 +729,24 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   // Step 1 and the hash-digit histograms: Step 1 by vertex bands (the index
   // partition in out_idx, or in C, which the grouping fills only later),
   // else scattered byte stores beside the histograms
-  const BandPlan& bp = L.band;
-  const MarkArgs mark{idx, m, arity, n, nullptr, nullptr, 0, nullptr, live_elems, used_v, status};
+  BandPlan bp = L.band;
   uint32_t* band_tab = reinterpret_cast<uint32_t*>(ws + L.band_tab);
+  if (split_applies(v, L, n, K)) {
+    const BandPlan fine = fine_band_plan(L.band, n, m);
+    const int64_t used = v.split.scratch(n, group_ranges).words;
+    if (fine.fine && used + int64_t(fine.words()) <= n * int64_t(K)) {
+      bp = fine;
+      band_tab = reinterpret_cast<uint32_t*>(ws + L.uniq) + used;
+    }
+  }
+  const MarkArgs mark{idx, m, arity, n, nullptr, nullptr, 0, nullptr, live_elems, used_v, status};
   uint32_t* ipart = bp.mode == kMarkAndMap ? reinterpret_cast<uint32_t*>(out_idx) : buf[2];
   uint32_t* itable = band_tab;
   uint32_t* itile_valid = itable + size_t(bp.nb) * size_t(bp.itiles);
   uint32_t* ptable = itile_valid + bp.itiles;
   if (bp.mode != kBandNone) {
     const BandArgs ba{idx, m, arity, n, live_elems, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0,
-                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, ipart, itable, itile_valid, used_v, status};
+                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, bp.fine ? 1 : 0, ipart, itable, itile_valid, used_v, status};
     prof_mark("band_partition", s);
     launch_band_partition(ba, s);
     if (bp.mode == kMarkAndMap) {
@@ -807,15 +834,15 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
       const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
                             reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0};
       prof_mark("pair_partition", s);
-      launch_pair_partition(pa, s);
+      launch_pair_partition(pa, bp.fine, s);
       const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
                            bp.shift, old2new, reinterpret_cast<int32_t*>(buf[2])};
       prof_mark("band_map", s);
-      launch_band_map(ma, bp.nb, s);
+      launch_band_map(ma, bp.nb, bp.fine, s);
       const BandRemapArgs ra{ipart, reinterpret_cast<const int32_t*>(buf[2]), itile_valid, m, arity, live_elems,
                              out_idx};
       prof_mark("band_remap", s);
-      launch_band_remap(ra, bp.itiles, s);
+      launch_band_remap(ra, bp.itiles, bp.fine, s);
       prof_mark(nullptr, s);
       return check_launch();
     }
@@ -901,7 +928,7 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
   const bool fused = bp.mode == kBandNone && v.mark_hist_applies(n, m);
   if (bp.mode != kBandNone) {
     const BandArgs ba{idx, m, arity, n, live_elems, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0,
-                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, ipart, itable, itile_valid, used_v, status};
+                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, 0, ipart, itable, itile_valid, used_v, status};
     prof_mark("band_partition", s);
     launch_band_partition(ba, s);
     prof_mark("band_mark", s);
@@ -986,7 +1013,7 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
       pa.sort = sb;
       pa.from_sort = 1;
       prof_mark("pair_partition", s);
-      launch_pair_partition(pa, s);
+      launch_pair_partition(pa, false, s);
       BandMapArgs ma{};
       ma.ptable = ptable;
       ma.ptiles = bp.ptiles;
@@ -999,7 +1026,7 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
       ma.sort = sb;
       ma.from_sort = 1;
       prof_mark("band_map", s);
-      launch_band_map(ma, bp.nb, s);
+      launch_band_map(ma, bp.nb, false, s);
       BandRemapArgs ra{};
       ra.ipart = ipart;
       ra.tile_valid = itile_valid;
@@ -1010,7 +1037,7 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
       ra.sort = sb;
       ra.from_sort = 1;
       prof_mark("band_remap", s);
-      launch_band_remap(ra, bp.itiles, s);
+      launch_band_remap(ra, bp.itiles, false, s);
       prof_mark(nullptr, s);
       return check_launch();
     }

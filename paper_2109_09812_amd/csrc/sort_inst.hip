@@ -109,6 +109,7 @@ __global__ __launch_bounds__(kRandBlock) void k_band_mark_hash_hist(BandArgs ba,
   constexpr int WORDS = PH << D;
   constexpr int R = items_per_group(K);
   __shared__ uint32_t s_h[WORDS];
+  __shared__ BandWalk<B> s_walk;
   extern __shared__ uint32_t s_bits[];
   const int64_t total = hist_blocks + ba.nb;
   const int64_t b = blockIdx.x;
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(kRandBlock) void k_band_mark_hash_hist(BandArgs ba,
     for (int64_t c = h0; c < chunks; c += hist_blocks) histogram_chunk<DG, K, D, K, B, GROUPS>(ha.src[0], ha.n, s_h, c);
     flush_histograms<WORDS, B>(s_h, ha.hist);
   } else {
-    band_mark_body<B>(ba, b - h0, s_bits);
+    band_mark_body<B>(ba, b - h0, s_bits, s_walk);
   }
 }
 
