@@ -115,8 +115,8 @@ typedef struct {
  * index entries are scattered, as in soups, it is faster); this flag asks for
  * it at any size and on the sort-all path too (where indices stored in order
  * make the scattered accesses cheap), wherever it applies (at most
- * (K + 1) * num_vtx index entries). Batched calls never do. The result is
- * identical either way. */
+ * (K + 1) * num_vtx index entries). Batched calls choose by themselves. The
+ * result is identical either way. */
 #define MRX_TUNING_BANDS 16
 
 /* Library ABI version (MRX_ABI_VERSION of the build). */

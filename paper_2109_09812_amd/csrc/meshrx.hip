@@ -317,6 +317,27 @@ BandPlan fine_band_plan(const BandPlan& coarse, int64_t n, int64_t m) {
   return b;
 }
 
+// Bands of a batch (hash path), over the packed vertex ids: always the
+// smaller tiles, since a tile's entries and pairs lie in the vertex ranges of
+// its few meshes and so in few bands, whatever the number of bands. For
+// meshes of 2^12 vertices and more on average: the scattered accesses of
+// smaller ones stay within a few cache lines each (4,096 meshes of 400
+// vertices: 308 us a call without bands, 342 with; 256 meshes of 80,000:
+// 1,788 and 1,666).
+BandPlan batch_band_plan(int64_t n, int64_t m, int s, int32_t nmesh) {
+  BandPlan b;
+  if (m < kBandMinEntries || m > n * int64_t(s) || n < int64_t(nmesh) << 12) return b;
+  b.shift = kMinFineShift;
+  while (((n - 1) >> b.shift) + 1 > 512 && b.shift < kMaxMapShift) ++b.shift;
+  if (((n - 1) >> b.shift) + 1 > kMaxBands) return b;
+  b.mode = kMarkAndMap;
+  b.fine = true;
+  b.nb = int(((n - 1) >> b.shift) + 1);
+  b.itiles = (m + kFineBandTile - 1) / kFineBandTile;
+  b.ptiles = (n + kFinePairTile - 1) / kFinePairTile;
+  return b;
+}
+
 struct Layout {
   int K = 0, S = 0, P_key = 0, P_mesh = 0, P_hash = 0;  // P_hash > 0: hash grouping
   BandPlan band;                                         // hash grouping only
@@ -746,7 +767,8 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   uint32_t* ptable = itile_valid + bp.itiles;
   if (bp.mode != kBandNone) {
     const BandArgs ba{idx, m, arity, n, live_elems, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0,
-                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, bp.fine ? 1 : 0, ipart, itable, itile_valid, used_v, status};
+                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, bp.fine ? 1 : 0, ipart, itable, itile_valid, used_v, status, nullptr,
+                      nullptr, nullptr, 0};
     prof_mark("band_partition", s);
     launch_band_partition(ba, s);
     if (bp.mode == kMarkAndMap) {
@@ -832,7 +854,8 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
       // X and C are free again: X takes the partitioned pairs, C the new ids
       // of the index entries
       const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
-                            reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0};
+                            reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0, nullptr,
+                            nullptr, nullptr, 0};
       prof_mark("pair_partition", s);
       launch_pair_partition(pa, bp.fine, s);
       const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
@@ -928,7 +951,8 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
   const bool fused = bp.mode == kBandNone && v.mark_hist_applies(n, m);
   if (bp.mode != kBandNone) {
     const BandArgs ba{idx, m, arity, n, live_elems, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0,
-                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, 0, ipart, itable, itile_valid, used_v, status};
+                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, 0, ipart, itable, itile_valid, used_v, status, nullptr,
+                      nullptr, nullptr, 0};
     prof_mark("band_partition", s);
     launch_band_partition(ba, s);
     prof_mark("band_mark", s);
@@ -1121,12 +1145,36 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   prof_mark("mesh_buckets", s);
   hipLaunchKernelGGL(k_mesh_buckets, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes,
                      int32_t(v.group_mesh_target_bucket), mbk);
-  // Step 1 (scattered byte stores; reports out-of-range entries) beside the
+  // Step 1 by vertex bands, or by scattered byte stores beside the
   // bucket-digit histograms of the stable sort of (record, id | used << 31)
   // by the buckets of (mesh id, record)
+  BandPlan bp;
+  uint32_t* band_tab = nullptr;
+  if (split_applies(v, L, n, K) && etab) {
+    const BandPlan want = batch_band_plan(n, m, K + 1, num_meshes);
+    const int64_t used = v.split_mesh.scratch(n, group_ranges).words;
+    if (want.mode != kBandNone && used + int64_t(want.words()) <= n * int64_t(K)) {
+      bp = want;
+      band_tab = reinterpret_cast<uint32_t*>(ws + L.uniq) + used;
+    }
+  }
+  const bool bands = bp.mode == kMarkAndMap;
+  uint32_t* ipart = reinterpret_cast<uint32_t*>(out_idx);
+  uint32_t* itable = band_tab;
+  uint32_t* itile_valid = itable + size_t(bp.nb) * size_t(bp.itiles);
+  uint32_t* ptable = itile_valid + bp.itiles;
+  if (bands) {
+    const BandArgs ba{idx, m, arity, n, nullptr, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0, 1, bp.itiles, 1,
+                      ipart, itable, itile_valid, used_v, status, vtx_offsets, elem_offsets, etab, num_meshes};
+    prof_mark("band_partition", s);
+    launch_band_partition(ba, s);
+    prof_mark("band_mark", s);
+    launch_band_mark(ba, true, s);
+  }
   const MarkArgs mark{idx, m, arity, n, vtx_offsets, elem_offsets, num_meshes, etab, nullptr, used_v, status};
-  prof_mark(m > 0 ? "mark_histogram" : "hash_histogram", s);
-  v.hash_mesh_hist(m > 0 ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, vtx_offsets, num_meshes, vtab, mbk,
+  const bool fused_mark = m > 0 && !bands;
+  prof_mark(fused_mark ? "mark_histogram" : "hash_histogram", s);
+  v.hash_mesh_hist(fused_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, vtx_offsets, num_meshes, vtab, mbk,
                    ph, hist_hash, s);
   prof_mark("scan_buckets", s);
   v.scan(hist_hash, ph, n, nullptr, dead_hash, s);
@@ -1202,6 +1250,23 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   order_used_groups(v, L, n, K, o, s);
 
   // Step 4's map and new2old, both mesh-local, remap
+  if (bands) {
+    const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
+                          reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0, vtx_offsets,
+                          out_vtx_offsets, vtab, num_meshes};
+    prof_mark("pair_partition", s);
+    launch_pair_partition(pa, true, s);
+    const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
+                         bp.shift, old2new, reinterpret_cast<int32_t*>(buf[2]), SortBuffers{}, 0};
+    prof_mark("band_map", s);
+    launch_band_map(ma, bp.nb, true, s);
+    const BandRemapArgs ra{ipart, reinterpret_cast<const int32_t*>(buf[2]), itile_valid, m, arity, nullptr, out_idx,
+                           SortBuffers{}, 0};
+    prof_mark("band_remap", s);
+    launch_band_remap(ra, bp.itiles, true, s);
+    prof_mark(nullptr, s);
+    return check_launch();
+  }
   prof_mark("old2new", s);
   hipLaunchKernelGGL((k_scatter_old2new<true>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                      SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs), cmap, n,

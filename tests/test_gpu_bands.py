@@ -50,3 +50,33 @@ def test_more_entries_than_fine_tiles_take():
     vtx = rng.integers(0, 300, size=(n, 3), dtype=np.uint64).astype(np.uint32)
     for m in (1 << 23, (1 << 23) + 1):
         check(vtx, rng.integers(0, n, m).astype(np.int32).reshape(-1, 1), f"m={m}")
+
+
+@pytest.mark.parametrize("k,arity", [(1, 2), (3, 3), (5, 1)])
+def test_batches_by_bands(k, arity):
+    """Batches of 2^20 entries and more: meshes that share tiles, one that
+    spans many, empty ones, an entry beyond its own mesh."""
+    import paper_2109_09812_amd as mrx
+    rng = np.random.default_rng(40 + k)
+    sizes = np.concatenate([rng.integers(0, 3000, 200), [0, 400_000, 1, 0], rng.integers(0, 60_000, 20)])
+    vs, is_ = [], []
+    for sz in sizes.tolist():
+        vs.append(rng.integers(0, max(2, sz // 3), size=(sz, k), dtype=np.uint64).astype(np.uint32))
+        is_.append(rng.integers(0, max(sz, 1), size=((sz * 4) // (3 * arity), arity)).astype(np.int32))
+    vo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    eo = np.concatenate([[0], np.cumsum([x.shape[0] for x in is_])]).astype(np.int64)
+    vtx, idx = np.concatenate(vs), np.concatenate(is_)
+    assert idx.size >= 1 << 20
+    print("[case] batch by bands", vtx.shape, idx.shape, flush=True)
+    t = [torch.from_numpy(x).to(DEV) for x in (vtx.view(np.int32), vo, idx, eo)]
+    r = mrx.reindex_mesh_batched(*t)
+    ov, ooff, oi, o2n, n2o = oracle.reindex_batched(vtx, idx, vo, eo)
+    assert np.array_equal(r.out_vtx_offsets.cpu().numpy(), ooff)
+    assert np.array_equal(r.out_vtx.cpu().numpy().view(np.uint32), ov.view(np.uint32))
+    assert np.array_equal(r.out_idx.cpu().numpy(), oi)
+    assert np.array_equal(r.old2new.cpu().numpy(), o2n)
+    assert np.array_equal(r.new2old.cpu().numpy(), n2o)
+    e = int(eo[201])
+    t[2][e, arity - 1] = 400_000
+    with pytest.raises(IndexError):
+        mrx.reindex_mesh_batched(*t)
