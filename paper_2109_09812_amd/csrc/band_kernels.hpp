@@ -306,7 +306,8 @@ struct PairPartArgs {
   uint2* part;                 // [n] (new id or -1, vertex - band start)
   uint32_t* table;             // [nb][tiles]
   int32_t* status;
-  int32_t* new2old;            // nullable: receives the ids with kRepBit, at their group's new id
+  const uint32_t* rep;         // [n] representative of each used group, by name
+  int32_t* new2old;            // nullable (hash grouping): receives them, at the groups' new ids
   SortBuffers sort;
   int32_t from_sort;
   // batches: new ids and representatives become mesh-local (a pair's mesh is
@@ -343,6 +344,14 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
   int32_t val[kPairItems];
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i) val[i] = a.cmap[min(p[i].x, last)];
+  // representatives: the pair of one takes its group's place in new2old (the
+  // entry is 0xFFFFFFFF for all other pairs)
+  uint32_t at[kPairItems];
+#pragma unroll
+  for (int i = 0; i < kPairItems; ++i) {
+    at[i] = 0xFFFFFFFFu;
+    if (a.new2old) at[i] = a.rep[min(p[i].x, last)];
+  }
   uint32_t vtx[kPairItems];
   bool bad = false;
   int64_t out0 = 0, vtx0 = 0;  // output and vertex offsets of the pairs' mesh
@@ -357,10 +366,9 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i) {
     const int64_t k = base + int64_t(i) * kPairBlock + tid;
-    const uint32_t id = p[i].y & ~kRepBit;
-    const bool ok = p[i].x <= last && id <= last;
+    const bool ok = p[i].x <= last && p[i].y <= last;
     if (k < a.n && !ok) bad = true;  // only after a failed wait
-    vtx[i] = k < a.n && ok ? id : 0xFFFFFFFFu;
+    vtx[i] = k < a.n && ok ? p[i].y : 0xFFFFFFFFu;
     if constexpr (BATCHED) {
       if (!one_mesh && k < a.n) {
         const uint32_t b = mesh_of(a.vtx_off, a.nmesh, k, a.vtx_tab);
@@ -368,9 +376,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
         vtx0 = a.vtx_off[b];
       }
     }
-    // where representative p[i] goes in new2old, else 0xFFFFFFFF
-    p[i].x = a.new2old && k < a.n && ok && (p[i].y & kRepBit) && uint32_t(val[i]) <= last ? uint32_t(val[i]) : 0xFFFFFFFFu;
-    p[i].y = uint32_t(id - uint32_t(vtx0));
+    at[i] = at[i] == p[i].y && k < a.n && ok && uint32_t(val[i]) <= last ? uint32_t(val[i]) : 0xFFFFFFFFu;
+    p[i].y -= uint32_t(vtx0);
     if constexpr (BATCHED) val[i] = val[i] < 0 ? -1 : int32_t(val[i] - out0);
   }
   if (bad) atomicMax(a.status, kBandErrInternal);
@@ -402,11 +409,10 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
       s_stage[s_off[vtx[i] >> a.shift] + r[i]] = make_uint2(uint32_t(val[i] < 0 ? -1 : val[i]), vtx[i] & mask);
   __syncthreads();
   for (uint32_t j = tid; j < valid; j += kPairBlock) stream_store(out + base + j, s_stage[j]);
-  // scattered, so after the last barrier: a barrier waits for every store
-  // before it (0.177 -> 0.169 ms for 26.4M pairs with 4.2M representatives)
+  // scattered, so last: nothing waits behind them
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i)
-    if (p[i].x != 0xFFFFFFFFu) a.new2old[p[i].x] = int32_t(p[i].y);
+    if (at[i] != 0xFFFFFFFFu) a.new2old[at[i]] = int32_t(p[i].y);
 }
 
 struct BandMapArgs {

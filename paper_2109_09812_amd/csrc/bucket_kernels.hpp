@@ -1,0 +1,517 @@
+// Hash buckets in one partition pass, grouped whole.
+//
+// For up to some tens of millions of vertices the records go straight into up
+// to kBucketMax hash buckets, each grouped by one workgroup. Compared with two
+// or three stable 8-bit passes (k_onesweep) and a grouping that rebuilds the
+// bucket borders from overlapping windows (k_group), the elements move once
+// instead of two or three times, nothing waits on other tiles, and every
+// element is hashed into a table once instead of 1.5 times.
+//  * k_bucket_count: elements per (tile, bucket), beside Step 1's marking;
+//  * k_bucket_offsets: each tile's place in every bucket (a scan down the
+//    tiles) and the elements per bucket;
+//  * k_bucket_scatter: elements (record, id | used << 31) to their buckets,
+//    put in bucket order in LDS first so that runs are written together;
+//  * k_group_bucket: equal records of a bucket by a hash table in LDS.
+// The order inside a bucket is that of atomics, so a group's representative is
+// the minimum of its ids. Only a bucket's distinct records take LDS, and where
+// they do not fit, the rest of the bucket takes another round.
+#pragma once
+
+#include <algorithm>
+
+#include "band_kernels.hpp"
+#include "group_kernels.hpp"
+#include "scan_kernels.hpp"
+
+namespace mrx {
+
+constexpr int kBucketBlock = 512;
+// Buckets: LDS counters of k_bucket_scatter (20 or 48 KB for two tables of
+// them, so that two workgroups or one share a CU).
+constexpr int kBucketMax = 2560;      // one mesh
+constexpr int kBucketMaxMesh = 6144;  // batches: at least one per mesh
+constexpr int kBucketMostPer = 10400; // vertices per bucket
+constexpr int kGroupBlock = 1024;     // k_group_bucket
+// larger buckets (values with thousands of copies) go through
+// group_big_bucket, whose time does not depend on how many of them differ
+constexpr int kGroupSlots = 1 << 15;
+
+template <int K>
+struct BucketShape {
+  static constexpr int S = K + 1;
+  // elements per thread of a large tile (registers) and of a small one
+  static constexpr int EPT = K <= 4 ? 16 : K <= 8 ? 8 : 4;
+  static constexpr int EPT_SMALL = 4;
+  // slots of the LDS stage (32 KB)
+  static constexpr int STAGE = 8192 / S / 64 * 64;
+  // distinct records a workgroup of k_group_bucket holds (two workgroups per
+  // CU) and its table
+  static constexpr int DCAP = K == 1 ? 4096 : K <= 4 ? 3072 : K == 5 ? 2560 : K == 6 ? 2048 : K <= 10 ? 1536
+                              : 1024;
+  static constexpr int TB = DCAP > 3072 ? 13 : DCAP > 1536 ? 12 : DCAP > 768 ? 11 : 10;
+  static constexpr int TS = 1 << TB;
+  static_assert(TS * 3 >= DCAP * 4, "table load");
+  static_assert(DCAP % 32 == 0, "bits of the used groups");
+  // average bucket: all distinct records of it fit at once
+  static constexpr int TARGET = DCAP * 3 / 4;
+};
+
+// Buckets and tiles for n vertices in nmesh meshes; buckets = 0: too many
+// vertices or meshes.
+struct BucketPlan {
+  int32_t buckets = 0;   // columns (a batch may use fewer)
+  int32_t target = 0;    // vertices per bucket aimed at
+  int32_t ept = 0;       // elements per thread of a tile
+  int64_t tiles = 0;
+  int64_t count_words() const { return tiles * ((buckets + 1) / 2); }   // 16-bit counts
+  int64_t base_words() const { return tiles * int64_t(buckets); }
+};
+
+template <int K>
+inline BucketPlan bucket_plan(int64_t n, int32_t nmesh, int64_t words) {
+  using SH = BucketShape<K>;
+  BucketPlan p;
+  const int64_t most = nmesh > 1 ? int64_t(kBucketMaxMesh) - nmesh : int64_t(kBucketMax);
+  if (n <= 0 || most < 512) return p;
+  // about 1,024 buckets where that leaves them small, then as large as fits
+  // one round, then as large as the limit on buckets makes them
+  int64_t t = std::max<int64_t>(256, std::min<int64_t>(n / 1024, SH::TARGET));
+  t = std::max(t, (n + most - 1) / most);
+  if (t > kBucketMostPer) return p;
+  p.target = int32_t(t);
+  p.buckets = int32_t((n + t - 1) / t + (nmesh > 1 ? nmesh : 0));
+  // small tiles while the large ones would not fill the GPU twice
+  for (int ept : {int(SH::EPT_SMALL), int(SH::EPT)}) {
+    if (ept != SH::EPT && n > int64_t(kBucketBlock) * SH::EPT * 128) continue;
+    p.ept = ept;
+    p.tiles = (n + kBucketBlock * ept - 1) / (kBucketBlock * ept);
+    if (p.count_words() + p.base_words() <= words) return p;
+  }
+  return BucketPlan{};
+}
+
+struct BucketArgs {
+  const uint32_t* vtx;         // [n][K]
+  const uint8_t* used;         // [n]
+  int64_t n;
+  int32_t buckets;
+  int64_t tiles;
+  int32_t tile;                // elements per tile
+  uint16_t* counts;            // [tiles][stride]
+  int32_t stride;              // even
+  uint32_t* base;              // [tiles][buckets]
+  uint32_t* totals;            // [buckets]
+  uint32_t* starts;            // [buckets + 1]
+  uint32_t* elems;             // [n][K+1]
+  // batches: vertex offsets, their bucket table, and each mesh's (first
+  // bucket, buckets)
+  const int64_t* mesh_off;
+  const int32_t* mesh_tab;
+  const uint2* mesh_buckets;
+  int32_t nmesh;
+};
+
+// Bucket of a record: the hash scaled to the number of buckets (of its mesh).
+__device__ __forceinline__ uint32_t scaled_bucket(uint32_t h, uint32_t buckets) { return __umulhi(h, buckets); }
+
+// Meshes of the first and last vertex of [i0, i1).
+struct TileMesh {
+  uint32_t lo, hi;
+  uint2 buckets;  // of mesh lo
+};
+__device__ __forceinline__ TileMesh tile_mesh(const BucketArgs& a, int64_t i0, int64_t i1) {
+  TileMesh t;
+  t.lo = __builtin_amdgcn_readfirstlane(mesh_of(a.mesh_off, a.nmesh, i0, a.mesh_tab));
+  t.hi = __builtin_amdgcn_readfirstlane(mesh_of(a.mesh_off, a.nmesh, i1 - 1, a.mesh_tab));
+  t.buckets = a.mesh_buckets[t.lo];
+  return t;
+}
+
+template <int K, bool MESH>
+__device__ __forceinline__ uint32_t bucket_of(const BucketArgs& a, const TileMesh& tm, int64_t i,
+                                              const uint32_t (&x)[K]) {
+  const uint32_t h = hash_words<K>(x);
+  if constexpr (MESH) {
+    const uint2 b = tm.lo == tm.hi ? tm.buckets : a.mesh_buckets[mesh_of(a.mesh_off, a.nmesh, i, a.mesh_tab)];
+    return b.x + scaled_bucket(h, b.y);
+  } else {
+    return scaled_bucket(h, uint32_t(a.buckets));
+  }
+}
+
+// Elements per bucket of one tile; s_cnt holds a.buckets words.
+template <int K, bool MESH, int BLOCK>
+__device__ __forceinline__ void bucket_count_tile(const BucketArgs& a, int64_t tile, uint32_t* s_cnt) {
+  constexpr int U = K <= 4 ? 8 : K <= 8 ? 4 : 2;
+  const int tid = threadIdx.x;
+  const int64_t i0 = tile * a.tile, i1 = min(i0 + a.tile, a.n);
+  for (int f = tid; f < a.buckets; f += BLOCK) s_cnt[f] = 0;
+  TileMesh tm{};
+  if constexpr (MESH) tm = tile_mesh(a, i0, i1);
+  __syncthreads();
+  for (int64_t j0 = i0; j0 < i1; j0 += BLOCK * U) {
+    uint32_t x[U][K];
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t i = min(j0 + r * BLOCK + tid, i1 - 1);
+#pragma unroll
+      for (int w = 0; w < K; ++w) x[r][w] = a.vtx[i * K + w];
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t i = j0 + r * BLOCK + tid;
+      if (i < i1) atomicAdd(&s_cnt[bucket_of<K, MESH>(a, tm, i, x[r])], 1u);
+    }
+  }
+  __syncthreads();
+  uint32_t* row = reinterpret_cast<uint32_t*>(a.counts + tile * int64_t(a.stride));
+  for (int f = 2 * tid; f < a.buckets; f += 2 * BLOCK)
+    row[f >> 1] = s_cnt[f] | (f + 1 < a.buckets ? s_cnt[f + 1] << 16 : 0u);
+}
+
+// Step 1's marking and the bucket counts in one launch, their workgroups
+// spread evenly over the grid (as in k_mark_histogram): MARK 0 counts alone,
+// 1 marks by scattered stores, 2 by vertex bands.
+template <int K, bool MESH, int MARK>
+__global__ __launch_bounds__(kRandBlock) void k_bucket_count(BucketArgs a, MarkArgs ma, BandArgs ba,
+                                                             int64_t mark_blocks) {
+  __shared__ uint32_t s_cnt[MESH ? kBucketMaxMesh : kBucketMax];
+  const int64_t total = a.tiles + mark_blocks;
+  const int64_t b = blockIdx.x;
+  const int64_t c0 = b * a.tiles / total, c1 = (b + 1) * a.tiles / total;
+  if (c1 > c0) {
+    bucket_count_tile<K, MESH, kRandBlock>(a, c0, s_cnt);
+  } else if constexpr (MARK == 1) {
+    mark_used_tile<MESH>(ma, b - c0);
+  } else if constexpr (MARK == 2) {
+    __shared__ BandWalk<kRandBlock> s_walk;
+    extern __shared__ uint32_t s_bits[];
+    band_mark_body<kRandBlock>(ba, b - c0, s_bits, s_walk);
+  }
+}
+
+// Scan down the tiles, 32 buckets per workgroup, 32 runs of tiles. (The bucket
+// starts are left to the readers of the totals: a last workgroup that scans
+// them needs device-wide fences, which took longer than all else here.)
+constexpr int kOffsetCols = 32;
+constexpr int kOffsetRuns = 32;
+static __global__ __launch_bounds__(kOffsetCols* kOffsetRuns) void k_bucket_offsets(BucketArgs a) {
+  constexpr int U = 16;  // tiles in flight per thread
+  __shared__ uint32_t s_sum[kOffsetRuns][kOffsetCols];
+  const int tid = threadIdx.x, c = tid % kOffsetCols, run = tid / kOffsetCols;
+  const int f = min(int(blockIdx.x) * kOffsetCols + c, a.buckets - 1);
+  const bool own = int(blockIdx.x) * kOffsetCols + c < a.buckets;
+  const uint16_t* __restrict__ counts = a.counts + f;
+  uint32_t* __restrict__ base = a.base + f;
+  const int tiles = int(a.tiles), stride = a.stride;
+  const int per = (tiles + kOffsetRuns - 1) / kOffsetRuns;
+  const int t0 = min(run * per, tiles), t1 = min(t0 + per, tiles);
+  uint32_t sum = 0;
+  for (int t = t0; t < t1; t += U) {
+    uint32_t x[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) x[j] = counts[int64_t(min(t + j, tiles - 1)) * stride];
+#pragma unroll
+    for (int j = 0; j < U; ++j) sum += t + j < t1 ? x[j] : 0u;
+  }
+  s_sum[run][c] = sum;
+  __syncthreads();
+  uint32_t at = 0;
+  for (int r = 0; r < run; ++r) at += s_sum[r][c];
+  if (own && run == kOffsetRuns - 1) a.totals[f] = at + sum;
+  for (int t = t0; t < t1; t += U) {
+    uint32_t x[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) x[j] = counts[int64_t(min(t + j, tiles - 1)) * stride];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      if (own && t + j < t1) base[int64_t(t + j) * a.buckets] = at;
+      at += x[j];
+    }
+  }
+}
+
+// One tile's elements to their buckets. FMAX bounds the buckets.
+template <int K, int EPT, int FMAX, bool MESH>
+__global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a) {
+  using SH = BucketShape<K>;
+  constexpr int S = SH::S, BLOCK = kBucketBlock, Q = SH::STAGE, TILE = BLOCK * EPT;
+  __shared__ uint32_t s_off[FMAX];    // elements of a bucket, then its place in the tile
+  __shared__ uint32_t s_delta[FMAX];  // place in the bucket order minus place in the tile
+  __shared__ alignas(16) uint32_t s_stage[Q * S];
+  __shared__ uint16_t s_id[TILE];
+  __shared__ uint32_t s_wave[BLOCK / kWave];
+  const int tid = threadIdx.x, lane = lane_id();
+  const int64_t tile = blockIdx.x;
+  const int64_t i0 = tile * TILE, i1 = min(i0 + TILE, a.n);
+  for (int f = tid; f < a.buckets; f += BLOCK) s_off[f] = 0;
+  TileMesh tm{};
+  if constexpr (MESH) tm = tile_mesh(a, i0, i1);
+  __syncthreads();
+  uint32_t e[EPT][S];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int64_t v = min(i0 + i * BLOCK + tid, i1 - 1);
+#pragma unroll
+    for (int w = 0; w < K; ++w) e[i][w] = a.vtx[v * K + w];
+  }
+  // used flags: a wave's 64 bytes of item i are 16 words; lane l loads word
+  // l % 16 of item 4 r + l / 16 and the lanes exchange them
+  uint32_t flags[EPT / 4];
+  static_assert(EPT % 4 == 0, "flags are loaded for four items at once");
+#pragma unroll
+  for (int r = 0; r < EPT / 4; ++r) {
+    const int64_t at = i0 + (4 * r + (lane >> 4)) * BLOCK + (tid - lane) + 4 * (lane & 15);
+    flags[r] = 0;
+    if (at + 4 <= a.n) {
+      flags[r] = *reinterpret_cast<const uint32_t*>(a.used + at);
+    } else {
+      for (int c = 0; c < 4; ++c)
+        if (at + c < a.n) flags[r] |= uint32_t(a.used[at + c]) << (8 * c);
+    }
+  }
+  uint32_t pos[EPT];
+  uint32_t fb[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int64_t v = i0 + i * BLOCK + tid;
+    const uint32_t word = __shfl(flags[i / 4], ((i & 3) << 4) + (lane >> 2));
+    uint32_t x[K];
+#pragma unroll
+    for (int w = 0; w < K; ++w) x[w] = e[i][w];
+    e[i][K] = uint32_t(v) | ((word >> (8 * (lane & 3)) & 1u) << 31);
+    fb[i] = 0;
+    pos[i] = 0xFFFFFFFFu;
+    if (v < i1) {
+      fb[i] = bucket_of<K, MESH>(a, tm, v, x);
+      pos[i] = atomicAdd(&s_off[fb[i]], 1u);
+    }
+  }
+  __syncthreads();
+  {
+    constexpr int PER = (FMAX + BLOCK - 1) / BLOCK;
+    const int per = (a.buckets + BLOCK - 1) / BLOCK;
+    uint32_t c[PER], t[PER], sum = 0, before = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int f = tid * per + j;
+      const bool in = j < per && f < a.buckets;
+      c[j] = in ? s_off[f] : 0u;
+      t[j] = in ? a.totals[f] : 0u;
+      sum += c[j];
+      before += t[j];
+    }
+    uint32_t all;
+    uint32_t at = block_exclusive_scan<BLOCK>(sum, s_wave, &all);
+    uint32_t start = block_exclusive_scan<BLOCK>(before, s_wave, &all);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int f = tid * per + j;
+      if (j < per && f < a.buckets) {
+        s_off[f] = at;
+        s_delta[f] = start - at;
+        if (tile == 0) a.starts[f] = start;
+      }
+      at += c[j];
+      start += t[j];
+    }
+    if (tile == 0 && tid == 0) a.starts[a.buckets] = all;
+  }
+  __syncthreads();
+  const uint32_t* base = a.base + tile * int64_t(a.buckets);
+  for (int f = tid; f < a.buckets; f += BLOCK) s_delta[f] += base[f];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    if (pos[i] == 0xFFFFFFFFu) continue;
+    pos[i] += s_off[fb[i]];
+    s_id[pos[i]] = uint16_t(fb[i]);
+  }
+  const int total = int(i1 - i0);
+  for (int q0 = 0; q0 < total; q0 += Q) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      const uint32_t q = pos[i] - uint32_t(q0);
+      if (q < uint32_t(Q)) store_words<S>(s_stage + q * S, e[i]);
+    }
+    __syncthreads();
+    for (int j = tid; j < min(Q, total - q0); j += BLOCK) {
+      uint32_t x[S];
+      load_words<S>(s_stage + j * S, x);
+      const uint32_t at = s_delta[s_id[q0 + j]] + uint32_t(q0 + j);
+      if (int64_t(at) < a.n) store_words<S>(a.elems + int64_t(at) * S, x);
+    }
+    __syncthreads();
+  }
+}
+
+struct GroupBucketArgs {
+  GroupArgs g;              // elems, n, pairs, rep, cmap, uelems, chunks, range_sums, ranges, mesh_*
+  const uint32_t* starts;   // [buckets + 1]
+  int32_t buckets;          // the grid
+};
+
+// Groups of one bucket, whose records stream past a table in LDS. A thread
+// that finds an empty slot writes its record to a free place of the list of
+// distinct records and then publishes the place in the slot; if another
+// thread was faster it keeps the place for its next new record. A group is
+// named by the bucket's start plus its place (no more places are taken than
+// there are elements), so an element's pair is written at once. When the list
+// is full nothing is added any more; the elements not found in the table by
+// then (all copies of a record alike) wait for the next round, and the
+// groups of such a bucket get dense names.
+template <int K, bool MESH>
+__global__ __launch_bounds__(kGroupBlock, K <= 9 ? 8 : 4) void k_group_bucket(GroupBucketArgs b) {
+  using SH = BucketShape<K>;
+  constexpr int S = SH::S, BLOCK = kGroupBlock, DCAP = SH::DCAP, TS = SH::TS, TB = SH::TB;
+  constexpr int PER = (DCAP + BLOCK - 1) / BLOCK;
+  constexpr uint32_t kEmpty = 0xFFFFFFFFu, kUsedBit = 0x80000000u, kOpen = 0xFFFFFFFFu;
+  __shared__ uint32_t s_key[K * DCAP];     // distinct records, word-major
+  __shared__ uint32_t s_tab[TS];           // place in that list; later dense names
+  __shared__ uint32_t s_min[DCAP];         // smallest id
+  __shared__ uint32_t s_used[DCAP / 32];
+  __shared__ uint32_t s_wave[BLOCK / kWave];
+  __shared__ uint32_t s_n, s_full;
+  __shared__ uint32_t s_big[4];
+  const GroupArgs& a = b.g;
+  const int tid = threadIdx.x;
+  const int64_t f = blockIdx.x;
+  const int64_t b0 = b.starts[f], b1 = b.starts[f + 1];
+  uint32_t used_all = 0;
+  if (b1 - b0 > kGroupSlots) {
+    used_all = group_big_bucket<K, MESH, BLOCK>(a, b0, b1, b0, s_big);
+  } else if (b1 > b0) {
+    const uint32_t cnt = uint32_t(b1 - b0), last = cnt - 1u;
+    const uint32_t* const elems = a.elems + b0 * S;
+    uint2* const pairs = a.pairs + b0;
+    uint32_t names = uint32_t(b0);  // first name of the round
+    for (int round = 0;; ++round) {
+      for (int i = tid; i < TS; i += BLOCK) s_tab[i] = kEmpty;
+      for (int i = tid; i < DCAP; i += BLOCK) s_min[i] = kEmpty;
+      for (int i = tid; i < DCAP / 32; i += BLOCK) s_used[i] = 0;
+      if (tid == 0) s_n = s_full = 0;
+      __syncthreads();
+      uint32_t mine = kEmpty;  // a place of this thread's own in the list
+      // sweep 0 adds records; sweep 1, after the list has filled up, only looks
+      for (int sweep = 0; sweep < 2; ++sweep) {
+        bool open = false;
+        uint32_t next[S];  // the record after the one in hand is on its way
+        load_words<S>(elems + min(uint32_t(tid), last) * S, next);
+        for (uint32_t q = tid; q < cnt; q += BLOCK) {
+          uint32_t e[S];
+#pragma unroll
+          for (int w = 0; w < S; ++w) e[w] = next[w];
+          load_words<S>(elems + min(q + BLOCK, last) * S, next);
+          // found in an earlier round, or by this round's first sweep
+          if ((round > 0 || sweep > 0) && pairs[q].x != kOpen) continue;
+          const uint32_t v = e[K];
+          uint32_t sl = (hash_words<K>(e) * 0x9E3779B1u) >> (32 - TB);
+          uint32_t at = kOpen;
+          while (true) {
+            uint32_t cur = __hip_atomic_load(&s_tab[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (cur == kEmpty) {
+              if (sweep != 0) break;
+              if (mine == kEmpty) mine = atomicAdd(&s_n, 1u);
+              if (mine >= uint32_t(DCAP)) break;
+#pragma unroll
+              for (int w = 0; w < K; ++w) s_key[w * DCAP + mine] = e[w];
+              __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+              cur = atomicCAS(&s_tab[sl], kEmpty, mine);
+              if (cur == kEmpty) {
+                at = mine;
+                mine = kEmpty;
+                break;
+              }
+            }
+            bool eq = true;
+#pragma unroll
+            for (int w = 0; w < K; ++w) eq = eq && s_key[w * DCAP + cur] == e[w];
+            if (eq) {
+              at = cur;
+              break;
+            }
+            sl = (sl + 1) & (TS - 1);
+          }
+          const uint32_t id = v & ~kUsedBit;
+          pairs[q] = make_uint2(at == kOpen ? kOpen : names + at, id);
+          if (at == kOpen) {
+            open = true;
+            continue;
+          }
+          if (id < __hip_atomic_load(&s_min[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+            atomicMin(&s_min[at], id);
+          if ((v & kUsedBit) && !(__hip_atomic_load(&s_used[at >> 5], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP) >> (at & 31) & 1u))
+            atomicOr(&s_used[at >> 5], 1u << (at & 31));
+        }
+        if (open) s_full = 1;
+        __syncthreads();
+        if (s_full == 0) break;
+      }
+      const bool again = s_full != 0;
+      const bool dense = again || round > 0;
+      const uint32_t places = min(s_n, uint32_t(DCAP));
+      // slots of the used groups, and dense names where there are several
+      // rounds; places nobody published are skipped
+      uint32_t x[PER], sum = 0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int d = tid * PER + j;
+        x[j] = d >= DCAP || s_min[d] == kEmpty ? 0u : 1u | (s_used[d >> 5] >> (d & 31) & 1u) << 16;
+        sum += x[j];
+      }
+      uint32_t all;
+      uint32_t at = block_exclusive_scan<BLOCK>(sum, s_wave, &all);
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int d = tid * PER + j;
+        if (x[j] == 0) continue;
+        const uint32_t name = names + (dense ? at & 0xFFFFu : uint32_t(d));
+        s_tab[d] = name;
+        if (x[j] >> 16) {
+          uint32_t e[S];
+#pragma unroll
+          for (int w = 0; w < K; ++w) e[w] = s_key[w * DCAP + d];
+          e[K] = name;
+          store_words<S>(a.uelems + (b0 + used_all + (at >> 16)) * S, e);
+          a.rep[name] = s_min[d];
+        } else {
+          a.cmap[name] = -1;
+        }
+        at += x[j];
+      }
+      static_assert(TS >= DCAP, "names fit the table");
+      used_all += all >> 16;
+      if (!dense) break;
+      __syncthreads();
+      for (uint32_t q = tid; q < cnt; q += BLOCK) {
+        const uint32_t was = pairs[q].x - names;  // earlier rounds' names are smaller, open ones larger
+        if (was < places) pairs[q].x = s_tab[was];
+      }
+      names += all & 0xFFFFu;
+      if (!again) break;
+      __syncthreads();
+    }
+  }
+  if (tid == 0) {
+    a.chunks[f] = make_uint2(uint32_t(b0), used_all);
+    if (used_all) atomicAdd(&a.range_sums[group_run_of(f, gridDim.x, a.ranges)], used_all);
+  }
+}
+
+// Hash buckets of a batch's meshes for k_bucket_count: ceil(vertices /
+// target) each, in mesh order. One workgroup.
+static __global__ __launch_bounds__(1024) void k_mesh_bucket_ranges(const int64_t* __restrict__ off, int32_t nmesh,
+                                                                    int32_t target, uint2* __restrict__ mb) {
+  __shared__ uint32_t s_wave[1024 / kWave];
+  uint32_t carry = 0;
+  for (int64_t b0 = 0; b0 < nmesh; b0 += 1024) {
+    const int64_t b = b0 + threadIdx.x;
+    const uint32_t cnt = b < nmesh ? uint32_t((off[b + 1] - off[b] + target - 1) / target) : 0u;
+    uint32_t total;
+    const uint32_t ex = block_exclusive_scan<1024>(cnt, s_wave, &total);
+    if (b < nmesh) mb[b] = make_uint2(carry + ex, cnt);
+    carry += total;
+  }
+}
+
+}  // namespace mrx

@@ -112,13 +112,6 @@ __device__ __forceinline__ int32_t flag_load(const int32_t* p) {
 // within microseconds; the bound only keeps a broken launch from hanging.
 constexpr uint32_t kSpinLimit = 1u << 20;
 
-// Pairs (group, original id) of the grouping carry this bit in the id of the
-// smallest copy of a used group, its representative: the step that reads the
-// pairs together with the groups' new ids then writes new2old too (one
-// scattered store per output vertex beside a stream, where a gather of
-// representatives in output order cost 0.08 ms for 4.2M outputs).
-constexpr uint32_t kRepBit = 0x80000000u;
-
 // Control block kept in the (zeroed) workspace.
 struct Control {
   int32_t abort;        // set once any wait exceeds kSpinLimit; all waits then give up

@@ -66,8 +66,8 @@ struct GroupArgs {
   const uint32_t* elems;   // [n][K+1] elements in (hash bucket, id) order
   int64_t n;
   uint32_t bucket_mask;    // bucket of a record = hash & bucket_mask
-  uint2* pairs;            // [n] (group name, original id | kRepBit) per position
-  uint32_t* rep;           // [n] scratch of group_big_bucket: smallest id of a group, by name
+  uint2* pairs;            // [n] (group name, original id) per position
+  uint32_t* rep;           // [n] smallest original id of each used group, by name
   int32_t* cmap;           // [n] -1 for unused groups (used ones are set by the key sort's finalisation)
   uint32_t* uelems;        // [n][K+1] (record, group name) of every used group, in its span's slots
   uint2* chunks;           // [chunks] (span start, used groups)
@@ -97,6 +97,14 @@ __host__ __device__ inline int64_t group_range_start(int64_t w, int64_t tiles, i
   return w * tiles / ranges;
 }
 
+// Run of a chunk: the last one whose first chunk is not after it.
+__device__ __forceinline__ int64_t group_run_of(int64_t tile, int64_t tiles, int64_t ranges) {
+  int64_t w = tile * ranges / tiles;
+  while (w + 1 < ranges && group_range_start(w + 1, tiles, ranges) <= tile) ++w;
+  while (w > 0 && group_range_start(w, tiles, ranges) > tile) --w;
+  return w;
+}
+
 template <int K>
 __device__ __forceinline__ bool lds_keys_equal(const uint32_t* s_keys, int a, int b, int win) {
   bool eq = true;
@@ -121,8 +129,44 @@ constexpr int group_min_waves() {
                         : GroupShape<MESH ? K + 1 : K>::MIN_WAVES_PER_SIMD;
 }
 
-// Groups one bucket of any size that starts at position b0 (the last one of
-// a chunk, running past its window). The distinct records of the bucket hang
+// End of the bucket that starts at position b0 (of the last one of a chunk of
+// k_group that runs past its window): the first position after it whose
+// element hashes elsewhere.
+template <int K, bool MESH, int BLOCK>
+__device__ int64_t end_of_bucket(const GroupArgs& a, int64_t b0, uint32_t* s_x) {
+  constexpr int S = K + 1;
+  constexpr int U = 4;  // elements in flight per thread
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
+  const int tid = threadIdx.x;
+  uint32_t mesh = 0;
+  if constexpr (MESH) mesh = mesh_of(a.mesh_off, a.nmesh, b0, a.mesh_tab);
+  const int64_t lim = MESH ? min(a.n, a.mesh_off[mesh + 1]) : a.n;  // buckets belong to meshes
+  auto bucket_at = [&](int64_t p) {
+    uint32_t e[S];
+    load_words<S>(a.elems + p * S, e);
+    if constexpr (MESH) return mesh_bucket(a.mesh_buckets, mesh, hash_mesh_words<K>(mesh, e));
+    else return hash_words<K>(e) & a.bucket_mask;
+  };
+  const uint32_t bucket = bucket_at(b0);
+  if (tid == 0) s_x[0] = kNone;
+  __syncthreads();
+  for (int64_t base = b0 + 1; base < lim; base += BLOCK * U) {
+    uint32_t first = kNone;
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t p = base + r * BLOCK + tid;
+      if (p < lim && bucket_at(p) != bucket) first = min(first, uint32_t(p));
+    }
+    if (first != kNone) atomicMin(&s_x[0], first);
+    __syncthreads();
+    const uint32_t end = s_x[0];
+    __syncthreads();
+    if (end != kNone) return end;
+  }
+  return lim;
+}
+
+// Groups one bucket of any size, [b0, b1). The distinct records of the bucket hang
 // in chains off a table in `uelems`, of which the bucket's positions own two
 // words each (head of a chain, next of a node) until its elements are written
 // there; a node is the position of some copy and names its group. The record
@@ -135,53 +179,14 @@ constexpr int group_min_waves() {
 // value needs over a million copies before that is felt in a call. Returns
 // the number of used groups; their elements start at slot `upre`.
 template <int K, bool MESH, int BLOCK>
-__device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t upre, uint32_t* s_x) {
+__device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t b1, int64_t upre, uint32_t* s_x) {
   constexpr int S = K + 1;
   constexpr int U = 4;  // elements in flight per thread
   constexpr uint32_t kNone = 0xFFFFFFFFu, kUsedBit = 0x80000000u;
   constexpr int32_t kUsedMark = -2;
   const int tid = threadIdx.x;
-  const int64_t n = a.n;
-  uint32_t mesh = 0;
-  if constexpr (MESH) mesh = mesh_of(a.mesh_off, a.nmesh, b0, a.mesh_tab);
-  // bucket and hash of the element at a position (all of one mesh: buckets
-  // belong to meshes, and a mesh's positions are its vertex range)
-  auto hash_of = [&](const uint32_t(&e)[S]) {
-    if constexpr (MESH) return hash_mesh_words<K>(mesh, e);
-    else return hash_words<K>(e);
-  };
-  const int64_t lim = MESH ? min(n, a.mesh_off[mesh + 1]) : n;
-  auto bucket_of = [&](uint32_t h) {
-    if constexpr (MESH) return mesh_bucket(a.mesh_buckets, mesh, h);
-    else return h & a.bucket_mask;
-  };
   uint32_t hot[S];
   load_words<S>(a.elems + b0 * S, hot);
-  const uint32_t bucket = bucket_of(hash_of(hot));
-  // ---- end of the bucket
-  if (tid == 0) s_x[0] = kNone;
-  __syncthreads();
-  int64_t b1 = lim;
-  for (int64_t base = b0 + 1; base < lim; base += BLOCK * U) {
-    uint32_t first = kNone;
-#pragma unroll
-    for (int r = 0; r < U; ++r) {
-      const int64_t p = base + r * BLOCK + tid;
-      if (p < lim) {
-        uint32_t e[S];
-        load_words<S>(a.elems + p * S, e);
-        if (bucket_of(hash_of(e)) != bucket) first = min(first, uint32_t(p));
-      }
-    }
-    if (first != kNone) atomicMin(&s_x[0], first);
-    __syncthreads();
-    const uint32_t end = s_x[0];
-    __syncthreads();
-    if (end != kNone) {
-      b1 = end;
-      break;
-    }
-  }
   const uint32_t cnt = uint32_t(b1 - b0);
   uint32_t* const table = a.uelems + b0 * S;  // head of chain h: [h * S], next of node b0 + i: [i * S + 1]
   for (uint32_t i = tid; i < cnt; i += BLOCK) lb_store(table + int64_t(i) * S, kNone);
@@ -216,7 +221,7 @@ __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t upr
         if ((e[r][K] & kUsedBit) && s_x[1] == 0u) s_x[1] = 1u;
         if (id < s_x[2]) atomicMin(&s_x[2], id);
       } else {
-        const uint32_t h = uint32_t((uint64_t(hash_of(e[r]) * 0x9E3779B1u) * cnt) >> 32);
+        const uint32_t h = __umulhi(hash_words<K>(e[r]) * 0x9E3779B1u, cnt);
         uint32_t* const head = table + int64_t(h) * S;
         uint32_t seen = kNone;  // nodes from here on are known not to match
         uint32_t cur = lb_load(head);
@@ -255,13 +260,9 @@ __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t upr
     __threadfence();
   }
   __syncthreads();
-  // ---- representatives, and one element per used group (the table is no
-  // longer needed)
+  // ---- one element per used group (the table is no longer needed)
   for (int64_t p = b0 + tid; p < b1; p += BLOCK) {
-    const uint2 pr = a.pairs[p];  // written by this thread
-    if (lb_load(cm + pr.x) != uint32_t(kUsedMark)) continue;
-    if (lb_load(rep + pr.x) == pr.y) a.pairs[p].y = pr.y | kRepBit;
-    if (pr.x != uint32_t(p)) continue;
+    if (a.pairs[p].x != uint32_t(p) || lb_load(cm + p) != uint32_t(kUsedMark)) continue;
     const int64_t u = upre + atomicAdd(&s_x[3], 1u);
     uint32_t e[S];
     load_words<S>(a.elems + p * S, e);
@@ -476,9 +477,10 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
       atomicMax(a.status, 7 /* MRX_ERR_INTERNAL */);
       continue;
     }
-    a.pairs[pos] = make_uint2(g, org | ((uheadm >> i) & 1u ? kRepBit : 0u));
+    a.pairs[pos] = make_uint2(g, org);
     if (!((headm >> i) & 1u)) continue;
     if ((uheadm >> i) & 1u) {
+      a.rep[g] = org;
       const uint32_t u = upre + (ranks >> 16);
       if (int64_t(u) >= n) {
         atomicMax(a.status, 7 /* MRX_ERR_INTERNAL */);
@@ -494,16 +496,15 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
     }
   }
   uint32_t u_own = active ? ut : 0u;
-  if (over) u_own += group_big_bucket<K, MESH, BLOCK>(a, c0 - 1 + int(s_lq), int64_t(upre) + ut, s_big);
+  if (over) {
+    const int64_t big = c0 - 1 + int(s_lq);
+    const int64_t big_end = end_of_bucket<K, MESH, BLOCK>(a, big, s_big);
+    u_own += group_big_bucket<K, MESH, BLOCK>(a, big, big_end, int64_t(upre) + ut, s_big);
+  }
   // ---- the chunk's record and its share of its run's sum
   if (tid == 0) {
     a.chunks[tile] = make_uint2(span0, u_own);
-    // run of this chunk: the last w whose first chunk is at most `tile`
-    const int64_t T = int64_t(gridDim.x);
-    int64_t w = int64_t(tile) * a.ranges / T;
-    while (w + 1 < a.ranges && group_range_start(w + 1, T, a.ranges) <= tile) ++w;
-    while (w > 0 && group_range_start(w, T, a.ranges) > tile) --w;
-    if (u_own) atomicAdd(&a.range_sums[w], u_own);
+    if (u_own) atomicAdd(&a.range_sums[group_run_of(tile, gridDim.x, a.ranges)], u_own);
   }
 }
 

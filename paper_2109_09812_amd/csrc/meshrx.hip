@@ -691,6 +691,64 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
   v.finalize(fa, grid_for(n, 256, 4096), s);
 }
 
+// Where the bucket path (bucket_kernels.hpp) keeps its state: starts, totals,
+// chunk records and run sums in the look-back words, which nothing else uses
+// on that path, and the counts in the buffer that takes the pairs.
+struct BucketState {
+  BucketPlan plan;           // buckets = 0: the call sorts by hash digits instead
+  BucketArgs args{};
+  uint2* chunks = nullptr;
+  uint32_t* range_sums = nullptr;
+  int64_t ranges = 0;
+};
+
+BucketState bucket_state(const SortVariant& v, Layout L, int64_t n, int K, int32_t nmesh, uint32_t* lookback,
+                         uint32_t* matrix) {
+  BucketState b;
+  const BucketGroup& g = nmesh > 1 ? v.bucket_mesh : v.bucket;
+  const BucketPlan p = g.plan(n, nmesh, n * int64_t(K + 1));
+  const int64_t F = p.buckets;
+  const int64_t ranges = group_compact_ranges(F);
+  if (F == 0 || F > (nmesh > 1 ? kBucketMaxMesh : kBucketMax) ||
+      4 * F + 2 + ranges > 2 * L.tiles_sort * int64_t(v.radix()))
+    return b;
+  L.tiles_group = F;
+  if (!split_applies(v, L, n, K)) return b;
+  b.plan = p;
+  b.chunks = reinterpret_cast<uint2*>(lookback);
+  b.args.starts = lookback + 2 * F;
+  b.args.totals = b.args.starts + F + 1;
+  b.range_sums = b.args.totals + F;
+  b.ranges = ranges;
+  b.args.n = n;
+  b.args.buckets = int32_t(F);
+  b.args.tiles = p.tiles;
+  b.args.tile = kBucketBlock * p.ept;
+  b.args.stride = int32_t((F + 1) / 2 * 2);
+  b.args.counts = reinterpret_cast<uint16_t*>(matrix);
+  b.args.base = matrix + p.count_words();
+  return b;
+}
+
+// Elements into their buckets (in args.elems) and the buckets grouped.
+void group_buckets(const BucketState& b, const BucketGroup& g, const MarkArgs* mark, const BandArgs* band,
+                   GroupArgs ga, hipStream_t s) {
+  prof_mark(mark || band ? "mark_bucket_count" : "bucket_count", s);
+  g.count(b.args, mark, band, s);
+  prof_mark("bucket_offsets", s);
+  hipLaunchKernelGGL(k_bucket_offsets, dim3((b.args.buckets + kOffsetCols - 1) / kOffsetCols),
+                     dim3(kOffsetCols * kOffsetRuns), 0, s, b.args);
+  prof_mark("bucket_scatter", s);
+  g.scatter(b.args, s);
+  ga.elems = b.args.elems;
+  ga.chunks = b.chunks;
+  ga.range_sums = b.range_sums;
+  ga.ranges = b.ranges;
+  const GroupBucketArgs a{ga, b.args.starts, b.args.buckets};
+  prof_mark("group", s);
+  g.group(a, s);
+}
+
 // The hash-grouping launch sequence of one mesh (see group_kernels.hpp):
 //   Step 1 (marking, by vertex bands or by scattered stores) with the
 //   hash-digit histograms; stable sort of (record, id | used << 31) by
@@ -705,11 +763,12 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
 // partition when only the marking goes by bands); the ordering works in X and
 // C; by bands, Step 4 then partitions the pairs into X and puts the index
 // entries' new ids in C.
-mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, int64_t num_vtx,
+mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* vtx, int64_t num_vtx,
                        int32_t vtx_bytes, const int32_t* idx, int64_t num_elems, int32_t arity,
                        const int64_t* live_elems, void* out_vtx, int32_t* out_idx, int32_t* old2new,
                        int32_t* new2old, int64_t* out_num_vtx, int32_t* dev_status, void* workspace,
                        const mrx_tuning* tuning, void* stream_, bool state_zeroed) {
+  Layout L = layout;
   const int K = vtx_bytes / 4;
   const int64_t n = num_vtx, m = num_elems * arity;
   const int ph = L.P_hash;
@@ -725,7 +784,6 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   uint64_t* lookback = reinterpret_cast<uint64_t*>(ws + L.lookback);
   uint2* group_chunks = reinterpret_cast<uint2*>(ws + L.group_chunks);
   uint32_t* group_range_sums = reinterpret_cast<uint32_t*>(ws + L.group_ranges);
-  const int64_t group_ranges = group_compact_ranges(L.tiles_group);
   const bool wide = wide_lookback(n, tuning);
   const bool claimed = tuning && (tuning->flags & MRX_TUNING_CLAIMED_TILES);
   uint32_t* const lb32[2] = {reinterpret_cast<uint32_t*>(lookback),
@@ -739,6 +797,12 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   int counter = 0;  // next tile counter (claimed tiles)
   auto next_counter = [&]() { return claimed ? counters + counter++ : nullptr; };
 
+  // one partition pass where the buckets suffice, else two or three stable
+  // passes by hash digits; the order of the used groups takes either's chunks
+  BucketState bs = bucket_state(v, L, n, K, 1, reinterpret_cast<uint32_t*>(lookback), buf[1]);
+  const bool bucketed = bs.plan.buckets > 0;
+  if (bucketed) L.tiles_group = bs.plan.buckets;
+  const int64_t group_ranges = group_compact_ranges(L.tiles_group);
   if (!state_zeroed) {
     // band marking writes every used flag: those need no clearing
     const int64_t words = int64_t((L.band.mode != kBandNone ? L.used_v : L.zero_end) / 16);
@@ -765,71 +829,81 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
   uint32_t* itable = band_tab;
   uint32_t* itile_valid = itable + size_t(bp.nb) * size_t(bp.itiles);
   uint32_t* ptable = itile_valid + bp.itiles;
+  const BandArgs ba{idx, m, arity, n, live_elems, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0,
+                    bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, bp.fine ? 1 : 0, ipart, itable, itile_valid, used_v,
+                    status, nullptr, nullptr, nullptr, 0};
   if (bp.mode != kBandNone) {
-    const BandArgs ba{idx, m, arity, n, live_elems, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0,
-                      bp.mode == kMarkAndMap ? 1 : 0, bp.itiles, bp.fine ? 1 : 0, ipart, itable, itile_valid, used_v, status, nullptr,
-                      nullptr, nullptr, 0};
     prof_mark("band_partition", s);
     launch_band_partition(ba, s);
-    if (bp.mode == kMarkAndMap) {
-      prof_mark("band_mark_histogram", s);
-      v.band_mark_hash_hist(ba, static_cast<const uint32_t*>(vtx), n, ph, hist_hash, s);
-    } else {
-      prof_mark("band_mark", s);
-      launch_band_mark(ba, false, s);
-    }
   }
-  if (bp.mode != kMarkAndMap) {
-    const bool fused_mark = m > 0 && bp.mode == kBandNone;
-    prof_mark(fused_mark ? "mark_histogram" : "hash_histogram", s);
-    v.hash_hist(fused_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, ph, hist_hash, s);
+  if (bp.mode == kMarkOnly) {
+    prof_mark("band_mark", s);
+    launch_band_mark(ba, false, s);
+  }
+  const bool band_mark = bp.mode == kMarkAndMap, scatter_mark = m > 0 && bp.mode == kBandNone;
+  if (!bucketed) {
+    prof_mark(band_mark ? "band_mark_histogram" : scatter_mark ? "mark_histogram" : "hash_histogram", s);
+    if (band_mark)
+      v.band_mark_hash_hist(ba, static_cast<const uint32_t*>(vtx), n, ph, hist_hash, s);
+    else
+      v.hash_hist(scatter_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, ph, hist_hash, s);
   }
   if (n > 0) {
-    // stable sort by the hash digits; every hash pass runs (dead flags go to
-    // a word nobody reads), so the elements end in X = buf[(ph - 1) & 1]
-    prof_mark("scan_buckets", s);
-    v.scan(hist_hash, ph, n, nullptr, dead_hash, s);
-    const SortBuffers sbh{{buf[0], buf[1]}, plan_hash, ph};
+    uint32_t* X = buf[0];
+    uint32_t* Y = buf[1];
     int gp = 0;  // index of the pass in the call (look-back buffer parity, tag)
-    for (int p = 0; p < ph; ++p, ++gp) {
-      SortPassArgs a{};
-      a.vtx = static_cast<const uint32_t*>(vtx);
-      a.bufs = sbh;
-      a.pass = p;
-      a.used = used_v;
-      a.bucket_base = hist_hash + size_t(p) * v.radix();
-      a.lookback = wide ? static_cast<void*>(lookback) : static_cast<void*>(lb32[gp & 1]);
-      a.lookback_next = lb32[(gp + 1) & 1];
-      a.tile_counter = next_counter();
-      a.ctl = ctl;
-      a.status = status;
-      a.n = n;
-      a.lo_word = a.hi_word = -1;
-      a.shift = p * v.D;
-      a.tag = uint32_t(gp + 1);
-      prof_mark(p == 0 ? "onesweep_hash_first" : "onesweep_hash", s);
-      v.pass(a, p == 0 ? kPassFirstHash : kPassHash, wide, L.tiles_sort, s);
-    }
-    uint32_t* X = buf[(ph - 1) & 1];
-    uint32_t* Y = buf[((ph - 1) & 1) ^ 1];
-    uint2* pairs = reinterpret_cast<uint2*>(Y);
-
-    // group each hash bucket
     GroupArgs g{};
-    g.elems = X;
     g.n = n;
-    g.bucket_mask = ph * v.D >= 32 ? 0xFFFFFFFFu : (1u << (ph * v.D)) - 1u;
-    g.pairs = pairs;
     g.rep = reinterpret_cast<uint32_t*>(rep);
     g.cmap = cmap;
     g.uelems = buf[2];
-    g.chunks = group_chunks;
-    g.range_sums = group_range_sums;
-    g.ranges = group_ranges;
     g.status = status;
-    prof_mark("group", s);
-    v.group(g, L.tiles_group, s);
-
+    if (bucketed) {
+      bs.args.vtx = static_cast<const uint32_t*>(vtx);
+      bs.args.used = used_v;
+      bs.args.elems = X;
+      g.pairs = reinterpret_cast<uint2*>(Y);
+      group_chunks = bs.chunks;
+      group_range_sums = bs.range_sums;
+      group_buckets(bs, v.bucket, scatter_mark ? &mark : nullptr, band_mark ? &ba : nullptr, g, s);
+    } else {
+      // stable sort by the hash digits; every hash pass runs (dead flags go to
+      // a word nobody reads), so the elements end in X = buf[(ph - 1) & 1]
+      prof_mark("scan_buckets", s);
+      v.scan(hist_hash, ph, n, nullptr, dead_hash, s);
+      const SortBuffers sbh{{buf[0], buf[1]}, plan_hash, ph};
+      for (int p = 0; p < ph; ++p, ++gp) {
+        SortPassArgs a{};
+        a.vtx = static_cast<const uint32_t*>(vtx);
+        a.bufs = sbh;
+        a.pass = p;
+        a.used = used_v;
+        a.bucket_base = hist_hash + size_t(p) * v.radix();
+        a.lookback = wide ? static_cast<void*>(lookback) : static_cast<void*>(lb32[gp & 1]);
+        a.lookback_next = lb32[(gp + 1) & 1];
+        a.tile_counter = next_counter();
+        a.ctl = ctl;
+        a.status = status;
+        a.n = n;
+        a.lo_word = a.hi_word = -1;
+        a.shift = p * v.D;
+        a.tag = uint32_t(gp + 1);
+        prof_mark(p == 0 ? "onesweep_hash_first" : "onesweep_hash", s);
+        v.pass(a, p == 0 ? kPassFirstHash : kPassHash, wide, L.tiles_sort, s);
+      }
+      X = buf[(ph - 1) & 1];
+      Y = buf[((ph - 1) & 1) ^ 1];
+      // group each hash bucket
+      g.elems = X;
+      g.pairs = reinterpret_cast<uint2*>(Y);
+      g.bucket_mask = ph * v.D >= 32 ? 0xFFFFFFFFu : (1u << (ph * v.D)) - 1u;
+      g.chunks = group_chunks;
+      g.range_sums = group_range_sums;
+      g.ranges = group_ranges;
+      prof_mark("group", s);
+      v.group(g, L.tiles_group, s);
+    }
+    uint2* pairs = reinterpret_cast<uint2*>(Y);
     OrderArgs o{};
     o.X = X;
     o.C = buf[2];
@@ -854,7 +928,8 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
       // X and C are free again: X takes the partitioned pairs, C the new ids
       // of the index entries
       const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
-                            reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0, nullptr,
+                            reinterpret_cast<uint2*>(X), ptable, status,
+                            reinterpret_cast<const uint32_t*>(rep), new2old, SortBuffers{}, 0, nullptr,
                             nullptr, nullptr, 0};
       prof_mark("pair_partition", s);
       launch_pair_partition(pa, bp.fine, s);
@@ -872,7 +947,7 @@ mrx_status launch_hash(const SortVariant& v, const Layout& L, const void* vtx, i
     prof_mark("old2new", s);
     hipLaunchKernelGGL((k_scatter_old2new<false>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                        SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs), cmap, n, nullptr,
-                       nullptr, 0, nullptr, old2new, new2old);
+                       nullptr, 0, nullptr, old2new, reinterpret_cast<const uint32_t*>(rep), new2old);
   }
   // Step 4: remap the index array
   if (m > 0) {
@@ -1068,7 +1143,7 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
     prof_mark("old2new", s);
     hipLaunchKernelGGL((k_scatter_old2new<false>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                        sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0, nullptr, old2new,
-                       static_cast<int32_t*>(nullptr));
+                       static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr));
   }
   // Step 4: remap the index array
   if (m > 0) {
@@ -1089,11 +1164,12 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
 // are ordered by (mesh id, record), the mesh of an element being that of its
 // name. New ids are numbered over the whole batch and made mesh-local by the
 // old2new scatter.
-mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void* vtx, const int64_t* vtx_offsets,
+mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const void* vtx, const int64_t* vtx_offsets,
                                int64_t n, int32_t vtx_bytes, const int32_t* idx, const int64_t* elem_offsets,
                                int64_t total_elems, int32_t arity, int32_t num_meshes, void* out_vtx,
                                int64_t* out_vtx_offsets, int32_t* out_idx, int32_t* old2new, int32_t* new2old,
                                int32_t* dev_status, void* workspace, const mrx_tuning* tuning, void* stream_) {
+  Layout L = layout;
   const int K = vtx_bytes / 4;
   const int64_t m = total_elems * arity;
   const int ph = L.P_hash;
@@ -1109,7 +1185,6 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   uint64_t* lookback = reinterpret_cast<uint64_t*>(ws + L.lookback);
   uint2* group_chunks = reinterpret_cast<uint2*>(ws + L.group_chunks);
   uint32_t* group_range_sums = reinterpret_cast<uint32_t*>(ws + L.group_ranges);
-  const int64_t group_ranges = group_compact_ranges(L.tiles_group);
   const bool wide = wide_lookback(n, tuning);
   const bool claimed = tuning && (tuning->flags & MRX_TUNING_CLAIMED_TILES);
   uint32_t* const lb32[2] = {reinterpret_cast<uint32_t*>(lookback),
@@ -1125,6 +1200,11 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   int32_t* status = dev_status;
   int counter = 0;  // next tile counter (claimed tiles)
   auto next_counter = [&]() { return claimed ? counters + counter++ : nullptr; };
+
+  BucketState bs = bucket_state(v, L, n, K, num_meshes, reinterpret_cast<uint32_t*>(lookback), buf[1]);
+  const bool bucketed = bs.plan.buckets > 0;
+  if (bucketed) L.tiles_group = bs.plan.buckets;
+  const int64_t group_ranges = group_compact_ranges(L.tiles_group);
 
   prof_mark("fill_zero", s);
   hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(int64_t(L.zero_end / 16), 256, 4096)), dim3(256), 0, s,
@@ -1143,8 +1223,11 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
     etab = nullptr;
   }
   prof_mark("mesh_buckets", s);
-  hipLaunchKernelGGL(k_mesh_buckets, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes,
-                     int32_t(v.group_mesh_target_bucket), mbk);
+  if (bucketed)
+    hipLaunchKernelGGL(k_mesh_bucket_ranges, dim3(1), dim3(1024), 0, s, vtx_offsets, num_meshes, bs.plan.target, mbk);
+  else
+    hipLaunchKernelGGL(k_mesh_buckets, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes,
+                       int32_t(v.group_mesh_target_bucket), mbk);
   // Step 1 by vertex bands, or by scattered byte stores beside the
   // bucket-digit histograms of the stable sort of (record, id | used << 31)
   // by the buckets of (mesh id, record)
@@ -1163,68 +1246,85 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   uint32_t* itable = band_tab;
   uint32_t* itile_valid = itable + size_t(bp.nb) * size_t(bp.itiles);
   uint32_t* ptable = itile_valid + bp.itiles;
+  const BandArgs ba{idx, m, arity, n, nullptr, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0, 1, bp.itiles, 1,
+                    ipart, itable, itile_valid, used_v, status, vtx_offsets, elem_offsets, etab, num_meshes};
   if (bands) {
-    const BandArgs ba{idx, m, arity, n, nullptr, bp.shift, bp.nb, aligned(idx, 16) ? 1 : 0, 1, bp.itiles, 1,
-                      ipart, itable, itile_valid, used_v, status, vtx_offsets, elem_offsets, etab, num_meshes};
     prof_mark("band_partition", s);
     launch_band_partition(ba, s);
-    prof_mark("band_mark", s);
-    launch_band_mark(ba, true, s);
   }
   const MarkArgs mark{idx, m, arity, n, vtx_offsets, elem_offsets, num_meshes, etab, nullptr, used_v, status};
-  const bool fused_mark = m > 0 && !bands;
-  prof_mark(fused_mark ? "mark_histogram" : "hash_histogram", s);
-  v.hash_mesh_hist(fused_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, vtx_offsets, num_meshes, vtab, mbk,
-                   ph, hist_hash, s);
-  prof_mark("scan_buckets", s);
-  v.scan(hist_hash, ph, n, nullptr, dead_hash, s);
-  const SortBuffers sbh{{buf[0], buf[1]}, plan_hash, ph};
+  const bool scatter_mark = m > 0 && !bands;
+  uint32_t* X = buf[0];
+  uint32_t* Y = buf[1];
   int gp = 0;  // index of the pass in the call (look-back buffer parity, tag)
-  for (int p = 0; p < ph; ++p, ++gp) {
-    SortPassArgs a{};
-    a.vtx = static_cast<const uint32_t*>(vtx);
-    a.bufs = sbh;
-    a.pass = p;
-    a.used = used_v;
-    a.bucket_base = hist_hash + size_t(p) * v.radix();
-    a.lookback = wide ? static_cast<void*>(lookback) : static_cast<void*>(lb32[gp & 1]);
-    a.lookback_next = lb32[(gp + 1) & 1];
-    a.tile_counter = next_counter();
-    a.ctl = ctl;
-    a.status = status;
-    a.n = n;
-    a.mesh_off = vtx_offsets;
-    a.mesh_tab = vtab;
-    a.mesh_buckets = mbk;
-    a.nmesh = num_meshes;
-    a.lo_word = a.hi_word = -1;
-    a.shift = p * v.D;
-    a.tag = uint32_t(gp + 1);
-    prof_mark(p == 0 ? "onesweep_hash_first" : "onesweep_hash", s);
-    v.pass(a, p == 0 ? kPassFirstHashMesh : kPassHashMesh, wide, L.tiles_sort, s);
-  }
-  uint32_t* X = buf[(ph - 1) & 1];
-  uint32_t* Y = buf[((ph - 1) & 1) ^ 1];
-  uint2* pairs = reinterpret_cast<uint2*>(Y);
-
-  // group each bucket by (mesh id, record)
   GroupArgs g{};
-  g.elems = X;
   g.n = n;
-  g.pairs = pairs;
   g.rep = reinterpret_cast<uint32_t*>(rep);
   g.cmap = cmap;
   g.uelems = buf[2];
-  g.chunks = group_chunks;
-  g.range_sums = group_range_sums;
-  g.ranges = group_ranges;
   g.status = status;
   g.mesh_off = vtx_offsets;
   g.mesh_tab = vtab;
   g.mesh_buckets = mbk;
   g.nmesh = num_meshes;
-  prof_mark("group", s);
-  v.group_mesh(g, L.tiles_group, s);
+  if (bucketed) {
+    bs.args.vtx = static_cast<const uint32_t*>(vtx);
+    bs.args.used = used_v;
+    bs.args.elems = X;
+    bs.args.mesh_off = vtx_offsets;
+    bs.args.mesh_tab = vtab;
+    bs.args.mesh_buckets = mbk;
+    bs.args.nmesh = num_meshes;
+    g.pairs = reinterpret_cast<uint2*>(Y);
+    group_chunks = bs.chunks;
+    group_range_sums = bs.range_sums;
+    group_buckets(bs, v.bucket_mesh, scatter_mark ? &mark : nullptr, bands ? &ba : nullptr, g, s);
+  } else {
+    if (bands) {
+      prof_mark("band_mark", s);
+      launch_band_mark(ba, true, s);
+    }
+    prof_mark(scatter_mark ? "mark_histogram" : "hash_histogram", s);
+    v.hash_mesh_hist(scatter_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, vtx_offsets, num_meshes,
+                     vtab, mbk, ph, hist_hash, s);
+    prof_mark("scan_buckets", s);
+    v.scan(hist_hash, ph, n, nullptr, dead_hash, s);
+    const SortBuffers sbh{{buf[0], buf[1]}, plan_hash, ph};
+    for (int p = 0; p < ph; ++p, ++gp) {
+      SortPassArgs a{};
+      a.vtx = static_cast<const uint32_t*>(vtx);
+      a.bufs = sbh;
+      a.pass = p;
+      a.used = used_v;
+      a.bucket_base = hist_hash + size_t(p) * v.radix();
+      a.lookback = wide ? static_cast<void*>(lookback) : static_cast<void*>(lb32[gp & 1]);
+      a.lookback_next = lb32[(gp + 1) & 1];
+      a.tile_counter = next_counter();
+      a.ctl = ctl;
+      a.status = status;
+      a.n = n;
+      a.mesh_off = vtx_offsets;
+      a.mesh_tab = vtab;
+      a.mesh_buckets = mbk;
+      a.nmesh = num_meshes;
+      a.lo_word = a.hi_word = -1;
+      a.shift = p * v.D;
+      a.tag = uint32_t(gp + 1);
+      prof_mark(p == 0 ? "onesweep_hash_first" : "onesweep_hash", s);
+      v.pass(a, p == 0 ? kPassFirstHashMesh : kPassHashMesh, wide, L.tiles_sort, s);
+    }
+    X = buf[(ph - 1) & 1];
+    Y = buf[((ph - 1) & 1) ^ 1];
+    // group each bucket by (mesh id, record)
+    g.elems = X;
+    g.pairs = reinterpret_cast<uint2*>(Y);
+    g.chunks = group_chunks;
+    g.range_sums = group_range_sums;
+    g.ranges = group_ranges;
+    prof_mark("group", s);
+    v.group_mesh(g, L.tiles_group, s);
+  }
+  uint2* pairs = reinterpret_cast<uint2*>(Y);
 
   OrderArgs o{};
   o.X = X;
@@ -1252,7 +1352,8 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   // Step 4's map and new2old, both mesh-local, remap
   if (bands) {
     const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
-                          reinterpret_cast<uint2*>(X), ptable, status, new2old, SortBuffers{}, 0, vtx_offsets,
+                          reinterpret_cast<uint2*>(X), ptable, status,
+                          reinterpret_cast<const uint32_t*>(rep), new2old, SortBuffers{}, 0, vtx_offsets,
                           out_vtx_offsets, vtab, num_meshes};
     prof_mark("pair_partition", s);
     launch_pair_partition(pa, true, s);
@@ -1271,7 +1372,8 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& L, const void
   hipLaunchKernelGGL((k_scatter_old2new<true>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                      SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs), cmap, n,
                      vtx_offsets, static_cast<const int64_t*>(out_vtx_offsets), num_meshes,
-                     static_cast<const int32_t*>(vtab), old2new, new2old);
+                     static_cast<const int32_t*>(vtab), old2new,
+                     reinterpret_cast<const uint32_t*>(rep), new2old);
   if (m > 0) {
     prof_mark("remap", s);
     hipLaunchKernelGGL((k_remap<true>), dim3(rand_grid(m)), dim3(kRandBlock), 0, s, idx, m, arity, n, vtx_offsets,
@@ -1599,7 +1701,8 @@ mrx_status mrx_reindex_mesh_batched(const void* vtx, const int64_t* vtx_offsets,
     prof_mark("old2new", s);
     hipLaunchKernelGGL((k_scatter_old2new<true>), dim3(rand_grid(n, kScatterItems)), dim3(kRandBlock), 0, s,
                        sb, static_cast<const uint2*>(nullptr), cmap, n, vtx_offsets, out_vtx_offsets, num_meshes,
-                       static_cast<const int32_t*>(vtab), old2new, static_cast<int32_t*>(nullptr));
+                       static_cast<const int32_t*>(vtab), old2new,
+                       static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr));
     if (new2old) {
       prof_mark("localize_new2old", s);
       hipLaunchKernelGGL(k_localize_new2old, dim3(grid_for(n, 256)), dim3(256), 0, s, new2old,

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "band_kernels.hpp"
+#include "bucket_kernels.hpp"
 #include "group_kernels.hpp"
 #include "scan_kernels.hpp"
 #include "small_kernels.hpp"
@@ -47,6 +48,17 @@ __global__ __launch_bounds__(BLOCK) void k_mark_histogram(MarkArgs ma, const uin
     mark_used_tile<BATCHED>(ma, b - h0);
   }
 }
+
+// One partition pass into hash buckets and their grouping
+// (bucket_kernels.hpp).
+struct BucketGroup {
+  BucketPlan (*plan)(int64_t n, int32_t nmesh, int64_t words) = nullptr;
+  // bucket counts, with Step 1's marking by scattered stores (`mark`) or by
+  // bands (`band`) in the same launch when given
+  void (*count)(const BucketArgs&, const MarkArgs* mark, const BandArgs* band, hipStream_t) = nullptr;
+  void (*scatter)(const BucketArgs&, hipStream_t) = nullptr;
+  void (*group)(const GroupBucketArgs&, hipStream_t) = nullptr;
+};
 
 struct SplitSort {
   SplitScratch (*scratch)(int64_t n, int64_t runs) = nullptr;
@@ -100,6 +112,8 @@ struct SortVariant {
   // small_entries index entries in one workgroup (small_kernels.hpp)
   void (*small)(const SmallArgs&, hipStream_t) = nullptr;
   int small_vertices = 0, small_entries = 0;
+  // hash buckets of one mesh and of a batch
+  BucketGroup bucket, bucket_mesh;
   // sample sort of the used groups (split_kernels.hpp), by record or, for a
   // batch, by (mesh id, record); `n` sizes the grids
   SplitSort split, split_mesh;

@@ -302,8 +302,9 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
 // output offset. A batch's pairs are in mesh order, mesh b's at positions
 // [vtx_off[b], vtx_off[b+1]) (sorted by (mesh id, record), or hash-ordered
 // with per-mesh bucket ranges), so the mesh of an element is that of its
-// position: one lookup for a tile inside one mesh. `new2old` (nullable)
-// receives the ids with kRepBit at their group's new id.
+// position: one lookup for a tile inside one mesh. `new2old` (nullable, after
+// hash grouping) receives the representatives `rep`, given by group name, at
+// their groups' new ids: the pair that holds one is found by comparison.
 template <bool BATCHED>
 __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs, const uint2* pairs_in,
                                                                 const int32_t* __restrict__ cmap, int64_t n,
@@ -311,6 +312,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
                                                                 const int64_t* __restrict__ out_off,
                                                                 int32_t nmesh, const int32_t* __restrict__ vtx_tab,
                                                                 int32_t* __restrict__ old2new,
+                                                                const uint32_t* __restrict__ rep,
                                                                 int32_t* __restrict__ new2old) {
   constexpr int TILE = kRandBlock * kScatterItems;
   const uint2* __restrict__ pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
@@ -364,10 +366,9 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   }
 #pragma unroll
   for (int it = 0; it < kScatterItems; ++it) {
-    const uint32_t id = p[it].y & ~kRepBit;
-    if (int64_t(p[it].x) >= n || int64_t(id) >= n) continue;  // past the end (or a failed wait)
+    if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) continue;  // past the end (or a failed wait)
     int32_t cc = c[it] < 0 ? -1 : c[it];
-    const bool rep = new2old && (p[it].y & kRepBit) && cc >= 0 && cc < n;
+    const bool is_rep = new2old && cc >= 0 && cc < n && rep[p[it].x] == p[it].y;
     if constexpr (BATCHED) {
       if (cc >= 0) {
         int64_t off = tile_off, first = tile_vtx;
@@ -376,13 +377,13 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
           off = out_off[b];
           first = vtx_off[b];
         }
-        if (rep) new2old[cc] = int32_t(int64_t(id) - first);
+        if (is_rep) new2old[cc] = int32_t(int64_t(p[it].y) - first);
         cc -= int32_t(off);
       }
     } else {
-      if (rep) new2old[cc] = int32_t(id);
+      if (is_rep) new2old[cc] = int32_t(p[it].y);
     }
-    old2new[id] = cc;
+    old2new[p[it].y] = cc;
   }
 }
 

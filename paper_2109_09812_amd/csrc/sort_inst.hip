@@ -308,6 +308,44 @@ void launch_flag_scan(const FlagScanArgs& a, bool batched, int64_t grid, hipStre
     hipLaunchKernelGGL((k_flag_scan<K, kScanBlock, kScanIpt, false>), dim3(grid), dim3(kScanBlock), 0, s, a);
 }
 
+template <bool MESH>
+void launch_bucket_count(const BucketArgs& a, const MarkArgs* ma, const BandArgs* ba, hipStream_t s) {
+  if (ba) {
+    const size_t bits_lds = (size_t(1) << ba->shift) / 8;
+    hipLaunchKernelGGL((k_bucket_count<K, MESH, 2>), dim3(a.tiles + ba->nb), dim3(kRandBlock), bits_lds, s, a,
+                       MarkArgs{}, *ba, int64_t(ba->nb));
+  } else if (ma) {
+    const int64_t mt = (ma->m + kRandBlock * kRandItems - 1) / (kRandBlock * kRandItems);
+    hipLaunchKernelGGL((k_bucket_count<K, MESH, 1>), dim3(a.tiles + mt), dim3(kRandBlock), 0, s, a, *ma, BandArgs{},
+                       mt);
+  } else {
+    hipLaunchKernelGGL((k_bucket_count<K, MESH, 0>), dim3(a.tiles), dim3(kRandBlock), 0, s, a, MarkArgs{}, BandArgs{},
+                       int64_t(0));
+  }
+}
+
+template <bool MESH>
+void launch_bucket_scatter(const BucketArgs& a, hipStream_t s) {
+  using SH = BucketShape<K>;
+  constexpr int FMAX = MESH ? kBucketMaxMesh : kBucketMax;
+  if (a.tile == kBucketBlock * SH::EPT)
+    hipLaunchKernelGGL((k_bucket_scatter<K, SH::EPT, FMAX, MESH>), dim3(a.tiles), dim3(kBucketBlock), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_bucket_scatter<K, SH::EPT_SMALL, FMAX, MESH>), dim3(a.tiles), dim3(kBucketBlock), 0, s, a);
+}
+
+template <bool MESH>
+BucketGroup make_bucket() {
+  BucketGroup g;
+  g.plan = &bucket_plan<K>;
+  g.count = &launch_bucket_count<MESH>;
+  g.scatter = &launch_bucket_scatter<MESH>;
+  g.group = [](const GroupBucketArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((k_group_bucket<K, MESH>), dim3(a.buckets), dim3(kGroupBlock), 0, s, a);
+  };
+  return g;
+}
+
 void launch_small(const SmallArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_small<K>), dim3(1), dim3(SmallShape<K>::BLOCK), 0, s, a);
 }
@@ -337,6 +375,8 @@ SortVariant make() {
   v.small = &launch_small;
   v.small_vertices = SmallShape<K>::CAP;
   v.small_entries = SmallShape<K>::MAX_ENTRIES;
+  v.bucket = make_bucket<false>();
+  v.bucket_mesh = make_bucket<true>();
   v.split = make_split<false>();
   v.split_mesh = make_split<true>();
   v.group_mesh = &launch_group_mesh;

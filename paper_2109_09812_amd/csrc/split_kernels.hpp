@@ -13,7 +13,9 @@
 //  * k_split_scatter: the elements bucket by bucket;
 //  * k_split_sort: one workgroup per bucket sorts it in LDS and finishes Step
 //    3: sorted position = new id; output record and the map from group to
-//    new id.
+//    new id. (The representatives wait for the step that reads the pairs with
+//    the groups' new ids: gathered here in output order they cost 0.08 ms for
+//    4.2M, carried along from the scatter on 0.08 ms.)
 // Measured (MI355X) against the packing, LSD passes and finalisation they
 // replace: 4.2M 12-byte values of a 26.4M-vertex soup 0.32 ms (0.67 ms, twelve
 // passes); 65,536 of a 429,165-vertex soup 0.062 ms (0.18 ms); 274,625 32-byte
