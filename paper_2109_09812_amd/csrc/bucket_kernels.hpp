@@ -26,12 +26,13 @@
 namespace mrx {
 
 constexpr int kBucketBlock = 512;
-// Buckets: LDS counters of k_bucket_scatter (20 or 48 KB for two tables of
-// them, so that two workgroups or one share a CU).
+// Buckets: the tables of k_bucket_scatter, 15 or 36 KB of LDS beside the
+// stage, leave room for two workgroups on a CU.
 constexpr int kBucketMax = 2560;      // one mesh
 constexpr int kBucketMaxMesh = 6144;  // batches: at least one per mesh
 constexpr int kBucketMostPer = 10400; // vertices per bucket
 constexpr int kGroupBlock = 1024;     // k_group_bucket
+constexpr int kGroupBlockSmall = 256; // where buckets are aimed to be small
 // larger buckets (values with thousands of copies) go through
 // group_big_bucket, whose time does not depend on how many of them differ
 constexpr int kGroupSlots = 1 << 15;
@@ -42,16 +43,15 @@ struct BucketShape {
   // elements per thread of a large tile (registers) and of a small one
   static constexpr int EPT = K <= 4 ? 16 : K <= 8 ? 8 : 4;
   static constexpr int EPT_SMALL = 4;
-  // slots of the LDS stage (32 KB)
-  static constexpr int STAGE = 8192 / S / 64 * 64;
-  // distinct records a workgroup of k_group_bucket holds (two workgroups per
-  // CU) and its table
+  // slots of the LDS stage (24 KB)
+  static constexpr int STAGE = 6144 / S / 64 * 64;
+  // distinct records a workgroup of k_group_bucket holds (two workgroups per CU)
   static constexpr int DCAP = K == 1 ? 4096 : K <= 4 ? 3072 : K == 5 ? 2560 : K == 6 ? 2048 : K <= 10 ? 1536
                               : 1024;
-  static constexpr int TB = DCAP > 3072 ? 13 : DCAP > 1536 ? 12 : DCAP > 768 ? 11 : 10;
-  static constexpr int TS = 1 << TB;
-  static_assert(TS * 3 >= DCAP * 4, "table load");
   static_assert(DCAP % 32 == 0, "bits of the used groups");
+  // the same for buckets of a few hundred elements: eight small workgroups
+  // on a CU
+  static constexpr int DCAP_SMALL = K <= 8 ? 1024 : 512;
   // average bucket: all distinct records of it fit at once
   static constexpr int TARGET = DCAP * 3 / 4;
 };
@@ -75,7 +75,7 @@ inline BucketPlan bucket_plan(int64_t n, int32_t nmesh, int64_t words) {
   if (n <= 0 || most < 512) return p;
   // about 1,024 buckets where that leaves them small, then as large as fits
   // one round, then as large as the limit on buckets makes them
-  int64_t t = std::max<int64_t>(256, std::min<int64_t>(n / 1024, SH::TARGET));
+  int64_t t = std::max<int64_t>(256, std::min<int64_t>(nmesh > 1 ? n / 2048 : n / 1024, SH::TARGET));
   t = std::max(t, (n + most - 1) / most);
   if (t > kBucketMostPer) return p;
   p.target = int32_t(t);
@@ -114,16 +114,27 @@ struct BucketArgs {
 // Bucket of a record: the hash scaled to the number of buckets (of its mesh).
 __device__ __forceinline__ uint32_t scaled_bucket(uint32_t h, uint32_t buckets) { return __umulhi(h, buckets); }
 
-// Meshes of the first and last vertex of [i0, i1).
+// What is the same for a whole tile [i0, i1): the meshes of its first and last
+// vertex and the buckets it can reach, [first, first + count): those of its
+// meshes, a few of a batch's thousands, and only these columns of the count
+// tables are written and read.
 struct TileMesh {
   uint32_t lo, hi;
   uint2 buckets;  // of mesh lo
+  int32_t first, count;
 };
+template <bool MESH>
 __device__ __forceinline__ TileMesh tile_mesh(const BucketArgs& a, int64_t i0, int64_t i1) {
-  TileMesh t;
-  t.lo = __builtin_amdgcn_readfirstlane(mesh_of(a.mesh_off, a.nmesh, i0, a.mesh_tab));
-  t.hi = __builtin_amdgcn_readfirstlane(mesh_of(a.mesh_off, a.nmesh, i1 - 1, a.mesh_tab));
-  t.buckets = a.mesh_buckets[t.lo];
+  TileMesh t{};
+  t.count = a.buckets;
+  if constexpr (MESH) {
+    t.lo = __builtin_amdgcn_readfirstlane(mesh_of(a.mesh_off, a.nmesh, i0, a.mesh_tab));
+    t.hi = __builtin_amdgcn_readfirstlane(mesh_of(a.mesh_off, a.nmesh, i1 - 1, a.mesh_tab));
+    t.buckets = a.mesh_buckets[t.lo];
+    const uint2 z = a.mesh_buckets[t.hi];
+    t.first = int32_t(t.buckets.x);
+    t.count = min(int32_t(z.x + z.y), a.buckets) - t.first;
+  }
   return t;
 }
 
@@ -139,15 +150,15 @@ __device__ __forceinline__ uint32_t bucket_of(const BucketArgs& a, const TileMes
   }
 }
 
-// Elements per bucket of one tile; s_cnt holds a.buckets words.
+// Elements per bucket of one tile; s_cnt holds a.buckets words (a record's
+// bucket lies in its mesh's range, so within the tile's).
 template <int K, bool MESH, int BLOCK>
 __device__ __forceinline__ void bucket_count_tile(const BucketArgs& a, int64_t tile, uint32_t* s_cnt) {
   constexpr int U = K <= 4 ? 8 : K <= 8 ? 4 : 2;
   const int tid = threadIdx.x;
   const int64_t i0 = tile * a.tile, i1 = min(i0 + a.tile, a.n);
-  for (int f = tid; f < a.buckets; f += BLOCK) s_cnt[f] = 0;
-  TileMesh tm{};
-  if constexpr (MESH) tm = tile_mesh(a, i0, i1);
+  const TileMesh tm = tile_mesh<MESH>(a, i0, i1);
+  for (int f = tid; f < tm.count; f += BLOCK) s_cnt[f] = 0;
   __syncthreads();
   for (int64_t j0 = i0; j0 < i1; j0 += BLOCK * U) {
     uint32_t x[U][K];
@@ -160,13 +171,12 @@ __device__ __forceinline__ void bucket_count_tile(const BucketArgs& a, int64_t t
 #pragma unroll
     for (int r = 0; r < U; ++r) {
       const int64_t i = j0 + r * BLOCK + tid;
-      if (i < i1) atomicAdd(&s_cnt[bucket_of<K, MESH>(a, tm, i, x[r])], 1u);
+      if (i < i1) atomicAdd(&s_cnt[bucket_of<K, MESH>(a, tm, i, x[r]) - tm.first], 1u);
     }
   }
   __syncthreads();
-  uint32_t* row = reinterpret_cast<uint32_t*>(a.counts + tile * int64_t(a.stride));
-  for (int f = 2 * tid; f < a.buckets; f += 2 * BLOCK)
-    row[f >> 1] = s_cnt[f] | (f + 1 < a.buckets ? s_cnt[f + 1] << 16 : 0u);
+  uint16_t* row = a.counts + tile * int64_t(a.stride) + tm.first;
+  for (int f = tid; f < tm.count; f += BLOCK) row[f] = uint16_t(s_cnt[f]);
 }
 
 // Step 1's marking and the bucket counts in one launch, their workgroups
@@ -195,7 +205,8 @@ __global__ __launch_bounds__(kRandBlock) void k_bucket_count(BucketArgs a, MarkA
 // them needs device-wide fences, which took longer than all else here.)
 constexpr int kOffsetCols = 32;
 constexpr int kOffsetRuns = 32;
-static __global__ __launch_bounds__(kOffsetCols* kOffsetRuns) void k_bucket_offsets(BucketArgs a) {
+template <bool MESH>
+__global__ __launch_bounds__(kOffsetCols* kOffsetRuns) void k_bucket_offsets(BucketArgs a) {
   constexpr int U = 16;  // tiles in flight per thread
   __shared__ uint32_t s_sum[kOffsetRuns][kOffsetCols];
   const int tid = threadIdx.x, c = tid % kOffsetCols, run = tid / kOffsetCols;
@@ -204,8 +215,20 @@ static __global__ __launch_bounds__(kOffsetCols* kOffsetRuns) void k_bucket_offs
   const uint16_t* __restrict__ counts = a.counts + f;
   uint32_t* __restrict__ base = a.base + f;
   const int tiles = int(a.tiles), stride = a.stride;
-  const int per = (tiles + kOffsetRuns - 1) / kOffsetRuns;
-  const int t0 = min(run * per, tiles), t1 = min(t0 + per, tiles);
+  int first = 0, end = tiles;  // tiles that reach bucket f
+  if constexpr (MESH) {
+    int lo = 0, hi = a.nmesh - 1;  // last mesh whose buckets start at or before f
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (int(a.mesh_buckets[mid].x) <= f) lo = mid; else hi = mid - 1;
+    }
+    const uint2 b = a.mesh_buckets[lo];
+    const bool in = f < int(b.x + b.y);  // the last columns may belong to no mesh
+    first = in ? int(a.mesh_off[lo] / a.tile) : 0;
+    end = in ? int((a.mesh_off[lo + 1] + a.tile - 1) / a.tile) : 0;
+  }
+  const int per = (end - first + kOffsetRuns - 1) / kOffsetRuns;
+  const int t0 = min(first + run * per, end), t1 = min(t0 + per, end);
   uint32_t sum = 0;
   for (int t = t0; t < t1; t += U) {
     uint32_t x[U];
@@ -231,22 +254,36 @@ static __global__ __launch_bounds__(kOffsetCols* kOffsetRuns) void k_bucket_offs
   }
 }
 
+// Workgroups go to the dies in turn; this gives every die a contiguous range of
+// tiles (-1: none left). Neighbouring tiles write neighbouring runs of every
+// bucket, which then meet in one die's L2 and leave it as whole lines.
+constexpr int kDies = 8;
+__host__ __device__ inline int64_t die_grid(int64_t tiles) { return (tiles + kDies - 1) / kDies * kDies; }
+__device__ __forceinline__ int64_t die_tile(int64_t block, int64_t tiles) {
+  const int64_t per = (tiles + kDies - 1) / kDies;
+  const int64_t t = block % kDies * per + block / kDies;
+  return block / kDies < per && t < tiles ? t : -1;
+}
+
 // One tile's elements to their buckets. FMAX bounds the buckets.
 template <int K, int EPT, int FMAX, bool MESH>
 __global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a) {
   using SH = BucketShape<K>;
   constexpr int S = SH::S, BLOCK = kBucketBlock, Q = SH::STAGE, TILE = BLOCK * EPT;
-  __shared__ uint32_t s_off[FMAX];    // elements of a bucket, then its place in the tile
+  // by bucket, from the tile's first: elements (two 16-bit counters a word, so
+  // that the most buckets leave room for two workgroups on a CU), then the
+  // place in the tile
+  __shared__ uint32_t s_off[FMAX / 2];
   __shared__ uint32_t s_delta[FMAX];  // place in the bucket order minus place in the tile
   __shared__ alignas(16) uint32_t s_stage[Q * S];
   __shared__ uint16_t s_id[TILE];
   __shared__ uint32_t s_wave[BLOCK / kWave];
   const int tid = threadIdx.x, lane = lane_id();
-  const int64_t tile = blockIdx.x;
+  const int64_t tile = die_tile(blockIdx.x, a.tiles);
+  if (tile < 0) return;
   const int64_t i0 = tile * TILE, i1 = min(i0 + TILE, a.n);
-  for (int f = tid; f < a.buckets; f += BLOCK) s_off[f] = 0;
-  TileMesh tm{};
-  if constexpr (MESH) tm = tile_mesh(a, i0, i1);
+  const TileMesh tm = tile_mesh<MESH>(a, i0, i1);
+  for (int f = tid; f < (tm.count + 1) / 2; f += BLOCK) s_off[f] = 0;
   __syncthreads();
   uint32_t e[EPT][S];
 #pragma unroll
@@ -283,47 +320,54 @@ __global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a
     fb[i] = 0;
     pos[i] = 0xFFFFFFFFu;
     if (v < i1) {
-      fb[i] = bucket_of<K, MESH>(a, tm, v, x);
-      pos[i] = atomicAdd(&s_off[fb[i]], 1u);
+      fb[i] = bucket_of<K, MESH>(a, tm, v, x) - uint32_t(tm.first);
+      const uint32_t sh = 16 * (fb[i] & 1);
+      pos[i] = atomicAdd(&s_off[fb[i] >> 1], 1u << sh) >> sh & 0xFFFFu;
     }
   }
   __syncthreads();
   {
-    constexpr int PER = (FMAX + BLOCK - 1) / BLOCK;
-    const int per = (a.buckets + BLOCK - 1) / BLOCK;
-    uint32_t c[PER], t[PER], sum = 0, before = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int f = tid * per + j;
-      const bool in = j < per && f < a.buckets;
-      c[j] = in ? s_off[f] : 0u;
-      t[j] = in ? a.totals[f] : 0u;
-      sum += c[j];
-      before += t[j];
+    // bucket starts, for an even number of buckets per thread; also left for
+    // the grouping, by tile 0 or, in a batch, by every tile for its own
+    // buckets (several may write the same)
+    uint32_t before = 0;
+    if constexpr (MESH) before = uint32_t(a.mesh_off[tm.lo]);  // buckets are in mesh order
+    const int per = (tm.count + 2 * BLOCK - 1) / (2 * BLOCK) * 2;
+    const int f0 = tid * per, f1 = min(f0 + per, tm.count);
+    uint32_t sum = 0, own = 0;
+    for (int f = f0; f < f1; ++f) {
+      const uint32_t t = a.totals[tm.first + f];
+      s_delta[f] = t;
+      own += t;
+      sum += s_off[f >> 1] >> (16 * (f & 1)) & 0xFFFFu;
     }
     uint32_t all;
     uint32_t at = block_exclusive_scan<BLOCK>(sum, s_wave, &all);
-    uint32_t start = block_exclusive_scan<BLOCK>(before, s_wave, &all);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int f = tid * per + j;
-      if (j < per && f < a.buckets) {
-        s_off[f] = at;
-        s_delta[f] = start - at;
-        if (tile == 0) a.starts[f] = start;
+    uint32_t start = before + block_exclusive_scan<BLOCK>(own, s_wave, &all);
+    for (int f = f0; f < f1; f += 2) {
+      const uint32_t c = s_off[f >> 1], t0 = s_delta[f], t1 = f + 1 < f1 ? s_delta[f + 1] : 0u;
+      const uint32_t at1 = at + (c & 0xFFFFu), start1 = start + t0;
+      s_off[f >> 1] = at | at1 << 16;
+      s_delta[f] = start - at;
+      if (f + 1 < f1) s_delta[f + 1] = start1 - at1;
+      if (MESH || tile == 0) {
+        a.starts[tm.first + f] = start;
+        if (f + 1 < f1) a.starts[tm.first + f + 1] = start1;
       }
-      at += c[j];
-      start += t[j];
+      at = at1 + (c >> 16);
+      start = start1 + t1;
     }
-    if (tile == 0 && tid == 0) a.starts[a.buckets] = all;
+    // the end of the last bucket, and the columns of a batch that no mesh uses
+    if (tile == a.tiles - 1)
+      for (int f = tm.first + tm.count + tid; f <= a.buckets; f += BLOCK) a.starts[f] = uint32_t(a.n);
   }
   __syncthreads();
-  const uint32_t* base = a.base + tile * int64_t(a.buckets);
-  for (int f = tid; f < a.buckets; f += BLOCK) s_delta[f] += base[f];
+  const uint32_t* base = a.base + tile * int64_t(a.buckets) + tm.first;
+  for (int f = tid; f < tm.count; f += BLOCK) s_delta[f] += base[f];
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     if (pos[i] == 0xFFFFFFFFu) continue;
-    pos[i] += s_off[fb[i]];
+    pos[i] += s_off[fb[i] >> 1] >> (16 * (fb[i] & 1)) & 0xFFFFu;
     s_id[pos[i]] = uint16_t(fb[i]);
   }
   const int total = int(i1 - i0);
@@ -348,6 +392,7 @@ struct GroupBucketArgs {
   GroupArgs g;              // elems, n, pairs, rep, cmap, uelems, chunks, range_sums, ranges, mesh_*
   const uint32_t* starts;   // [buckets + 1]
   int32_t buckets;          // the grid
+  int32_t target;           // elements per bucket aimed at
 };
 
 // Groups of one bucket, whose records stream past a table in LDS. A thread
@@ -359,10 +404,11 @@ struct GroupBucketArgs {
 // is full nothing is added any more; the elements not found in the table by
 // then (all copies of a record alike) wait for the next round, and the
 // groups of such a bucket get dense names.
-template <int K, bool MESH>
-__global__ __launch_bounds__(kGroupBlock, K <= 9 ? 8 : 4) void k_group_bucket(GroupBucketArgs b) {
-  using SH = BucketShape<K>;
-  constexpr int S = SH::S, BLOCK = kGroupBlock, DCAP = SH::DCAP, TS = SH::TS, TB = SH::TB;
+template <int K, bool MESH, int BLOCK, int DCAP>
+__global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBucketArgs b) {
+  constexpr int S = K + 1;
+  constexpr int TB = DCAP > 3072 ? 13 : DCAP > 1536 ? 12 : DCAP > 768 ? 11 : 10, TS = 1 << TB;
+  static_assert(TS * 3 >= DCAP * 4, "table load");
   constexpr int PER = (DCAP + BLOCK - 1) / BLOCK;
   constexpr uint32_t kEmpty = 0xFFFFFFFFu, kUsedBit = 0x80000000u, kOpen = 0xFFFFFFFFu;
   __shared__ uint32_t s_key[K * DCAP];     // distinct records, word-major

@@ -736,15 +736,18 @@ void group_buckets(const BucketState& b, const BucketGroup& g, const MarkArgs* m
   prof_mark(mark || band ? "mark_bucket_count" : "bucket_count", s);
   g.count(b.args, mark, band, s);
   prof_mark("bucket_offsets", s);
-  hipLaunchKernelGGL(k_bucket_offsets, dim3((b.args.buckets + kOffsetCols - 1) / kOffsetCols),
-                     dim3(kOffsetCols * kOffsetRuns), 0, s, b.args);
+  const dim3 columns((b.args.buckets + kOffsetCols - 1) / kOffsetCols), block(kOffsetCols * kOffsetRuns);
+  if (b.args.nmesh > 0)
+    hipLaunchKernelGGL(k_bucket_offsets<true>, columns, block, 0, s, b.args);
+  else
+    hipLaunchKernelGGL(k_bucket_offsets<false>, columns, block, 0, s, b.args);
   prof_mark("bucket_scatter", s);
   g.scatter(b.args, s);
   ga.elems = b.args.elems;
   ga.chunks = b.chunks;
   ga.range_sums = b.range_sums;
   ga.ranges = b.ranges;
-  const GroupBucketArgs a{ga, b.args.starts, b.args.buckets};
+  const GroupBucketArgs a{ga, b.args.starts, b.args.buckets, b.plan.target};
   prof_mark("group", s);
   g.group(a, s);
 }

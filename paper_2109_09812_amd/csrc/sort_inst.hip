@@ -227,13 +227,13 @@ SplitSort make_split() {
   using SH = SplitShape<KW>;
   SplitSort p;
   p.scratch = &split_scratch<KW>;
-  p.ranked = [](int64_t n) { return split_plan<KW>(n).samples > uint32_t(SH::SCAP); };
+  p.ranked = [](int64_t n) { return split_samples_bound<KW>(n) > SH::SCAP; };
   p.sample = [](const SplitArgs& a, hipStream_t s) {
-    const int64_t blocks = (int64_t(split_plan<KW>(a.n).samples) + SH::SCAP - 1) / SH::SCAP;
+    const int64_t blocks = (split_samples_bound<KW>(a.n) + SH::SCAP - 1) / SH::SCAP;
     hipLaunchKernelGGL((k_split_sample<K, MESH>), dim3(std::max<int64_t>(1, blocks)), dim3(SH::BLOCK), 0, s, a);
   };
   p.rank = [](const SplitArgs& a, hipStream_t s) {
-    const int64_t grid = (int64_t(split_plan<KW>(a.n).samples) + 7) / 8;
+    const int64_t grid = (split_samples_bound<KW>(a.n) + 7) / 8;
     if (grid > 0) hipLaunchKernelGGL((k_split_rank<K, MESH>), dim3(grid), dim3(256), 0, s, a);
   };
   p.count = [](const SplitArgs& a, hipStream_t s) {
@@ -243,7 +243,7 @@ SplitSort make_split() {
     hipLaunchKernelGGL((k_split_scatter<K, MESH>), dim3(a.runs), dim3(kSplitRunBlock), 0, s, a);
   };
   p.sort = [](const SplitArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_split_sort<K, MESH>), dim3(split_plan<KW>(a.n).buckets), dim3(SH::BLOCK), 0, s, a);
+    hipLaunchKernelGGL((k_split_sort<K, MESH>), dim3(split_buckets<KW>(a.n)), dim3(SH::BLOCK), 0, s, a);
   };
   return p;
 }
@@ -329,9 +329,9 @@ void launch_bucket_scatter(const BucketArgs& a, hipStream_t s) {
   using SH = BucketShape<K>;
   constexpr int FMAX = MESH ? kBucketMaxMesh : kBucketMax;
   if (a.tile == kBucketBlock * SH::EPT)
-    hipLaunchKernelGGL((k_bucket_scatter<K, SH::EPT, FMAX, MESH>), dim3(a.tiles), dim3(kBucketBlock), 0, s, a);
+    hipLaunchKernelGGL((k_bucket_scatter<K, SH::EPT, FMAX, MESH>), dim3(die_grid(a.tiles)), dim3(kBucketBlock), 0, s, a);
   else
-    hipLaunchKernelGGL((k_bucket_scatter<K, SH::EPT_SMALL, FMAX, MESH>), dim3(a.tiles), dim3(kBucketBlock), 0, s, a);
+    hipLaunchKernelGGL((k_bucket_scatter<K, SH::EPT_SMALL, FMAX, MESH>), dim3(die_grid(a.tiles)), dim3(kBucketBlock), 0, s, a);
 }
 
 template <bool MESH>
@@ -341,7 +341,13 @@ BucketGroup make_bucket() {
   g.count = &launch_bucket_count<MESH>;
   g.scatter = &launch_bucket_scatter<MESH>;
   g.group = [](const GroupBucketArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_group_bucket<K, MESH>), dim3(a.buckets), dim3(kGroupBlock), 0, s, a);
+    using SH = BucketShape<K>;
+    if (a.target <= SH::DCAP_SMALL * 4 / 5)
+      hipLaunchKernelGGL((k_group_bucket<K, MESH, kGroupBlockSmall, SH::DCAP_SMALL>), dim3(a.buckets),
+                         dim3(kGroupBlockSmall), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_group_bucket<K, MESH, kGroupBlock, SH::DCAP>), dim3(a.buckets), dim3(kGroupBlock), 0, s,
+                         a);
   };
   return g;
 }

@@ -31,6 +31,8 @@
 // its name, and becomes the first of KW = K + 1 key words.
 #pragma once
 
+#include <algorithm>
+
 #include "device_common.hpp"
 #include "group_kernels.hpp"
 
@@ -64,26 +66,47 @@ constexpr int kSplitParts = 64;        // parts an oversized bucket is cut into 
 struct SplitPlan {
   uint32_t buckets, os, samples;
 };
+
+// Buckets of about 256 elements up to 512 of them (a short sort on every CU
+// rather than a long one on some), then larger ones up to TARGET, then more.
+// Never fewer for more elements.
+template <int KW>
+__host__ __device__ inline uint32_t split_buckets(int64_t u) {
+  if (u <= 512) return 1u;
+  if (u <= 512 * 256) return uint32_t((u + 255) / 256);
+  const int64_t f = (u + SplitShape<KW>::TARGET - 1) / SplitShape<KW>::TARGET;
+  return uint32_t(f < 512 ? 512 : f < kMaxBuckets ? f : kMaxBuckets);
+}
+
 template <int KW>
 __host__ __device__ inline SplitPlan split_plan(int64_t u) {
   using SH = SplitShape<KW>;
-  SplitPlan p{1u, 0u, 0u};
-  if (u <= SH::CAP) return p;
-  const int64_t f = (u + SH::TARGET - 1) / SH::TARGET;
-  p.buckets = uint32_t(f < kMaxBuckets ? f : kMaxBuckets);
+  SplitPlan p{split_buckets<KW>(u), 0u, 0u};
+  if (p.buckets == 1) return p;
+  // small buckets may vary more in size
+  const int64_t t = u / p.buckets;
+  const uint32_t os = t * 8 <= SH::CAP ? kOversample / 4 : t * 4 <= SH::CAP ? kOversample / 2 : kOversample;
   const uint32_t most = uint32_t(kMaxSampleBlocks * SH::SCAP) / p.buckets;
-  p.os = most < uint32_t(kOversample) ? most : uint32_t(kOversample);
+  p.os = most < os ? most : os;
   p.samples = p.buckets * p.os;
   return p;
 }
 
-// Scratch words of the whole sort for n vertices and `runs` runs of chunks.
+// The most samples of any u <= n (not those of n: where the limit on samples
+// cuts os, fewer buckets may have more of them in all).
+template <int KW>
+inline int64_t split_samples_bound(int64_t n) {
+  const int64_t f = split_buckets<KW>(n);
+  return f == 1 ? 0 : std::min<int64_t>(f * kOversample, int64_t(kMaxSampleBlocks) * SplitShape<KW>::SCAP);
+}
+
+// Scratch words of the whole sort of up to n elements in `runs` runs of chunks.
 struct SplitScratch {
   int64_t samples, splitters, counts, starts, run_base, digits, words;
 };
 template <int KW>
 inline SplitScratch split_scratch(int64_t n, int64_t runs) {
-  const SplitPlan p = split_plan<KW>(n);
+  const int64_t buckets = split_buckets<KW>(n);
   SplitScratch s{};
   int64_t at = 0;
   auto take = [&](int64_t words) {
@@ -91,11 +114,11 @@ inline SplitScratch split_scratch(int64_t n, int64_t runs) {
     at += (words + 3) & ~int64_t(3);
     return r;
   };
-  s.samples = take(int64_t(p.samples) * KW);
-  s.splitters = take(int64_t(p.buckets) * KW);
-  s.counts = take(p.buckets);
-  s.starts = take(int64_t(p.buckets) + 1);
-  s.run_base = take(runs * int64_t(p.buckets));
+  s.samples = take(split_samples_bound<KW>(n) * KW);
+  s.splitters = take(buckets * KW);
+  s.counts = take(buckets);
+  s.starts = take(buckets + 1);
+  s.run_base = take(runs * buckets);
   s.digits = take((n + 1) / 2);
   s.words = at;
   return s;
@@ -700,7 +723,7 @@ __global__ __launch_bounds__(kSplitRunBlock) void k_split_scatter(SplitArgs a) {
     for (int r = 0; r < U; ++r) {
       const uint32_t j = min(j0 + uint32_t(r * BLOCK + tid), total - 1);
       load_words<S>(a.sparse + run_slot(s_base, s_span, nc, j) * S, e[r]);
-      f[r] = F > 1 ? a.digits[first + j] : 0u;
+      f[r] = F > 1 ? min(uint32_t(a.digits[first + j]), uint32_t(F - 1)) : 0u;
     }
 #pragma unroll
     for (int r = 0; r < U; ++r) {
@@ -725,7 +748,7 @@ __device__ __forceinline__ void split_output(const SplitArgs& a, const SortLds<K
   }
   for (int q = tid; q < n; q += BLOCK) {
     const uint32_t g = lds.x[KW * CAP + q];
-    a.cmap[g] = int32_t(c0 + q);
+    if (int64_t(g) < a.n) a.cmap[g] = int32_t(c0 + q);
     if constexpr (MESH) a.order[c0 + q] = g;
   }
 }
