@@ -424,6 +424,7 @@ struct BandMapArgs {
   int64_t itiles;
   int64_t n;
   int32_t shift;               // <= kMaxMapShift
+  int32_t nb;
   int32_t* old2new;            // [n]
   int32_t* values;             // [m]: new id of the entry at the same place in ipart
   SortBuffers sort;            // with from_sort: ppart = sort.sorted(), values = sort.spare()
@@ -435,7 +436,10 @@ __global__ __launch_bounds__(kBandBlock) void k_band_map(BandMapArgs a) {
   __shared__ alignas(16) int32_t s_map[1 << SHIFT];  // a.shift <= SHIFT
   __shared__ BandWalk<kBandBlock> s_walk;
   const int tid = threadIdx.x;
-  const int64_t band = blockIdx.x;
+  // the slices of neighbouring bands are neighbours in every tile's slot and
+  // share its cache lines
+  const int64_t band = die_tile(blockIdx.x, a.nb);
+  if (band < 0) return;
   const int64_t lo = band << a.shift;
   const int64_t hi = min(a.n, lo + (int64_t(1) << a.shift));
   const int len = int(hi - lo);
@@ -546,15 +550,16 @@ static inline void launch_pair_partition(const PairPartArgs& a, bool fine, hipSt
 // Fine bands hold at most 2^14 vertices, in 32 or 64 KB of LDS, so that
 // several of their workgroups share a CU.
 constexpr int kMaxFineShift = 14;
-static inline void launch_band_map(const BandMapArgs& a, int32_t nb, bool fine, hipStream_t s) {
+static inline void launch_band_map(const BandMapArgs& a, bool fine, hipStream_t s) {
+  const dim3 nb(die_grid(a.nb));
   if (fine && a.shift <= 13)
-    hipLaunchKernelGGL((k_band_map<512, 13, true>), dim3(nb), dim3(512), 0, s, a);
+    hipLaunchKernelGGL((k_band_map<512, 13, true>), nb, dim3(512), 0, s, a);
   else if (fine && a.shift <= kMaxFineShift)
-    hipLaunchKernelGGL((k_band_map<512, kMaxFineShift, true>), dim3(nb), dim3(512), 0, s, a);
+    hipLaunchKernelGGL((k_band_map<512, kMaxFineShift, true>), nb, dim3(512), 0, s, a);
   else if (fine)
-    hipLaunchKernelGGL((k_band_map<kBandBlock, kMaxMapShift, true>), dim3(nb), dim3(kBandBlock), 0, s, a);
+    hipLaunchKernelGGL((k_band_map<kBandBlock, kMaxMapShift, true>), nb, dim3(kBandBlock), 0, s, a);
   else
-    hipLaunchKernelGGL((k_band_map<kBandBlock, kMaxMapShift, false>), dim3(nb), dim3(kBandBlock), 0, s, a);
+    hipLaunchKernelGGL((k_band_map<kBandBlock, kMaxMapShift, false>), nb, dim3(kBandBlock), 0, s, a);
 }
 
 static inline void launch_band_remap(const BandRemapArgs& a, int64_t tiles, bool fine, hipStream_t s) {

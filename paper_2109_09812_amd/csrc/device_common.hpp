@@ -121,6 +121,20 @@ struct Control {
   int64_t pad2[2];
 };
 
+// ---------------------------------------------------------------- dies
+//
+// Workgroups go to the dies (each with its own L2) in turn. die_tile gives
+// every die a contiguous range of tiles instead (-1: none left), for kernels
+// whose neighbouring tiles read or write parts of the same cache lines; the
+// grid is die_grid(tiles).
+constexpr int kDies = 8;
+__host__ __device__ inline int64_t die_grid(int64_t tiles) { return (tiles + kDies - 1) / kDies * kDies; }
+__device__ __forceinline__ int64_t die_tile(int64_t block, int64_t tiles) {
+  const int64_t per = (tiles + kDies - 1) / kDies;
+  const int64_t t = block % kDies * per + block / kDies;
+  return block / kDies < per && t < tiles ? t : -1;
+}
+
 // ---------------------------------------------------------------- record hash
 //
 // 32-bit hash of a record's K words: the block and finalisation steps of

@@ -937,9 +937,9 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
       prof_mark("pair_partition", s);
       launch_pair_partition(pa, bp.fine, s);
       const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
-                           bp.shift, old2new, reinterpret_cast<int32_t*>(buf[2])};
+                           bp.shift, bp.nb, old2new, reinterpret_cast<int32_t*>(buf[2])};
       prof_mark("band_map", s);
-      launch_band_map(ma, bp.nb, bp.fine, s);
+      launch_band_map(ma, bp.fine, s);
       const BandRemapArgs ra{ipart, reinterpret_cast<const int32_t*>(buf[2]), itile_valid, m, arity, live_elems,
                              out_idx};
       prof_mark("band_remap", s);
@@ -1124,11 +1124,12 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
       ma.itiles = bp.itiles;
       ma.n = n;
       ma.shift = bp.shift;
+      ma.nb = bp.nb;
       ma.old2new = old2new;
       ma.sort = sb;
       ma.from_sort = 1;
       prof_mark("band_map", s);
-      launch_band_map(ma, bp.nb, false, s);
+      launch_band_map(ma, false, s);
       BandRemapArgs ra{};
       ra.ipart = ipart;
       ra.tile_valid = itile_valid;
@@ -1361,9 +1362,9 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
     prof_mark("pair_partition", s);
     launch_pair_partition(pa, true, s);
     const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
-                         bp.shift, old2new, reinterpret_cast<int32_t*>(buf[2]), SortBuffers{}, 0};
+                         bp.shift, bp.nb, old2new, reinterpret_cast<int32_t*>(buf[2]), SortBuffers{}, 0};
     prof_mark("band_map", s);
-    launch_band_map(ma, bp.nb, true, s);
+    launch_band_map(ma, true, s);
     const BandRemapArgs ra{ipart, reinterpret_cast<const int32_t*>(buf[2]), itile_valid, m, arity, nullptr, out_idx,
                            SortBuffers{}, 0};
     prof_mark("band_remap", s);

@@ -312,14 +312,14 @@ template <bool MESH>
 void launch_bucket_count(const BucketArgs& a, const MarkArgs* ma, const BandArgs* ba, hipStream_t s) {
   if (ba) {
     const size_t bits_lds = (size_t(1) << ba->shift) / 8;
-    hipLaunchKernelGGL((k_bucket_count<K, MESH, 2>), dim3(a.tiles + ba->nb), dim3(kRandBlock), bits_lds, s, a,
+    hipLaunchKernelGGL((k_bucket_count<K, MESH, 2>), dim3(die_grid(a.tiles + ba->nb)), dim3(kRandBlock), bits_lds, s, a,
                        MarkArgs{}, *ba, int64_t(ba->nb));
   } else if (ma) {
     const int64_t mt = (ma->m + kRandBlock * kRandItems - 1) / (kRandBlock * kRandItems);
-    hipLaunchKernelGGL((k_bucket_count<K, MESH, 1>), dim3(a.tiles + mt), dim3(kRandBlock), 0, s, a, *ma, BandArgs{},
+    hipLaunchKernelGGL((k_bucket_count<K, MESH, 1>), dim3(die_grid(a.tiles + mt)), dim3(kRandBlock), 0, s, a, *ma, BandArgs{},
                        mt);
   } else {
-    hipLaunchKernelGGL((k_bucket_count<K, MESH, 0>), dim3(a.tiles), dim3(kRandBlock), 0, s, a, MarkArgs{}, BandArgs{},
+    hipLaunchKernelGGL((k_bucket_count<K, MESH, 0>), dim3(die_grid(a.tiles)), dim3(kRandBlock), 0, s, a, MarkArgs{}, BandArgs{},
                        int64_t(0));
   }
 }
