@@ -79,29 +79,51 @@ __global__ __launch_bounds__(BLOCK) void k_select_elements(SelectArgs a) {
     if (w < wave) wave_excl += t;
     tile_total += t;
   }
-  if (tid == 0) {
+  if (wave == 0) {
     uint64_t* lb = a.lookback + tile;
-    uint32_t prev = 0;
-    if (tile == 0) {
-      lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, tile_total));
-    } else {
-      lb_store(lb, LbTagged::pack(kLbAggregate, a.tag, tile_total));
-      prev = lookback_exclusive(a.lookback, tile, 1, a.tag, a.ctl, a.status);
-      lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, prev + tile_total));
+    if (lane == 0) lb_store(lb, LbTagged::pack(tile == 0 ? kLbInclusive : kLbAggregate, a.tag, tile_total));
+    const uint32_t prev = lookback_exclusive(a.lookback, tile, a.tag, a.ctl, a.status);  // 0 for tile 0
+    if (lane == 0) {
+      if (tile > 0) lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, prev + tile_total));
+      s_prefix = prev;
+      if (int64_t(tile) == ntiles - 1) *a.out_count = int64_t(prev) + tile_total;
     }
-    s_prefix = prev;
-    if (int64_t(tile) == ntiles - 1) *a.out_count = int64_t(prev) + tile_total;
   }
   __syncthreads();
   const int64_t base = int64_t(s_prefix) + wave_excl;
   const int32_t A = a.arity;
+  if (A > 4) {
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    if (!kept[j]) continue;
-    const int64_t e = wave_base + j * kWave;
-    const int64_t o = base + excl[j];
-    if (o >= a.num_elems) continue;  // only after a failed look-back wait
-    for (int c = 0; c < A; ++c) a.out[o * A + c] = a.idx[e * A + c];
+    for (int j = 0; j < IPT; ++j) {
+      if (!kept[j]) continue;
+      const int64_t e = wave_base + j * kWave;
+      const int64_t o = base + excl[j];
+      if (o >= a.num_elems) continue;  // only after a failed look-back wait
+      for (int c = 0; c < A; ++c) a.out[o * A + c] = a.idx[e * A + c];
+    }
+    return;
+  }
+  // Up to 4 entries: all of four elements' loads are in flight before the
+  // first store (a loop that loads and stores entry by entry waits for each).
+  static_assert(IPT % 4 == 0, "");
+#pragma unroll
+  for (int j0 = 0; j0 < IPT; j0 += 4) {
+    int32_t x[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t e = wave_base + (j0 + j) * kWave;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (kept[j0 + j] && c < A) x[j][c] = a.idx[e * A + c];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t o = base + excl[j0 + j];
+      if (!kept[j0 + j] || o >= a.num_elems) continue;  // the latter only after a failed look-back wait
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (c < A) a.out[o * A + c] = x[j][c];
+    }
   }
 }
 

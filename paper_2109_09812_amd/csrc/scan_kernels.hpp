@@ -168,16 +168,17 @@ __global__ __launch_bounds__(BLOCK) void k_flag_scan(FlagScanArgs a) {
     if (w < wave) wave_excl += t;
     tile_total += t;
   }
-  if (tid == 0) {
+  if (wave == 0) {
     uint64_t* lb = a.lookback + tile;
-    if (tile == 0) {
-      lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, tile_total));
+    if (lane == 0) lb_store(lb, LbTagged::pack(tile == 0 ? kLbInclusive : kLbAggregate, a.tag, tile_total));
+    if (tile > 0) {
+      const uint32_t prev = lookback_exclusive(a.lookback, tile, a.tag, a.ctl, a.status);
+      if (lane == 0) {
+        lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, prev + tile_total));
+        s_prefix = prev;
+      }
+    } else if (lane == 0) {
       s_prefix = 0;
-    } else {
-      lb_store(lb, LbTagged::pack(kLbAggregate, a.tag, tile_total));
-      const uint32_t prev = lookback_exclusive(a.lookback, tile, 1, a.tag, a.ctl, a.status);
-      lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, prev + tile_total));
-      s_prefix = prev;
     }
   }
   __syncthreads();
@@ -262,16 +263,17 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
     if (w < wave) wave_excl += t;
     tile_total += t;
   }
-  if (tid == 0) {
+  if (wave == 0) {
     uint64_t* lb = a.lookback + tile;
-    if (tile == 0) {
-      lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, tile_total));
+    if (lane == 0) lb_store(lb, LbTagged::pack(tile == 0 ? kLbInclusive : kLbAggregate, a.tag, tile_total));
+    if (tile > 0) {
+      const uint32_t prev = lookback_exclusive(a.lookback, tile, a.tag, a.ctl, a.status);
+      if (lane == 0) {
+        lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, prev + tile_total));
+        s_prefix = prev;
+      }
+    } else if (lane == 0) {
       s_prefix = 0;
-    } else {
-      lb_store(lb, LbTagged::pack(kLbAggregate, a.tag, tile_total));
-      const uint32_t prev = lookback_exclusive(a.lookback, tile, 1, a.tag, a.ctl, a.status);
-      lb_store(lb, LbTagged::pack(kLbInclusive, a.tag, prev + tile_total));
-      s_prefix = prev;
     }
   }
   __syncthreads();
