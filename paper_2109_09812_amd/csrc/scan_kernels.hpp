@@ -17,6 +17,7 @@ constexpr int32_t kErrInternal = 7;  // MRX_ERR_INTERNAL
 constexpr int kRandBlock = 256;
 constexpr int kRandItems = 2;        // k_mark_used, k_remap
 constexpr int kScatterItems = 16;    // k_scatter_old2new
+constexpr int kScatterFew = 4;       // the same, where 16 would leave fewer than four workgroups per CU
 
 // Step 1: used[v] = 1 for every referenced vertex v. Batched meshes carry
 // mesh-local indices; the element's mesh supplies the vertex offset.
@@ -307,7 +308,7 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
 // position: one lookup for a tile inside one mesh. `new2old` (nullable, after
 // hash grouping) receives the representatives `rep`, given by group name, at
 // their groups' new ids: the pair that holds one is found by comparison.
-template <bool BATCHED>
+template <bool BATCHED, int kItems>
 __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs, const uint2* pairs_in,
                                                                 const int32_t* __restrict__ cmap, int64_t n,
                                                                 const int64_t* __restrict__ vtx_off,
@@ -316,7 +317,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
                                                                 int32_t* __restrict__ old2new,
                                                                 const uint32_t* __restrict__ rep,
                                                                 int32_t* __restrict__ new2old) {
-  constexpr int TILE = kRandBlock * kScatterItems;
+  constexpr int TILE = kRandBlock * kItems;
   const uint2* __restrict__ pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
   __shared__ int32_t s_cmap[TILE];
   __shared__ uint32_t s_g[2];
@@ -335,10 +336,10 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
       s_mesh[1] = mesh_of(vtx_off, nmesh, t1, vtx_tab);
     }
   }
-  uint2 p[kScatterItems];
-  int32_t c[kScatterItems];
+  uint2 p[kItems];
+  int32_t c[kItems];
 #pragma unroll
-  for (int it = 0; it < kScatterItems; ++it) {
+  for (int it = 0; it < kItems; ++it) {
     const int64_t i = base + it * kRandBlock;
     if (i < n) {
       p[it] = pairs[i];  // one 8-byte load
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
     s_cmap[i] = (int64_t(g0) + i < n) ? cmap[int64_t(g0) + i] : -1;
   __syncthreads();
 #pragma unroll
-  for (int it = 0; it < kScatterItems; ++it) {
+  for (int it = 0; it < kItems; ++it) {
     const int64_t off = int64_t(p[it].x) - int64_t(g0);
     if (int64_t(p[it].x) >= n) c[it] = -1;
     else c[it] = (off >= 0 && off < span) ? s_cmap[off] : cmap[p[it].x];  // outside: only after a failed wait
@@ -367,7 +368,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
     }
   }
 #pragma unroll
-  for (int it = 0; it < kScatterItems; ++it) {
+  for (int it = 0; it < kItems; ++it) {
     if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) continue;  // past the end (or a failed wait)
     int32_t cc = c[it] < 0 ? -1 : c[it];
     const bool is_rep = new2old && cc >= 0 && cc < n && rep[p[it].x] == p[it].y;

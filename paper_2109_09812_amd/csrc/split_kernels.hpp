@@ -68,7 +68,10 @@ struct SplitPlan {
 };
 
 // Buckets of about 256 elements up to 512 of them (a short sort on every CU
-// rather than a long one on some), then larger ones up to TARGET, then more.
+// rather than a long one on some), then larger ones up to TARGET, then more
+// (rounding their number up to whole rounds of the 512 workgroups that the
+// chip holds at once gained nothing: 48 and 46 us for a million elements, and
+// as much lost to the ranks of more samples).
 // Never fewer for more elements.
 template <int KW>
 __host__ __device__ inline uint32_t split_buckets(int64_t u) {
@@ -391,22 +394,6 @@ __device__ void block_sort(const uint32_t (&e)[E][NW], int n, SortLds<NW, CAP>& 
   __syncthreads();
 }
 
-// Total of the runs' used groups and those of the runs before `run`.
-template <int BLOCK>
-__device__ __forceinline__ uint32_t run_total(const uint32_t* sums, int64_t runs, int64_t run, uint32_t* s_wave,
-                                              uint32_t* before) {
-  uint32_t all = 0, pre = 0;
-  for (int64_t r = threadIdx.x; r < runs; r += BLOCK) {
-    const uint32_t x = sums[r];
-    all += x;
-    pre += r < run ? x : 0u;
-  }
-  uint32_t total;
-  (void)block_exclusive_scan<BLOCK>(pre, s_wave, before);
-  (void)block_exclusive_scan<BLOCK>(all, s_wave, &total);
-  return total;
-}
-
 // Slot of the element at place j, among nc chunks with places s_base (not
 // decreasing) and first slots s_span.
 __device__ __forceinline__ int64_t run_slot(const uint32_t* s_base, const uint32_t* s_span, int nc, uint32_t j) {
@@ -476,25 +463,25 @@ __global__ __launch_bounds__(SplitShape<K + (MESH ? 1 : 0)>::BLOCK) void k_split
   const int64_t tc = group_range_start(rz + 1, a.tiles, a.runs) - ta;
   const bool in_lds = tc <= kChunks;
   if (in_lds) {
-    const int per = int((tc + BLOCK - 1) / BLOCK);
+    constexpr int CPER = kChunks / BLOCK;
+    const int per = int((tc + BLOCK - 1) / BLOCK);  // <= CPER
+    uint2 c[CPER];
     uint32_t sum_c = 0;
-    for (int i = 0; i < per; ++i) {
+#pragma unroll
+    for (int i = 0; i < CPER; ++i) {
       const int t = tid * per + i;
-      if (t < tc) {
-        const uint2 c = a.chunks[ta + t];
-        s_span[t] = c.x;
-        s_base[t] = c.y;
-        sum_c += c.y;
-      }
+      c[i] = (i < per && t < tc) ? a.chunks[ta + t] : make_uint2(0, 0);
+      sum_c += c[i].y;
     }
     uint32_t all;
     uint32_t at = s_run[ra] + block_exclusive_scan<BLOCK>(sum_c, s_wave, &all);
-    for (int i = 0; i < per; ++i) {
+#pragma unroll
+    for (int i = 0; i < CPER; ++i) {
       const int t = tid * per + i;
-      if (t < tc) {
-        const uint32_t c = s_base[t];
+      if (i < per && t < tc) {
+        s_span[t] = c[i].x;
         s_base[t] = at;
-        at += c;
+        at += c[i].y;
       }
     }
     __syncthreads();
@@ -581,23 +568,41 @@ __global__ __launch_bounds__(256) void k_split_rank(SplitArgs a) {
   }
 }
 
-// The elements of run `run` of chunks: first is the run's place in chunk
-// order, s_base/s_span its chunks' places and slots. Returns the count.
+// The elements of run `run` of chunks: *first is the run's place in chunk
+// order, s_base/s_span its chunks' places and slots, *chunks their number.
+// Returns the run's elements. The loads of the chunks and of the other runs'
+// counts are in flight together and share one exchange: these kernels' chains
+// of dependent loads and barriers are what a small order costs.
 template <int BLOCK>
 __device__ __forceinline__ uint32_t open_run(const SplitArgs& a, int64_t run, uint32_t* s_base, uint32_t* s_span,
-                                             uint32_t* s_wave, int* chunks) {
+                                             uint2* s_wave, uint32_t* first, int* chunks) {
   static_assert(BLOCK >= kSplitMaxChunks, "one chunk per thread");
-  const int tid = threadIdx.x;
+  constexpr int WAVES = BLOCK / kWave;
+  const int tid = threadIdx.x, wave = tid / kWave;
   const int64_t t0 = group_range_start(run, a.tiles, a.runs);
   const int nc = int(group_range_start(run + 1, a.tiles, a.runs) - t0);
   uint2 c = make_uint2(0, 0);
   if (tid < nc) c = a.chunks[t0 + tid];
-  uint32_t total;
-  const uint32_t ex = block_exclusive_scan<BLOCK>(c.y, s_wave, &total);
+  uint32_t pre = 0;
+  for (int64_t r = tid; r < run; r += BLOCK) pre += a.range_sums[r];
+  const uint32_t inc = wave_inclusive_scan(c.y);
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) pre += __shfl_xor(pre, o);
+  if (lane_id() == kWave - 1) s_wave[wave] = make_uint2(inc, pre);
+  __syncthreads();
+  uint32_t at = inc - c.y, total = 0, f = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    const uint2 x = s_wave[w];
+    if (w < wave) at += x.x;
+    total += x.x;
+    f += x.y;
+  }
   if (tid < nc) {
-    s_base[tid] = ex;
+    s_base[tid] = at;
     s_span[tid] = c.x;
   }
+  *first = f;
   *chunks = nc;
   __syncthreads();
   return total;
@@ -613,7 +618,7 @@ __global__ __launch_bounds__(kSplitRunBlock) void k_split_count(SplitArgs a) {
   __shared__ uint32_t s_spl[kSplitLdsWords];
   __shared__ uint32_t s_cnt[kMaxBuckets];
   __shared__ uint32_t s_base[kSplitMaxChunks], s_span[kSplitMaxChunks];
-  __shared__ uint32_t s_wave[BLOCK / kWave];
+  __shared__ uint2 s_wave[BLOCK / kWave];
   const int tid = threadIdx.x;
   const int64_t run = blockIdx.x;
   const SplitPlan plan = split_plan<KW>(a.ctl->num_used);
@@ -622,19 +627,25 @@ __global__ __launch_bounds__(kSplitRunBlock) void k_split_count(SplitArgs a) {
     if (tid == 0) a.run_base[run] = atomicAdd(&a.counts[0], a.range_sums[run]);
     return;
   }
-  uint32_t first;
-  (void)run_total<BLOCK>(a.range_sums, a.runs, run, s_wave, &first);
-  int nc;
-  const uint32_t total = open_run<BLOCK>(a, run, s_base, s_span, s_wave, &nc);
   int sh = 0;
   while (((F - 1) >> sh) * KW > kSplitLdsWords) ++sh;
   const int m = (F - 1) >> sh;  // LDS entry i is splitter (i + 1) << sh
-  for (int t = tid; t < m * KW; t += BLOCK) {
-    const int i = t / KW, w = t - i * KW;
-    s_spl[w * m + i] = a.splitters[(int64_t(i + 1) << sh) * KW + w];
+  constexpr int PER = kSplitLdsWords / BLOCK;
+  uint32_t spl[PER];  // all in flight at once
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int t = i * BLOCK + tid, j = t / KW, w = t - j * KW;
+    spl[i] = t < m * KW ? a.splitters[(int64_t(j + 1) << sh) * KW + w] : 0u;
   }
   for (int f = tid; f < F; f += BLOCK) s_cnt[f] = 0;
-  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int t = i * BLOCK + tid, j = t / KW, w = t - j * KW;
+    if (t < m * KW) s_spl[w * m + j] = spl[i];
+  }
+  uint32_t first;
+  int nc;
+  const uint32_t total = open_run<BLOCK>(a, run, s_base, s_span, s_wave, &first, &nc);
   constexpr int U = S <= 5 ? 4 : 2;
   for (uint32_t j0 = 0; j0 < total; j0 += BLOCK * U) {
     uint32_t e[U][S];
@@ -682,35 +693,36 @@ __global__ __launch_bounds__(kSplitRunBlock) void k_split_scatter(SplitArgs a) {
   constexpr int KW = K + (MESH ? 1 : 0), S = K + 1, BLOCK = kSplitRunBlock;
   __shared__ uint32_t s_at[kMaxBuckets];
   __shared__ uint32_t s_base[kSplitMaxChunks], s_span[kSplitMaxChunks];
+  __shared__ uint2 s_wave2[BLOCK / kWave];
   __shared__ uint32_t s_wave[BLOCK / kWave];
   const int tid = threadIdx.x;
   const int64_t run = blockIdx.x;
   const int64_t u = a.ctl->num_used;
   const SplitPlan plan = split_plan<KW>(u);
   const int F = int(plan.buckets);
-  uint32_t first;
-  (void)run_total<BLOCK>(a.range_sums, a.runs, run, s_wave, &first);
-  int nc;
-  const uint32_t total = open_run<BLOCK>(a, run, s_base, s_span, s_wave, &nc);
   // bucket starts: PER consecutive counts per thread
   constexpr int PER = kMaxBuckets / BLOCK;
   const int per = (F + BLOCK - 1) / BLOCK;  // <= PER
-  uint32_t c[PER], sum = 0;
+  const uint32_t* base = a.run_base + run * int64_t(F);
+  uint32_t c[PER], at[PER], sum = 0;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int f = tid * per + i;
     c[i] = (i < per && f < F) ? a.counts[f] : 0u;
+    at[i] = (i < per && f < F) ? base[f] : 0u;
     sum += c[i];
   }
+  uint32_t first;
+  int nc;
+  const uint32_t total = open_run<BLOCK>(a, run, s_base, s_span, s_wave2, &first, &nc);
   uint32_t all;
   uint32_t acc = block_exclusive_scan<BLOCK>(sum, s_wave, &all);
-  const uint32_t* base = a.run_base + run * int64_t(F);
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int f = tid * per + i;
     if (i < per && f < F) {
       if (run == 0) a.starts[f] = acc;
-      s_at[f] = acc + base[f];
+      s_at[f] = acc + at[i];
       acc += c[i];
     }
   }

@@ -98,3 +98,23 @@ def test_batches_around_the_bucket_limit(meshes):
     assert np.array_equal(r.out_idx.cpu().numpy(), oi)
     assert np.array_equal(r.old2new.cpu().numpy(), o2n)
     assert np.array_equal(r.new2old.cpu().numpy(), n2o)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 4097, 4096 * 1023, 4096 * 1023 + 1])
+def test_map_scatter_tiles(n):
+    """Tiles of the map's scatter, of 4 and of 16 vertices per thread (from
+    1,024 workgroups of the latter), for meshes of few index entries."""
+    rng = np.random.default_rng(n)
+    vtx, idx = mesh(rng, n, 2, max(1, n // 5), n // 8 + 1)
+    out_vtx, out_idx, old2new, new2old = run(vtx, idx)
+    order = np.lexsort((np.arange(n), vtx[:, 1], vtx[:, 0]))  # groups in record order, members by old id
+    head = np.concatenate([[True], np.any(vtx[order][1:] != vtx[order][:-1], axis=1)])
+    group = np.empty(n, np.int64)
+    group[order] = np.cumsum(head) - 1
+    used = np.zeros(int(head.sum()), bool)
+    used[group[idx[:, 0]]] = True
+    new = np.where(used, np.cumsum(used) - 1, -1)[group]
+    assert np.array_equal(old2new, new)
+    assert np.array_equal(new2old, order[head][used])
+    assert np.array_equal(out_vtx, vtx[order[head][used]])
+    assert np.array_equal(out_idx[:, 0], new[idx[:, 0]])
