@@ -16,7 +16,8 @@ def _stream_handle(device) -> int:
 
 
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # a plain int: the declared argument types make the pointer of it
+    return None if t is None else t.data_ptr()
 
 
 def workspace_size(num_vtx: int, vtx_bytes: int, num_idx: int, num_meshes: int = 1,
@@ -53,7 +54,7 @@ class Reindexed:
 
     def trim(self) -> "Reindexed":
         """One device->host read of U and the status; raises on a data error."""
-        u, status = (int(x) for x in self.meta[:2].cpu())
+        u, status = self.meta[:2].tolist()
         status &= 0xFFFFFFFF
         if status == MRX_ERR_INDEX_OUT_OF_RANGE:
             raise IndexError("an index entry is out of range")
@@ -87,8 +88,8 @@ def reindex_mesh(vtx: torch.Tensor, idx: torch.Tensor, *, tuning=None, workspace
         workspace = torch.empty(max(wsb, 1), dtype=torch.uint8, device=dev)
     st = load().mrx_reindex_mesh(
         _ptr(vtx), n, 4 * k, _ptr(idx), idx.shape[0], idx.shape[1], _ptr(out_vtx), _ptr(out_idx),
-        _ptr(old2new), _ptr(new2old), _ptr(meta), ctypes.c_void_p(meta.data_ptr() + 8),
-        _ptr(workspace), workspace.numel(), make_tuning(tuning), ctypes.c_void_p(_stream_handle(dev)))
+        _ptr(old2new), _ptr(new2old), _ptr(meta), meta.data_ptr() + 8,
+        _ptr(workspace), workspace.numel(), make_tuning(tuning), _stream_handle(dev))
     check(st, "mrx_reindex_mesh")
     r = Reindexed(out_vtx, out_idx, old2new, new2old, meta)
     return r.trim() if sync else r
@@ -109,8 +110,8 @@ def reindex_mesh_noalloc(vtx: torch.Tensor, idx: torch.Tensor, out=None, *, tuni
                         torch.empty(n, dtype=torch.int32, device=dev), torch.zeros(2, dtype=torch.int64, device=dev))
     st = load().mrx_reindex_mesh_noalloc(
         _ptr(vtx), n, 4 * k, _ptr(idx), idx.shape[0], idx.shape[1], _ptr(out.out_vtx), _ptr(out.out_idx),
-        _ptr(out.old2new), _ptr(out.new2old), _ptr(out.meta), ctypes.c_void_p(out.meta.data_ptr() + 8),
-        make_tuning(tuning), ctypes.c_void_p(_stream_handle(dev)))
+        _ptr(out.old2new), _ptr(out.new2old), _ptr(out.meta), out.meta.data_ptr() + 8,
+        make_tuning(tuning), _stream_handle(dev))
     check(st, "mrx_reindex_mesh_noalloc")
     return out.trim() if sync else out
 
@@ -146,8 +147,8 @@ def merge_meshes(vtx: torch.Tensor, vtx_offsets: torch.Tensor, idx: torch.Tensor
     st = load().mrx_merge_meshes(
         _ptr(vtx), _ptr(vtx_offsets), n, 4 * k, _ptr(idx), _ptr(elem_offsets), idx.shape[0], idx.shape[1],
         vtx_offsets.numel() - 1, _ptr(out_vtx), _ptr(out_idx), _ptr(old2new), _ptr(new2old), _ptr(meta),
-        ctypes.c_void_p(meta.data_ptr() + 8), _ptr(workspace), workspace.numel(), make_tuning(tuning),
-        ctypes.c_void_p(_stream_handle(dev)))
+        meta.data_ptr() + 8, _ptr(workspace), workspace.numel(), make_tuning(tuning),
+        _stream_handle(dev))
     check(st, "mrx_merge_meshes")
     r = Reindexed(out_vtx, out_idx, old2new, new2old, meta)
     return r.trim() if sync else r
@@ -194,9 +195,9 @@ def extract_submesh(vtx: torch.Tensor, idx: torch.Tensor, keep: torch.Tensor, *,
         workspace = torch.empty(max(wsb, 1), dtype=torch.uint8, device=dev)
     st = load().mrx_extract_submesh(
         _ptr(vtx), n, 4 * k, _ptr(idx), idx.shape[0], idx.shape[1], _ptr(keep), _ptr(out_vtx), _ptr(out_idx),
-        ctypes.c_void_p(meta.data_ptr() + 16), _ptr(old2new), _ptr(new2old), _ptr(meta),
-        ctypes.c_void_p(meta.data_ptr() + 8), _ptr(workspace), workspace.numel(), make_tuning(tuning),
-        ctypes.c_void_p(_stream_handle(dev)))
+        meta.data_ptr() + 16, _ptr(old2new), _ptr(new2old), _ptr(meta),
+        meta.data_ptr() + 8, _ptr(workspace), workspace.numel(), make_tuning(tuning),
+        _stream_handle(dev))
     check(st, "mrx_extract_submesh")
     r = Extracted(out_vtx, out_idx, old2new, new2old, meta)
     return r.trim() if sync else r
@@ -231,8 +232,8 @@ class MeshMerger:
             _ptr(self.vtx), _ptr(self.vtx_offsets), n, 4 * k, _ptr(self.idx), _ptr(self.elem_offsets),
             self.idx.shape[0], self.idx.shape[1], self.vtx_offsets.numel() - 1, _ptr(self.out_vtx),
             _ptr(self.out_idx), _ptr(self.old2new), _ptr(self.new2old), _ptr(self.meta),
-            ctypes.c_void_p(self.meta.data_ptr() + 8), _ptr(self.workspace), self.workspace.numel(),
-            self._tuning_ptr, ctypes.c_void_p(_stream_handle(self.vtx.device)))
+            self.meta.data_ptr() + 8, _ptr(self.workspace), self.workspace.numel(),
+            self._tuning_ptr, _stream_handle(self.vtx.device))
         check(st, "mrx_merge_meshes")
 
     def result(self) -> Reindexed:
@@ -266,10 +267,10 @@ class SubmeshExtractor:
         n, k = self.vtx.shape
         st = load().mrx_extract_submesh(
             _ptr(self.vtx), n, 4 * k, _ptr(self.idx), self.idx.shape[0], self.idx.shape[1], _ptr(self.keep),
-            _ptr(self.out_vtx), _ptr(self.out_idx), ctypes.c_void_p(self.meta.data_ptr() + 16),
-            _ptr(self.old2new), _ptr(self.new2old), _ptr(self.meta), ctypes.c_void_p(self.meta.data_ptr() + 8),
+            _ptr(self.out_vtx), _ptr(self.out_idx), self.meta.data_ptr() + 16,
+            _ptr(self.old2new), _ptr(self.new2old), _ptr(self.meta), self.meta.data_ptr() + 8,
             _ptr(self.workspace), self.workspace.numel(), self._tuning_ptr,
-            ctypes.c_void_p(_stream_handle(self.vtx.device)))
+            _stream_handle(self.vtx.device))
         check(st, "mrx_extract_submesh")
 
     def result(self) -> "Extracted":
@@ -302,8 +303,8 @@ class Reindexer:
         st = load().mrx_reindex_mesh(
             _ptr(self.vtx), n, 4 * k, _ptr(self.idx), self.idx.shape[0], self.idx.shape[1],
             _ptr(self.out_vtx), _ptr(self.out_idx), _ptr(self.old2new), _ptr(self.new2old), _ptr(self.meta),
-            ctypes.c_void_p(self.meta.data_ptr() + 8), _ptr(self.workspace), self.workspace.numel(),
-            self._tuning_ptr, ctypes.c_void_p(_stream_handle(self.vtx.device)))
+            self.meta.data_ptr() + 8, _ptr(self.workspace), self.workspace.numel(),
+            self._tuning_ptr, _stream_handle(self.vtx.device))
         check(st, "mrx_reindex_mesh")
 
     def result(self) -> Reindexed:
@@ -318,13 +319,21 @@ class BatchReindexed:
     old2new: torch.Tensor
     new2old: torch.Tensor | None
     status: torch.Tensor            # int32 [1]
+    tail: torch.Tensor | None = None  # int64 [2] over the last offset and the status, where they are neighbours
 
     def trim(self) -> "BatchReindexed":
-        st = int(self.status.cpu()[0])
+        """One device->host read of the last offset and the status (two reads
+        where they are no neighbours); raises on a data error."""
+        if self.tail is not None:
+            u, st = self.tail.tolist()
+            st &= 0xFFFFFFFF
+        else:
+            u, st = None, int(self.status.cpu()[0])
         if st == MRX_ERR_INDEX_OUT_OF_RANGE:
             raise IndexError("an index entry is out of range")
         check(st, "mrx_reindex_mesh_batched (device)")
-        u = int(self.out_vtx_offsets[-1].cpu())
+        if u is None:
+            u = int(self.out_vtx_offsets[-1].cpu())
         self.out_vtx = self.out_vtx[:u]
         if self.new2old is not None:
             self.new2old = self.new2old[:u]
@@ -351,11 +360,13 @@ class BatchedReindexer:
         self.num_meshes = vtx_offsets.numel() - 1
         self.tuning = tuning
         self.out_vtx = torch.empty_like(vtx)
-        self.out_vtx_offsets = torch.empty(self.num_meshes + 1, dtype=torch.int64, device=dev)
+        # the status follows the offsets: one read gets it and the last offset
+        self._offsets_status = torch.zeros(self.num_meshes + 2, dtype=torch.int64, device=dev)
+        self.out_vtx_offsets = self._offsets_status[:-1]
         self.out_idx = torch.empty_like(idx)
         self.old2new = torch.empty(n, dtype=torch.int32, device=dev)
         self.new2old = torch.empty(n, dtype=torch.int32, device=dev) if want_new2old else None
-        self.status = torch.zeros(1, dtype=torch.int32, device=dev)
+        self.status = self._offsets_status[-1:].view(torch.int32)[:1]
         wsb = workspace_size(n, 4 * k, idx.numel(), self.num_meshes, tuning)
         self.workspace = torch.empty(max(wsb, 1), dtype=torch.uint8, device=dev)
         self._tuning_ptr = make_tuning(tuning)
@@ -368,12 +379,12 @@ class BatchedReindexer:
             self.idx.shape[0], self.idx.shape[1], self.num_meshes, _ptr(self.out_vtx),
             _ptr(self.out_vtx_offsets), _ptr(self.out_idx), _ptr(self.old2new), _ptr(self.new2old),
             _ptr(self.status), _ptr(self.workspace), self.workspace.numel(), self._tuning_ptr,
-            ctypes.c_void_p(_stream_handle(self.vtx.device)))
+            _stream_handle(self.vtx.device))
         check(st, "mrx_reindex_mesh_batched")
 
     def result(self) -> BatchReindexed:
         return BatchReindexed(self.out_vtx, self.out_vtx_offsets, self.out_idx, self.old2new,
-                              self.new2old, self.status).trim()
+                              self.new2old, self.status, self._offsets_status[-2:]).trim()
 
 
 def reindex_mesh_batched(vtx, vtx_offsets, idx, elem_offsets, *, tuning=None,
@@ -382,7 +393,8 @@ def reindex_mesh_batched(vtx, vtx_offsets, idx, elem_offsets, *, tuning=None,
     sequence. Indices in and out are mesh-local."""
     r = BatchedReindexer(vtx, vtx_offsets, idx, elem_offsets, tuning=tuning)
     r.launch()
-    res = BatchReindexed(r.out_vtx, r.out_vtx_offsets, r.out_idx, r.old2new, r.new2old, r.status)
+    res = BatchReindexed(r.out_vtx, r.out_vtx_offsets, r.out_idx, r.old2new, r.new2old, r.status,
+                         r._offsets_status[-2:])
     return res.trim() if sync else res
 
 
@@ -442,7 +454,7 @@ class GatherAttrs(torch.autograd.Function):
         status = torch.zeros(1, dtype=torch.int32, device=a.device) if validate else None
         check(load().mrx_gather_attrs(_ptr(a), a.shape[0], a.shape[1], _DT[a.dtype], _ptr(idx),
                                       idx.numel(), _ptr(out), _ptr(status),
-                                      ctypes.c_void_p(_stream_handle(a.device))),
+                                      _stream_handle(a.device)),
               "mrx_gather_attrs")
         if validate:
             _raise_on_status(status, "mrx_gather_attrs")
@@ -459,7 +471,7 @@ class GatherAttrs(torch.autograd.Function):
         # the map is the one the forward read (and, with validate, checked)
         check(load().mrx_gather_attrs_backward(_ptr(g), g.shape[0], g.shape[1], _DT[g.dtype], _ptr(idx),
                                                ctx.num_old, _ptr(grad), int(ctx.injective), None,
-                                               ctypes.c_void_p(_stream_handle(g.device))),
+                                               _stream_handle(g.device)),
               "mrx_gather_attrs_backward")
         return grad, None, None, None
 
