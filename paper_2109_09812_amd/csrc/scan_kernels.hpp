@@ -320,6 +320,8 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   constexpr int TILE = kRandBlock * kItems;
   const uint2* __restrict__ pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
   __shared__ int32_t s_cmap[TILE];
+  constexpr bool kStageRep = kItems == kScatterItems;
+  __shared__ uint32_t s_rep[kStageRep ? TILE : 1];
   __shared__ uint32_t s_g[2];
   __shared__ uint32_t s_mesh[2];
   const int64_t t0 = int64_t(blockIdx.x) * TILE;
@@ -350,8 +352,10 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   __syncthreads();
   const uint32_t g0 = s_g[0];
   const int64_t span = min(int64_t(TILE), int64_t(s_g[1]) - int64_t(g0) + 1);
-  for (int64_t i = threadIdx.x; i < span; i += kRandBlock)
+  for (int64_t i = threadIdx.x; i < span; i += kRandBlock) {
     s_cmap[i] = (int64_t(g0) + i < n) ? cmap[int64_t(g0) + i] : -1;
+    if (kStageRep && new2old) s_rep[i] = (int64_t(g0) + i < n) ? rep[int64_t(g0) + i] : 0xFFFFFFFFu;
+  }
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < kItems; ++it) {
@@ -371,17 +375,19 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   for (int it = 0; it < kItems; ++it) {
     if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) continue;  // past the end (or a failed wait)
     int32_t cc = c[it] < 0 ? -1 : c[it];
-    const bool is_rep = new2old && cc >= 0 && cc < n && rep[p[it].x] == p[it].y;
+    const int64_t off = int64_t(p[it].x) - int64_t(g0);
+    const bool is_rep = new2old && cc >= 0 && cc < n &&
+                        (kStageRep && off >= 0 && off < span ? s_rep[off] : rep[p[it].x]) == p[it].y;
     if constexpr (BATCHED) {
       if (cc >= 0) {
-        int64_t off = tile_off, first = tile_vtx;
+        int64_t out0 = tile_off, first = tile_vtx;
         if (!one_mesh) {
           const uint32_t b = mesh_of(vtx_off, nmesh, base + it * kRandBlock, vtx_tab);
-          off = out_off[b];
+          out0 = out_off[b];
           first = vtx_off[b];
         }
         if (is_rep) new2old[cc] = int32_t(int64_t(p[it].y) - first);
-        cc -= int32_t(off);
+        cc -= int32_t(out0);
       }
     } else {
       if (is_rep) new2old[cc] = int32_t(p[it].y);
