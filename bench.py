@@ -234,13 +234,22 @@ def bench_single(args, torch, mrx, meshgen):
             "band_mark_histogram": 4 * mi + n + n * r_bytes,
             "hash_histogram": n * r_bytes,
             # the used values' elements packed from their span slots, with
-            # their key digits counted (the all-element histogram runs only
-            # after a bucket overflowed)
+            # their key digits counted
             "compact_histogram": 2 * u * s_elem,
             "onesweep_hash_first": n * r_bytes + n + n * s_elem,
             "onesweep_hash": 2 * n * s_elem,
+            # one-pass hash buckets: the marking with the buckets' counts,
+            # then the records to their buckets
+            "mark_bucket_count": 4 * mi + n + n * r_bytes,
+            "bucket_count": n * r_bytes,
+            "bucket_scatter": n * r_bytes + n + n * s_elem,
             "group": n * s_elem + 8 * n + 4 * g + 4 * (g - u) + u * s_elem,
             "onesweep": 2 * u * s_elem,
+            # order of the used values by splitters: a 2-byte bucket per
+            # element, the elements bucket by bucket, records and new ids out
+            "split_count": u * s_elem + 2 * u,
+            "split_scatter": 2 * u * s_elem + 2 * u,
+            "split_sort": u * s_elem + u * r_bytes + 4 * u,
             "finalize": u * s_elem + u * r_bytes + 12 * u,
             "old2new": 12 * n + 4 * g,
             "remap": 12 * mi,
@@ -281,8 +290,12 @@ def bench_single(args, torch, mrx, meshgen):
                                        ((ow[0, k - 1 - p // 4] >> np.uint32(8 * (p % 4))) & np.uint32(255))))
         model["onesweep"] = model["onesweep"] * (passes - dead) // passes   # average over the launches
     run_bytes = sum(b * table[name][0] // args.steps for name, b in model.items() if name in table)
-    # the dominant kernel: the LSD digit pass, every launch of it in the step
-    sweep = [nm for nm in table if nm.startswith("onesweep")]
+    # the dominant kernel: the one that takes most of the step among those
+    # with a byte model (all LSD digit passes count as one)
+    family = {nm: "onesweep" if nm.startswith("onesweep") else nm for nm in table if nm in model}
+    spent = {f: sum(table[nm][0] * table[nm][1] for nm in family if family[nm] == f) for f in family.values()}
+    dominant = max(spent, key=spent.get)
+    sweep = [nm for nm in family if family[nm] == dominant]
     sweep_ms = sum(table[nm][0] * table[nm][1] for nm in sweep)
     sweep_bytes = sum(table[nm][0] * model.get(nm, 0) for nm in sweep)
     sweep_launches = sum(table[nm][0] for nm in sweep)
@@ -297,7 +310,7 @@ def bench_single(args, torch, mrx, meshgen):
                 "run_frac": round(run_bytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBPS, 4)}
     return dict(n=n, m=e * a, u=u, ms=ms, ms_prof=ms_prof, kernels=kernels, extract=extract, dist=dist, xfer=xfer,
                 pipeline=pipeline,
-                roofline_pass=dict(achieved=achieved, bytes=sweep_bytes // max(1, sweep_launches),
+                roofline_pass=dict(kernel=dominant, achieved=achieved, bytes=sweep_bytes // max(1, sweep_launches),
                                    mean_ms=sweep_ms / max(1, sweep_launches),
                                    launches_per_step=sweep_launches // args.steps),
                 r_bytes=r_bytes)
@@ -778,11 +791,13 @@ def main():
                                "(25,141,254 referenced + 5% unused), 8,380,418 int32 triangles, permuted",
                    "num_vertices": n, "num_indices": single["m"], "unique_out": single["u"],
                    "record_bytes": single["r_bytes"], "tuning": list(args.chosen_tuning)},
-        "roofline": {"bound": "hbm", "kernel": "k_onesweep (LSD digit pass; every launch of the step)",
+        "roofline": {"bound": "hbm", "kernel": "k_onesweep (LSD digit pass; every launch of the step)"
+                     if rp["kernel"] == "onesweep" else rp["kernel"],
                      "achieved": round(rp["achieved"], 1) if rp["achieved"] else None,
                      "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                      "frac": round(rp["achieved"] / PEAK_HBM_GBPS, 4) if rp["achieved"] else None,
-                     "traffic": measured_traffic(), "bytes_per_launch": rp["bytes"],
+                     "traffic": measured_traffic() if rp["kernel"] == "onesweep" else None,
+                     "bytes_per_launch": rp["bytes"],
                      "mean_launch_ms": rp["mean_ms"], "launches_per_step": rp["launches_per_step"],
                      # the whole step against the roofline: the plain method's
                      # algorithmic bytes for this workload / step time / peak

@@ -91,15 +91,14 @@ typedef struct {
  *   - sort-all: Section 2's method as printed: a stable LSD radix sort of all
  *     N (record, id) pairs by the full record (for a batch: by (mesh id,
  *     record)), then run-head flags and scans;
- *   - hash grouping: a stable sort of the pairs by a few hash digits of the
+ *   - hash grouping: the pairs are gathered in buckets by a hash of the
  *     record (for a batch: of (mesh id, record), in buckets owned by the
- *     vertex's mesh), grouping of equal records (of one mesh) in on-chip
- *     memory, and the full-key sort of the U used values only (falls back to
- *     sort-all on the device when a hash bucket is too large, e.g. a value
- *     with thousands of copies in one mesh).
- * Without either flag the library chooses (hash grouping for meshes and
- * batches of at least 2^16 and fewer than 2^30 vertices in all); setting
- * both is MRX_ERR_UNSUPPORTED. A batch whose meshes would need more than
+ *     vertex's mesh), equal records (of one mesh) are grouped bucket by
+ *     bucket, and only the U used values are put in the full key's order.
+ * Without either flag the library chooses (hash grouping for meshes of at
+ * least 2^10 and batches of at least 2^16 vertices in all, below 2^30; with
+ * an all-zero tuning, meshes that fit one workgroup are sorted whole by it);
+ * setting both is MRX_ERR_UNSUPPORTED. A batch whose meshes would need more than
  * 2^24 hash buckets in all (one per mesh at least, and about one per few
  * hundred vertices) sorts all whatever the flags say. */
 #define MRX_TUNING_SORT_ALL 4
