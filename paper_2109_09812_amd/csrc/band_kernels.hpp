@@ -38,14 +38,14 @@ constexpr int kIdxPartBlock = 512;                  // index partition
 constexpr int kIdxPartItems = 64;
 constexpr int kBandTile = kIdxPartBlock * kIdxPartItems;  // 32768 entries: offsets and counts fit 16 bits
 constexpr int kMaxBands = 1024;
-constexpr int kPairBlock = 512;
-constexpr int kPairItems = 32;
+constexpr int kPairBlock = 1024;  // 512 threads of 32 pairs: 0.204 against 0.197 ms for 26.4M pairs
+constexpr int kPairItems = 16;
 constexpr int kPairTile = kPairBlock * kPairItems;  // 16384 pairs (128 KB staged)
 // Up to some million entries, tiles of a quarter of that: the partitions and
 // the remap of 4.2M entries would otherwise run on 128 workgroups, half the
 // GPU, one to a CU (index partition of 4.2M entries 44 -> 23 us).
 constexpr int kFineIdxItems = 16, kFineBandTile = kIdxPartBlock * kFineIdxItems;
-constexpr int kFinePairItems = 8, kFinePairTile = kPairBlock * kFinePairItems;
+constexpr int kFinePairBlock = 512, kFinePairItems = 8, kFinePairTile = kFinePairBlock * kFinePairItems;
 constexpr int kMinBandShift = 12;                   // bands start 16-byte aligned
 constexpr int kMinFineShift = 8;
 constexpr int kMaxMarkShift = 19;                   // a band's bitmap: at most 64 KB
@@ -320,15 +320,15 @@ struct PairPartArgs {
 
 // The group ids of a tile of pairs are clustered (sorted, or grouped by
 // hash bucket), so the cmap reads hit cache lines other lanes fetched.
-template <int kPairItems, bool BATCHED>
-__global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
-  constexpr int kPairTile = kPairBlock * kPairItems;
+template <int BLOCK, int kPairItems, bool BATCHED>
+__global__ __launch_bounds__(BLOCK) void k_pair_partition(PairPartArgs a) {
+  constexpr int kPairTile = BLOCK * kPairItems;
   __shared__ uint32_t s_cnt[kMaxBands];
   __shared__ uint32_t s_off[kMaxBands];
   __shared__ uint2 s_stage[kPairTile];
-  __shared__ uint32_t s_wave[kPairBlock / kWave];
+  __shared__ uint32_t s_wave[BLOCK / kWave];
   const int tid = threadIdx.x;
-  for (int b = tid; b < kMaxBands; b += kPairBlock) s_cnt[b] = 0;
+  for (int b = tid; b < kMaxBands; b += BLOCK) s_cnt[b] = 0;
   __syncthreads();
   const uint2* pairs = a.from_sort ? reinterpret_cast<const uint2*>(a.sort.spare()) : a.pairs;
   uint2* out = a.from_sort ? reinterpret_cast<uint2*>(a.sort.sorted()) : a.part;
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
   uint2 p[kPairItems];
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i)
-    p[i] = stream_load(pairs + min(uint32_t(base + int64_t(i) * kPairBlock + tid), last));
+    p[i] = stream_load(pairs + min(uint32_t(base + int64_t(i) * BLOCK + tid), last));
   int32_t val[kPairItems];
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i) val[i] = a.cmap[min(p[i].x, last)];
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
   }
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i) {
-    const int64_t k = base + int64_t(i) * kPairBlock + tid;
+    const int64_t k = base + int64_t(i) * BLOCK + tid;
     const bool ok = p[i].x <= last && p[i].y <= last;
     if (k < a.n && !ok) bad = true;  // only after a failed wait
     vtx[i] = k < a.n && ok ? p[i].y : 0xFFFFFFFFu;
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
   for (int i = 0; i < kPairItems; ++i)
     if (vtx[i] != 0xFFFFFFFFu) r[i] = atomicAdd(&s_cnt[vtx[i] >> a.shift], 1u);
   __syncthreads();
-  constexpr int PER = kMaxBands / kPairBlock;
+  constexpr int PER = kMaxBands / BLOCK;
   uint32_t loc[PER], sum = 0;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
     sum += s_cnt[tid * PER + j];
   }
   uint32_t valid;
-  const uint32_t ex = block_exclusive_scan<kPairBlock>(sum, s_wave, &valid);
+  const uint32_t ex = block_exclusive_scan<BLOCK>(sum, s_wave, &valid);
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int b = tid * PER + j;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_partition(PairPartArgs a) {
     if (vtx[i] != 0xFFFFFFFFu)
       s_stage[s_off[vtx[i] >> a.shift] + r[i]] = make_uint2(uint32_t(val[i] < 0 ? -1 : val[i]), vtx[i] & mask);
   __syncthreads();
-  for (uint32_t j = tid; j < valid; j += kPairBlock) stream_store(out + base + j, s_stage[j]);
+  for (uint32_t j = tid; j < valid; j += BLOCK) stream_store(out + base + j, s_stage[j]);
   // scattered, so last: nothing waits behind them
 #pragma unroll
   for (int i = 0; i < kPairItems; ++i)
@@ -540,11 +540,11 @@ static inline void launch_band_mark(const BandArgs& a, bool small_bands, hipStre
 static inline void launch_pair_partition(const PairPartArgs& a, bool fine, hipStream_t s) {
   if (a.tiles <= 0) return;
   if (a.nmesh > 0)
-    hipLaunchKernelGGL((k_pair_partition<kFinePairItems, true>), dim3(a.tiles), dim3(kPairBlock), 0, s, a);
+    hipLaunchKernelGGL((k_pair_partition<kFinePairBlock, kFinePairItems, true>), dim3(a.tiles), dim3(kFinePairBlock), 0, s, a);
   else if (fine)
-    hipLaunchKernelGGL((k_pair_partition<kFinePairItems, false>), dim3(a.tiles), dim3(kPairBlock), 0, s, a);
+    hipLaunchKernelGGL((k_pair_partition<kFinePairBlock, kFinePairItems, false>), dim3(a.tiles), dim3(kFinePairBlock), 0, s, a);
   else
-    hipLaunchKernelGGL((k_pair_partition<kPairItems, false>), dim3(a.tiles), dim3(kPairBlock), 0, s, a);
+    hipLaunchKernelGGL((k_pair_partition<kPairBlock, kPairItems, false>), dim3(a.tiles), dim3(kPairBlock), 0, s, a);
 }
 
 // Fine bands hold at most 2^14 vertices, in 32 or 64 KB of LDS, so that

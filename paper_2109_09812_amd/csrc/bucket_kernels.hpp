@@ -260,6 +260,10 @@ template <int K, int EPT, int FMAX, bool MESH>
 __global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a) {
   using SH = BucketShape<K>;
   constexpr int S = SH::S, BLOCK = kBucketBlock, Q = SH::STAGE, TILE = BLOCK * EPT;
+  // a mesh's columns are read with all loads in flight (0.262 -> 0.241 ms for
+  // 26.4M vertices); a batch's tile has few of its many columns, and registers
+  // for all of them would spill (0.196 -> 0.216 ms for 15M)
+  constexpr bool kAllCols = !MESH;
   // by bucket, from the tile's first: elements (two 16-bit counters a word, so
   // that the most buckets leave room for two workgroups on a CU), then the
   // place in the tile
@@ -324,14 +328,30 @@ __global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a
     // buckets (several may write the same)
     uint32_t before = 0;
     if constexpr (MESH) before = uint32_t(a.mesh_off[tm.lo]);  // buckets are in mesh order
-    const int per = (tm.count + 2 * BLOCK - 1) / (2 * BLOCK) * 2;
+    constexpr int PER = (FMAX + 2 * BLOCK - 1) / (2 * BLOCK) * 2;
+    const int per = (tm.count + 2 * BLOCK - 1) / (2 * BLOCK) * 2;  // <= PER
     const int f0 = tid * per, f1 = min(f0 + per, tm.count);
     uint32_t sum = 0, own = 0;
-    for (int f = f0; f < f1; ++f) {
-      const uint32_t t = a.totals[tm.first + f];
-      s_delta[f] = t;
-      own += t;
-      sum += s_off[f >> 1] >> (16 * (f & 1)) & 0xFFFFu;
+    if constexpr (kAllCols) {
+      uint32_t t[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) t[i] = i < per && f0 + i < f1 ? a.totals[tm.first + f0 + i] : 0u;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int f = f0 + i;
+        if (i < per && f < f1) {
+          s_delta[f] = t[i];
+          own += t[i];
+          sum += s_off[f >> 1] >> (16 * (f & 1)) & 0xFFFFu;
+        }
+      }
+    } else {
+      for (int f = f0; f < f1; ++f) {
+        const uint32_t t = a.totals[tm.first + f];
+        s_delta[f] = t;
+        own += t;
+        sum += s_off[f >> 1] >> (16 * (f & 1)) & 0xFFFFu;
+      }
     }
     uint32_t all;
     uint32_t at = block_exclusive_scan<BLOCK>(sum, s_wave, &all);
@@ -353,9 +373,20 @@ __global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a
     if (tile == a.tiles - 1)
       for (int f = tm.first + tm.count + tid; f <= a.buckets; f += BLOCK) a.starts[f] = uint32_t(a.n);
   }
-  __syncthreads();
   const uint32_t* base = a.base + tile * int64_t(a.buckets) + tm.first;
-  for (int f = tid; f < tm.count; f += BLOCK) s_delta[f] += base[f];
+  if constexpr (kAllCols) {
+    constexpr int BPER = (FMAX + BLOCK - 1) / BLOCK;
+    uint32_t bs[BPER];
+#pragma unroll
+    for (int i = 0; i < BPER; ++i) bs[i] = i * BLOCK + tid < tm.count ? base[i * BLOCK + tid] : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < BPER; ++i)
+      if (i * BLOCK + tid < tm.count) s_delta[i * BLOCK + tid] += bs[i];
+  } else {
+    __syncthreads();
+    for (int f = tid; f < tm.count; f += BLOCK) s_delta[f] += base[f];
+  }
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     if (pos[i] == 0xFFFFFFFFu) continue;

@@ -3,10 +3,11 @@
 //
 // Section 2 finds duplicates by sorting all N (record, id) pairs by the full
 // record; the sort is the dominant cost. Grouping only needs equal records
-// to be adjacent, so here the N pairs are first sorted by a few hash digits
-// of the record (stable, so within a bucket of equal hash digits ids stay
-// ascending). Equal records share their hash, so every group of duplicates
-// lies inside one bucket, and buckets are small enough (a few hundred
+// to be adjacent. Up to some 26 million vertices they are put in buckets in
+// one pass (bucket_kernels.hpp); beyond that, and with k_group below, the N
+// pairs are first sorted by a few hash digits of the record (stable, so within
+// a bucket of equal hash digits ids stay ascending). Equal records share
+// their hash, so every group of duplicates lies inside one bucket, and buckets are small enough (a few hundred
 // records) to be grouped in LDS: k_group numbers the groups of each bucket in
 // order of their first copy, which is the smallest original id (Step 2's
 // representative rule), and emits one element per *used* group. Only those U
