@@ -33,9 +33,12 @@ constexpr int kBucketMaxMesh = 6144;  // batches: at least one per mesh
 constexpr int kBucketMostPer = 10400; // vertices per bucket
 constexpr int kGroupBlock = 1024;     // k_group_bucket
 constexpr int kGroupBlockSmall = 256; // where buckets are aimed to be small
-// larger buckets (values with thousands of copies) go through
-// group_big_bucket, whose time does not depend on how many of them differ
-constexpr int kGroupSlots = 1 << 15;
+// Larger buckets whose distinct records do not fit the table at once start
+// over through group_big_bucket, whose time does not depend on how many of
+// them differ. Smaller ones take another round, and copies cost nothing in
+// LDS: 25M vertices with 12,000 copies of each used value have buckets of up to
+// 80,000, 2.6 ms when all above 2^15 went through group_big_bucket.
+constexpr int kGroupSlots = 1 << 17;
 
 template <int K>
 struct BucketShape {
@@ -446,9 +449,8 @@ __global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBuc
   const int64_t f = blockIdx.x;
   const int64_t b0 = b.starts[f], b1 = b.starts[f + 1];
   uint32_t used_all = 0;
-  if (b1 - b0 > kGroupSlots) {
-    used_all = group_big_bucket<K, MESH, BLOCK>(a, b0, b1, b0, s_big);
-  } else if (b1 > b0) {
+  bool big = false;
+  if (b1 > b0) {
     const uint32_t cnt = uint32_t(b1 - b0), last = cnt - 1u;
     const uint32_t* const elems = a.elems + b0 * S;
     uint2* const pairs = a.pairs + b0;
@@ -517,6 +519,8 @@ __global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBuc
         if (s_full == 0) break;
       }
       const bool again = s_full != 0;
+      big = again && round == 0 && b1 - b0 > kGroupSlots;
+      if (big) break;  // nothing is kept but pairs, which are written again
       const bool dense = again || round > 0;
       const uint32_t places = min(s_n, uint32_t(DCAP));
       // slots of the used groups, and dense names where there are several
@@ -561,6 +565,7 @@ __global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBuc
       __syncthreads();
     }
   }
+  if (big) used_all = group_big_bucket<K, MESH, BLOCK>(a, b0, b1, b0, s_big);
   if (tid == 0) {
     a.chunks[f] = make_uint2(uint32_t(b0), used_all);
     if (used_all) atomicAdd(&a.range_sums[group_run_of(f, gridDim.x, a.ranges)], used_all);

@@ -118,3 +118,15 @@ def test_map_scatter_tiles(n):
     assert np.array_equal(new2old, order[head][used])
     assert np.array_equal(out_vtx, vtx[order[head][used]])
     assert np.array_equal(out_idx[:, 0], new[idx[:, 0]])
+
+
+@pytest.mark.parametrize("copies", [100_000, 200_000])
+def test_many_copies_beside_more_distinct_records_than_fit(copies):
+    """A bucket of 103,000 takes further rounds, one of 203,000 starts over in
+    global memory."""
+    rng = np.random.default_rng(copies)
+    n = 9_000_000
+    vtx = rng.integers(0, 2**32, size=(n, 3), dtype=np.uint64).astype(np.uint32)
+    vtx[rng.choice(n, copies, replace=False)] = vtx[0]
+    idx = rng.integers(0, n, n // 4).astype(np.int32).reshape(-1, 1)
+    check(vtx, idx, f"copies={copies}", run(vtx, idx, SORT_ALL))
