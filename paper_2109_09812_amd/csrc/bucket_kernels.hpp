@@ -12,6 +12,11 @@
 //  * k_bucket_scatter: elements (record, id | used << 31) to their buckets,
 //    put in bucket order in LDS first so that runs are written together;
 //  * k_group_bucket: equal records of a bucket by a hash table in LDS.
+// Measured (MI355X), 26.4M 12-byte vertices of a soup: offsets 0.035, scatter
+// 0.235 (3.3 TB/s, bound by runs of three elements per tile and bucket) and
+// grouping 0.242 ms (3.0 TB/s, phases of memory and LDS work of two workgroups
+// a CU), where two stable passes and k_group took 0.21 + 0.24 and 0.27 ms; 15M
+// in 256 meshes 0.010 + 0.196 + 0.185 ms, the whole call 1.65 -> 1.23 ms.
 // The order inside a bucket is that of atomics, so a group's representative is
 // the minimum of its ids. Only a bucket's distinct records take LDS, and where
 // they do not fit, the rest of the bucket takes another round.
