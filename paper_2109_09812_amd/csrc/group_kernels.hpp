@@ -175,9 +175,10 @@ __device__ int64_t end_of_bucket(const GroupArgs& a, int64_t b0, uint32_t* s_x) 
 // by a comparison in registers and touch no table. Everything the
 // workgroup's waves tell each other through memory goes by agent-scope
 // atomics (L2), ordered by fences. Chains are only ever prepended to, so a
-// failed insertion re-reads what was added and retries. Bound: one
-// workgroup's streaming rate, about 2,000 elements per 2 microseconds; a
-// value needs over a million copies before that is felt in a call. Returns
+// failed insertion re-reads what was added and retries. Bound: the round trips
+// of one workgroup's atomics, some 30 elements a microsecond where copies of
+// several values meet; k_group_bucket comes here only when LDS rounds would
+// take longer. Returns
 // the number of used groups; their elements start at slot `upre`.
 template <int K, bool MESH, int BLOCK>
 __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t b1, int64_t upre, uint32_t* s_x) {
