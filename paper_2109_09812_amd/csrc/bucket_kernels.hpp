@@ -577,20 +577,4 @@ __global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBuc
   }
 }
 
-// Hash buckets of a batch's meshes for k_bucket_count: ceil(vertices /
-// target) each, in mesh order. One workgroup.
-static __global__ __launch_bounds__(1024) void k_mesh_bucket_ranges(const int64_t* __restrict__ off, int32_t nmesh,
-                                                                    int32_t target, uint2* __restrict__ mb) {
-  __shared__ uint32_t s_wave[1024 / kWave];
-  uint32_t carry = 0;
-  for (int64_t b0 = 0; b0 < nmesh; b0 += 1024) {
-    const int64_t b = b0 + threadIdx.x;
-    const uint32_t cnt = b < nmesh ? uint32_t((off[b + 1] - off[b] + target - 1) / target) : 0u;
-    uint32_t total;
-    const uint32_t ex = block_exclusive_scan<1024>(cnt, s_wave, &total);
-    if (b < nmesh) mb[b] = make_uint2(carry + ex, cnt);
-    carry += total;
-  }
-}
-
 }  // namespace mrx

@@ -12,6 +12,7 @@
 #include "../../include/meshrx.h"
 #include "band_kernels.hpp"
 #include "edit_kernels.hpp"
+#include "mesh_ranges.hpp"
 #include "registry.hpp"
 
 namespace mrx {
@@ -58,8 +59,7 @@ __global__ void k_batch_offsets(const int64_t* __restrict__ vtx_off, int32_t nme
 // or those of the output vertices. Mesh b's outputs start at the
 // number of entries below vtx_off[b] (a binary search per mesh).
 __global__ void k_batch_offsets_dense(const uint32_t* __restrict__ dense, int32_t stride, const Control* ctl,
-                                      const int64_t* __restrict__ vtx_off, int32_t nmesh,
-                                      int64_t* __restrict__ out_off) {
+                                      const int64_t* vtx_off, int32_t nmesh, int64_t* out_off) {
   const int32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b > nmesh) return;
   const int64_t u = ctl->num_used;
@@ -70,31 +70,6 @@ __global__ void k_batch_offsets_dense(const uint32_t* __restrict__ dense, int32_
     if (int64_t(dense[mid * stride + stride - 1]) < start) lo = mid + 1; else hi = mid;
   }
   out_off[b] = lo;
-}
-
-// Hash buckets of a batch's meshes (mesh_bucket): mesh b gets the smallest
-// power-of-two count of buckets that brings its vertices per bucket down to
-// `target`, and the meshes' ranges follow each other in mesh order. One
-// workgroup.
-constexpr int kMeshBucketBlock = 1024;
-__global__ __launch_bounds__(kMeshBucketBlock) void k_mesh_buckets(const int64_t* __restrict__ off, int32_t nmesh,
-                                                                   int32_t target, uint2* __restrict__ mb) {
-  __shared__ uint32_t s_wave[kMeshBucketBlock / kWave];
-  uint32_t carry = 0;
-  for (int64_t b0 = 0; b0 < nmesh; b0 += kMeshBucketBlock) {
-    const int64_t b = b0 + threadIdx.x;
-    uint32_t cnt = 0;
-    if (b < nmesh) {
-      const int64_t nb = off[b + 1] - off[b];
-      int k = 0;
-      while (k < 30 && (nb >> k) > target) ++k;
-      cnt = 1u << k;
-    }
-    uint32_t total;
-    const uint32_t ex = block_exclusive_scan<kMeshBucketBlock>(cnt, s_wave, &total);
-    if (b < nmesh) mb[b] = make_uint2(carry + ex, cnt - 1u);
-    carry += total;
-  }
 }
 
 __global__ void k_localize_new2old(int32_t* __restrict__ new2old, const int64_t* __restrict__ total_used,
@@ -583,10 +558,10 @@ struct OrderArgs {
   bool wide;
   uint32_t* counter;         // nullable
   int gp;                    // passes of the call so far
-  const int64_t* mesh_off;   // batches
+  const int64_t* vtx_off;    // batches
   const int32_t* mesh_tab;
   int32_t nmesh;
-  int64_t* out_off;
+  int64_t* out_off;          // holds the meshes' ordered vertex offsets and receives the output offsets
 };
 
 // The sample sort's buckets and samples are sized for tens of millions of
@@ -624,7 +599,7 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
     a.order = o.C;  // free once scattered
     a.out_num = o.out_num;
     a.ctl = o.ctl;
-    a.mesh_off = o.mesh_off;
+    a.mesh_off = o.out_off;
     a.mesh_tab = o.mesh_tab;
     a.nmesh = o.nmesh;
     prof_mark("split_sample", s);
@@ -643,7 +618,7 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
       prof_mark("batch_offsets", s);
       hipLaunchKernelGGL(k_batch_offsets_dense, dim3((o.nmesh + 1 + 255) / 256), dim3(256), 0, s,
                          static_cast<const uint32_t*>(a.order), 1, static_cast<const Control*>(o.ctl),
-                         o.mesh_off, o.nmesh, o.out_off);
+                         static_cast<const int64_t*>(o.out_off), o.nmesh, o.out_off);
     }
     return;
   }
@@ -658,7 +633,7 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
     prof_mark("batch_offsets", s);
     hipLaunchKernelGGL(k_batch_offsets_dense, dim3((o.nmesh + 1 + 255) / 256), dim3(256), 0, s,
                        static_cast<const uint32_t*>(o.X), int32_t(K + 1), static_cast<const Control*>(o.ctl),
-                       o.mesh_off, o.nmesh, o.out_off);
+                       static_cast<const int64_t*>(o.out_off), o.nmesh, o.out_off);
     prof_mark("mesh_histogram", s);
     v.mesh_hist(o.out_off, o.nmesh, L.P_mesh, o.hist + size_t(L.P_key) * v.radix(), s);
   }
@@ -679,7 +654,7 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
     a.status = o.status;
     a.n = n;
     a.n_dev = &o.ctl->num_used;
-    a.mesh_off = o.mesh_off;
+    a.mesh_off = o.vtx_off;
     a.mesh_tab = o.mesh_tab;
     a.nmesh = o.nmesh;
     a.tag = uint32_t(gp + 1);
@@ -1227,9 +1202,20 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(int64_t(L.zero_end / 16), 256, 4096)), dim3(256), 0, s,
                      reinterpret_cast<uint4*>(ws), int64_t(L.zero_end / 16), dev_status,
                      static_cast<int64_t*>(nullptr), static_cast<int64_t*>(nullptr));
-  // n > 0 and num_meshes > 1 here (use_batched_hash)
+  // n > 0 and num_meshes > 1 here (use_batched_hash). The grouping and the
+  // ordering go by the ordered offsets, which the output offsets' array holds
+  // until those are known; Steps 1 and 4, which check every place they touch,
+  // by the caller's.
+  const int64_t* ordered = out_vtx_offsets;
+  prof_mark("mesh_buckets", s);
+  if (bucketed)
+    hipLaunchKernelGGL(k_mesh_buckets<false>, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes, n,
+                       bs.plan.target, out_vtx_offsets, mbk);
+  else
+    hipLaunchKernelGGL(k_mesh_buckets<true>, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes, n,
+                       int32_t(v.group_mesh_target_bucket), out_vtx_offsets, mbk);
   prof_mark("mesh_tables", s);
-  hipLaunchKernelGGL(k_mesh_table, dim3((L.vtx_tab_n + 255) / 256), dim3(256), 0, s, vtx_offsets, num_meshes, n,
+  hipLaunchKernelGGL(k_mesh_table, dim3((L.vtx_tab_n + 255) / 256), dim3(256), 0, s, ordered, num_meshes, n,
                      vtab, L.vtx_tab_n);
   const int64_t num_e = total_elems;
   if (etab && num_e > 0) {
@@ -1239,12 +1225,6 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   } else {
     etab = nullptr;
   }
-  prof_mark("mesh_buckets", s);
-  if (bucketed)
-    hipLaunchKernelGGL(k_mesh_bucket_ranges, dim3(1), dim3(1024), 0, s, vtx_offsets, num_meshes, bs.plan.target, mbk);
-  else
-    hipLaunchKernelGGL(k_mesh_buckets, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes,
-                       int32_t(v.group_mesh_target_bucket), mbk);
   // Step 1 by vertex bands, or by scattered byte stores beside the
   // bucket-digit histograms of the stable sort of (record, id | used << 31)
   // by the buckets of (mesh id, record)
@@ -1280,7 +1260,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   g.cmap = cmap;
   g.uelems = buf[2];
   g.status = status;
-  g.mesh_off = vtx_offsets;
+  g.mesh_off = ordered;
   g.mesh_tab = vtab;
   g.mesh_buckets = mbk;
   g.nmesh = num_meshes;
@@ -1288,7 +1268,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
     bs.args.vtx = static_cast<const uint32_t*>(vtx);
     bs.args.used = used_v;
     bs.args.elems = X;
-    bs.args.mesh_off = vtx_offsets;
+    bs.args.mesh_off = ordered;
     bs.args.mesh_tab = vtab;
     bs.args.mesh_buckets = mbk;
     bs.args.nmesh = num_meshes;
@@ -1302,7 +1282,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
       launch_band_mark(ba, true, s);
     }
     prof_mark(scatter_mark ? "mark_histogram" : "hash_histogram", s);
-    v.hash_mesh_hist(scatter_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, vtx_offsets, num_meshes,
+    v.hash_mesh_hist(scatter_mark ? &mark : nullptr, static_cast<const uint32_t*>(vtx), n, ordered, num_meshes,
                      vtab, mbk, ph, hist_hash, s);
     prof_mark("scan_buckets", s);
     v.scan(hist_hash, ph, n, nullptr, dead_hash, s);
@@ -1320,7 +1300,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
       a.ctl = ctl;
       a.status = status;
       a.n = n;
-      a.mesh_off = vtx_offsets;
+      a.mesh_off = ordered;
       a.mesh_tab = vtab;
       a.mesh_buckets = mbk;
       a.nmesh = num_meshes;
@@ -1360,7 +1340,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   o.wide = wide;
   o.counter = claimed ? counters + counter : nullptr;
   o.gp = gp;
-  o.mesh_off = vtx_offsets;
+  o.vtx_off = vtx_offsets;
   o.mesh_tab = vtab;
   o.nmesh = num_meshes;
   o.out_off = out_vtx_offsets;

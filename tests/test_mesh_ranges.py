@@ -1,0 +1,146 @@
+"""Batches whose device offsets break their rules. The grouping indexes tables
+by a mesh's vertex range and buckets, so the offsets are put in order first
+(csrc/mesh_ranges.hpp). CPU: whatever the offsets hold, the ordered ranges
+stay inside the vertices and the buckets inside the tables sized for them.
+GPU: vertices behind the last offset count with the last mesh, and offsets in
+disorder leave everything around the call's buffers alone."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "bucket_kernels.hpp"
+#include "mesh_ranges.hpp"
+using namespace mrx;
+static int fail(const char* what, int form, long long n, int nmesh) {
+  printf("%s: form %d, n %lld, %d meshes\n", what, form, n, nmesh);
+  return 1;
+}
+template <int K>
+static int check(int form, int64_t n, int32_t nmesh, const std::vector<int64_t>& off) {
+  const BucketPlan p = bucket_plan<K>(n, nmesh, n * (K + 1));
+  std::vector<int64_t> ordered(nmesh + 1);
+  uint32_t reached = 0;
+  int64_t buckets = 0, digits = 0;
+  const int target = GroupShape<K + 1>::TARGET_BUCKET;
+  for (int b = 0; b < nmesh; ++b) {
+    const uint32_t lo = std::max(reached, cut_offset(off.data(), b, nmesh, n));
+    const uint32_t hi = std::max(lo, cut_offset(off.data(), b + 1, nmesh, n));
+    ordered[b] = lo;
+    reached = lo;
+    if (p.buckets) buckets += mesh_bucket_count(hi - lo, p.target, false);
+    digits += mesh_bucket_count(hi - lo, target, true);
+    if (b + 1 == nmesh && int64_t(hi) != n) return fail("last range", form, n, nmesh);
+  }
+  ordered[nmesh] = n;
+  if (ordered[0] != 0) return fail("first range", form, n, nmesh);
+  for (int b = 0; b < nmesh; ++b)
+    if (ordered[b] < 0 || ordered[b] > ordered[b + 1] || ordered[b + 1] > n) return fail("order", form, n, nmesh);
+  if (form == 0 && ordered != off) return fail("valid offsets changed", form, n, nmesh);
+  if (p.buckets && buckets > p.buckets) return fail("buckets", form, n, nmesh);
+  if (p.buckets > kBucketMaxMesh) return fail("columns", form, n, nmesh);
+  if (digits > int64_t(nmesh) + 2 * n / target + 1) return fail("digit buckets", form, n, nmesh);
+  return 0;
+}
+int main() {
+  std::mt19937_64 rng(5);
+  for (int it = 0; it < 4000; ++it) {
+    const int form = it % 6;
+    const int32_t nmesh = 2 + int32_t(rng() % (it % 7 ? 40 : 6000));
+    const int64_t n = 1 + int64_t(rng() % (it % 5 ? 300000 : 40000000));
+    std::vector<int64_t> off(nmesh + 1, 0);
+    for (int b = 1; b < nmesh; ++b) off[b] = int64_t(rng() % uint64_t(n + 1));
+    std::sort(off.begin(), off.end() - 1);
+    off[nmesh] = n;
+    if (form == 1) for (auto& x : off) x = x * 2 / 3;                          // ends early
+    if (form == 2) for (auto& x : off) x = int64_t(rng() % uint64_t(n + 1));   // no order
+    if (form == 3) for (auto& x : off) x = int64_t(rng());                     // anything
+    if (form == 4) for (auto& x : off) x = 3 * x + 7;                          // runs past the end
+    if (form == 5) std::reverse(off.begin(), off.end());
+    if (check<1>(form, n, nmesh, off) || check<3>(form, n, nmesh, off) || check<15>(form, n, nmesh, off)) return 1;
+  }
+  printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_ordered_ranges_stay_inside_the_tables(tmp_path):
+    src, exe = tmp_path / "ranges.hip", str(tmp_path / "ranges")
+    src.write_text(PROGRAM)
+    hipcc = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
+    subprocess.check_call([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                           "-packed-fp32-ops", "-I", os.path.join(ROOT, "paper_2109_09812_amd", "csrc"), str(src),
+                           "-o", exe], stderr=subprocess.DEVNULL)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
+
+
+def _batch(sizes, seed):
+    rng = np.random.default_rng(seed)
+    vs = [rng.integers(0, max(2, s // 3), size=(s, 3), dtype=np.uint64).astype(np.uint32) for s in sizes]
+    es = [rng.integers(0, max(s, 1), size=(s // 2, 2)).astype(np.int32) for s in sizes]
+    vo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    eo = np.concatenate([[0], np.cumsum([e.shape[0] for e in es])]).astype(np.int64)
+    return np.concatenate(vs), vo, np.concatenate(es), eo
+
+
+def _dev(*arrays):
+    return [torch.from_numpy(np.ascontiguousarray(a if a.dtype != np.uint32 else a.view(np.int32))).to("cuda:0")
+            for a in arrays]
+
+
+# one partition pass with and without bands, and (more meshes than it has
+# columns for) passes by hash digits
+@pytest.mark.gpu
+@pytest.mark.parametrize("meshes,size", [(40, 2000), (300, 7000), (6000, 12)])
+def test_vertices_behind_the_last_offset(meshes, size):
+    """A packed buffer with spare room: copies of the last mesh's records and
+    others, which no entry names."""
+    import paper_2109_09812_amd as mrx
+    vtx, vo, idx, eo = _batch([size + b % 5 for b in range(meshes - 1)] + [9000], meshes)
+    last = vtx[vo[-2]:]
+    spare = np.concatenate([last[::-1], last[: 2000] + np.uint32(1 << 20)])
+    packed = np.concatenate([vtx, spare])
+    print("[case] spare room,", meshes, "meshes,", packed.shape[0], "vertices", flush=True)
+    r = mrx.reindex_mesh_batched(*_dev(packed, vo, idx, eo))
+    whole = vo.copy()
+    whole[-1] = packed.shape[0]
+    want = oracle.reindex_batched(packed, idx, whole, eo)
+    for name, e in zip(("out_vtx", "out_vtx_offsets", "out_idx", "old2new", "new2old"), want):
+        g = getattr(r, name).cpu().numpy()
+        assert np.array_equal(g.view(np.uint32) if name == "out_vtx" else g, e), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("meshes,size", [(40, 2000), (300, 7000), (6000, 12)])
+@pytest.mark.parametrize("form", ["decreasing", "past the end", "negative"])
+def test_offsets_in_disorder_stay_in_bounds(meshes, size, form):
+    import paper_2109_09812_amd as mrx
+    vtx, vo, idx, eo = _batch([size] * meshes, meshes)
+    bad = {"decreasing": vo[::-1].copy(), "past the end": vo * 5 + 3, "negative": vo - vo[-1] // 2}[form]
+    print("[case]", form, meshes, "meshes,", vtx.shape[0], "vertices", flush=True)
+    r = mrx.BatchedReindexer(*_dev(vtx, bad, idx, eo))
+    guard, room = 1 << 20, r.workspace.numel()
+    around = torch.full((room + 2 * guard,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    r.workspace = around[guard:guard + room]
+    r.launch()
+    torch.cuda.synchronize()
+    assert bool((around[:guard] == 0x5A).all()) and bool((around[guard + room:] == 0x5A).all())
+    # the same buffers serve the same meshes with their offsets in order
+    r.vtx_offsets = torch.from_numpy(vo).to("cuda:0")
+    r.launch()
+    res = r.result()
+    want = oracle.reindex_batched(vtx, idx, vo, eo)
+    assert np.array_equal(res.out_idx.cpu().numpy(), want[2]) and np.array_equal(res.old2new.cpu().numpy(), want[3])
