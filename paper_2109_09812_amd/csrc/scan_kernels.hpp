@@ -319,9 +319,8 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
                                                                 int32_t* __restrict__ new2old) {
   constexpr int TILE = kRandBlock * kItems;
   const uint2* __restrict__ pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
-  __shared__ int32_t s_cmap[TILE];
+  __shared__ int32_t s_stage[TILE];  // cmap, then (large tiles) the representatives
   constexpr bool kStageRep = kItems == kScatterItems;
-  __shared__ uint32_t s_rep[kStageRep ? TILE : 1];
   __shared__ uint32_t s_g[2];
   __shared__ uint32_t s_mesh[2];
   const int64_t t0 = int64_t(blockIdx.x) * TILE;
@@ -353,15 +352,40 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   const uint32_t g0 = s_g[0];
   const int64_t span = min(int64_t(TILE), int64_t(s_g[1]) - int64_t(g0) + 1);
   for (int64_t i = threadIdx.x; i < span; i += kRandBlock) {
-    s_cmap[i] = (int64_t(g0) + i < n) ? cmap[int64_t(g0) + i] : -1;
-    if (kStageRep && new2old) s_rep[i] = (int64_t(g0) + i < n) ? rep[int64_t(g0) + i] : 0xFFFFFFFFu;
+    s_stage[i] = (int64_t(g0) + i < n) ? cmap[int64_t(g0) + i] : -1;
   }
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < kItems; ++it) {
     const int64_t off = int64_t(p[it].x) - int64_t(g0);
     if (int64_t(p[it].x) >= n) c[it] = -1;
-    else c[it] = (off >= 0 && off < span) ? s_cmap[off] : cmap[p[it].x];  // outside: only after a failed wait
+    else c[it] = (off >= 0 && off < span) ? s_stage[off] : cmap[p[it].x];  // outside: only after a failed wait
+  }
+  // which pairs hold their group's representative: staged in the same LDS where
+  // many groups of the tile are used (with room for both, half as many
+  // workgroups on a CU took 0.69 ms for 26M vertices of which few were used,
+  // 0.57 with the stage in every tile, and 0.46 as it is)
+  uint32_t reps = 0;
+  if (new2old) {
+    int used = 0;
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) used += c[it] >= 0 ? 1 : 0;
+    const bool staged = kStageRep && __syncthreads_or(used > kItems / 2);
+    if (staged) {
+      for (int64_t i = threadIdx.x; i < span; i += kRandBlock)
+        s_stage[i] = (int64_t(g0) + i < n) ? int32_t(rep[int64_t(g0) + i]) : -1;
+      __syncthreads();
+    }
+    uint32_t r[kItems];
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+      const int64_t off = int64_t(p[it].x) - int64_t(g0);
+      r[it] = 0xFFFFFFFFu;
+      if (c[it] < 0 || c[it] >= n) continue;
+      r[it] = staged && off >= 0 && off < span ? uint32_t(s_stage[off]) : rep[p[it].x];
+    }
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) reps |= r[it] == p[it].y ? 1u << it : 0u;
   }
   int64_t tile_off = 0, tile_vtx = 0;  // output and vertex offsets of the tile's mesh, if it has one
   const bool one_mesh = BATCHED && s_mesh[0] == s_mesh[1];
@@ -375,9 +399,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   for (int it = 0; it < kItems; ++it) {
     if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) continue;  // past the end (or a failed wait)
     int32_t cc = c[it] < 0 ? -1 : c[it];
-    const int64_t off = int64_t(p[it].x) - int64_t(g0);
-    const bool is_rep = new2old && cc >= 0 && cc < n &&
-                        (kStageRep && off >= 0 && off < span ? s_rep[off] : rep[p[it].x]) == p[it].y;
+    const bool is_rep = reps >> it & 1u;
     if constexpr (BATCHED) {
       if (cc >= 0) {
         int64_t out0 = tile_off, first = tile_vtx;
