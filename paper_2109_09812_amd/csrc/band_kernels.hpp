@@ -298,7 +298,8 @@ __global__ __launch_bounds__(BLOCK) void k_band_mark(BandArgs a) {
 // pointers.
 struct PairPartArgs {
   const uint2* pairs;          // [n] (group, vertex) pairs of Step 3
-  const int32_t* cmap;         // [G] new id of each group, negative if the group is unused
+  const int32_t* cmap;         // [G] new id of each group, negative if the group is unused (after hash grouping
+                               // -1, or led_name)
   int64_t n;
   int32_t shift;
   int32_t nb;
@@ -308,6 +309,7 @@ struct PairPartArgs {
   int32_t* status;
   const uint32_t* rep;         // [n] representative of each used group, by name
   int32_t* new2old;            // nullable (hash grouping): receives them, at the groups' new ids
+  const uint32_t* large;       // null after sort-all; not 0: there were large buckets (led_name)
   SortBuffers sort;
   int32_t from_sort;
   // batches: new ids and representatives become mesh-local (a pair's mesh is
@@ -351,6 +353,16 @@ __global__ __launch_bounds__(BLOCK) void k_pair_partition(PairPartArgs a) {
   for (int i = 0; i < kPairItems; ++i) {
     at[i] = 0xFFFFFFFFu;
     if (a.new2old) at[i] = a.rep[min(p[i].x, last)];
+  }
+  if (a.large && *a.large != 0) {
+    // names that lead to another of their group
+#pragma unroll
+    for (int i = 0; i < kPairItems; ++i) {
+      if (val[i] >= -1 || p[i].x > last) continue;
+      p[i].x = led_name(val[i]);
+      val[i] = a.cmap[min(p[i].x, last)];
+      if (a.new2old) at[i] = a.rep[min(p[i].x, last)];
+    }
   }
   uint32_t vtx[kPairItems];
   bool bad = false;

@@ -38,12 +38,6 @@ constexpr int kBucketMaxMesh = 6144;  // batches: at least one per mesh
 constexpr int kBucketMostPer = 10400; // vertices per bucket
 constexpr int kGroupBlock = 1024;     // k_group_bucket
 constexpr int kGroupBlockSmall = 256; // where buckets are aimed to be small
-// Larger buckets whose distinct records do not fit the table at once start
-// over through group_big_bucket, whose time does not depend on how many of
-// them differ. Smaller ones take another round, and copies cost nothing in
-// LDS: 25M vertices with 12,000 copies of each used value have buckets of up to
-// 80,000, 2.6 ms when all above 2^15 went through group_big_bucket.
-constexpr int kGroupSlots = 1 << 17;
 
 template <int K>
 struct BucketShape {
@@ -111,6 +105,8 @@ struct BucketArgs {
   uint32_t* totals;            // [buckets]
   uint32_t* starts;            // [buckets + 1]
   uint32_t* elems;             // [n][K+1]
+  uint32_t most;               // a bucket of more elements is large
+  uint32_t* large;             // zeroed; set where there is one
   // batches: vertex offsets, their bucket table, and each mesh's (first
   // bucket, buckets)
   const int64_t* mesh_off;
@@ -250,7 +246,10 @@ __global__ __launch_bounds__(kOffsetCols* kOffsetRuns) void k_bucket_offsets(Buc
   __syncthreads();
   uint32_t at = 0;
   for (int r = 0; r < run; ++r) at += s_sum[r][c];
-  if (own && run == kOffsetRuns - 1) a.totals[f] = at + sum;
+  if (own && run == kOffsetRuns - 1) {
+    a.totals[f] = at + sum;
+    if (at + sum > a.most) *a.large = 1;
+  }
   for (int t = t0; t < t1; t += U) {
     uint32_t x[U];
 #pragma unroll
@@ -419,161 +418,317 @@ __global__ __launch_bounds__(kBucketBlock, 4) void k_bucket_scatter(BucketArgs a
   }
 }
 
+// A bucket of more elements than two parts (many copies of some records) is
+// grouped by several workgroups: its own takes the elements up to the next
+// multiple of `part`, and for every multiple of `part` inside the bucket one
+// more the part that begins there. Where there is no large bucket, these
+// helpers, the last of the grid, leave after one load.
+struct LargeBuckets {
+  int32_t part;             // elements
+  int32_t helpers;          // multiples of `part` in (0, n)
+  const uint32_t* any;      // not 0: some bucket is large
+  uint32_t* state;          // [helpers + 1][2] zeroed, by b0 / part: parts done, groups listed
+
+  __device__ __forceinline__ uint32_t* listed(int64_t b0) const {
+    return state + 2 * (uint32_t(b0) / uint32_t(part)) + 1;
+  }
+  // End of the part of a large bucket that begins at q0.
+  __device__ __forceinline__ int64_t end(int64_t q0, int64_t b1) const {
+    return min(b1, int64_t(uint32_t(q0) / uint32_t(part) + 1) * part);
+  }
+};
+// One workgroup streams about 1,400 elements a microsecond: parts of n / 256
+// take less time than the other buckets together, and below 4,096 elements the
+// merge costs more than they share out.
+constexpr int kLeastPart = 4096;
+inline int32_t large_part(int64_t n) { return int32_t(std::max<int64_t>(kLeastPart, (n + 255) / 256)); }
+inline int32_t large_helpers(int64_t n) { return int32_t((n + large_part(n) - 1) / large_part(n)) - 1; }
+
 struct GroupBucketArgs {
   GroupArgs g;              // elems, n, pairs, rep, cmap, uelems, chunks, range_sums, ranges, mesh_*
   const uint32_t* starts;   // [buckets + 1]
-  int32_t buckets;          // the grid
+  int32_t buckets;          // the grid is buckets + helpers
   int32_t target;           // elements per bucket aimed at
+  LargeBuckets large;
 };
 
-// Groups of one bucket, whose records stream past a table in LDS. A thread
-// that finds an empty slot writes its record to a free place of the list of
-// distinct records and then publishes the place in the slot; if another
-// thread was faster it keeps the place for its next new record. A group is
-// named by the bucket's start plus its place (no more places are taken than
-// there are elements), so an element's pair is written at once. When the list
-// is full nothing is added any more; the elements not found in the table by
-// then (all copies of a record alike) wait for the next round, and the
-// groups of such a bucket get dense names.
+// LDS of a workgroup that groups records: up to DCAP distinct ones at a time.
+template <int K, int BLOCK, int DCAP>
+struct GroupTable {
+  static constexpr int TB = DCAP > 3072 ? 13 : DCAP > 1536 ? 12 : DCAP > 768 ? 11 : 10, TS = 1 << TB;
+  static_assert(TS * 3 >= DCAP * 4, "table load");
+  uint32_t key[K * DCAP];        // distinct records, word-major
+  uint32_t tab[TS];              // place in that list
+  uint32_t min[DCAP];            // smallest id
+  uint32_t used[DCAP / 32];
+  uint32_t wave[BLOCK / kWave];
+  uint32_t n, full;
+  uint32_t x[4];
+};
+
+// Share (hash interval) of a record, by bits that neither its bucket nor its
+// slot goes by.
+__device__ __forceinline__ uint32_t hash_share(uint32_t h, uint32_t shares) {
+  h = (h ^ (h >> 15)) * 0x2C1B3C6Du;
+  return __umulhi((h ^ (h >> 13)) * 0x297A2D39u, shares);
+}
+
+// Shares for a bucket of cnt elements whose list of dcap distinct records was
+// full after e of them: records as many as would leave that many distinct ones
+// among e if all were equally frequent, a little less than a list a share. Too
+// few shares show as another full list.
+__device__ __forceinline__ uint32_t group_shares(uint32_t e, uint32_t cnt, float dcap) {
+  float lo = dcap, hi = float(cnt);
+  for (int i = 0; i < 12; ++i) {
+    const float d = 0.5f * (lo + hi);
+    if (d * (1.0f - __expf(-float(e) / d)) < dcap) lo = d; else hi = d;
+  }
+  return max(2u, uint32_t(ceilf(hi / (0.93f * dcap))));
+}
+// Most shares a list's worth of elements may be cut into: records of different
+// hashes need two at most.
+constexpr uint32_t kMostShares = 8;
+
+// Groups the elements [q0, q1) of the bucket [b0, b1), all of it or one part,
+// and where this part is the last of its bucket to end, the bucket: true then,
+// with the number of used groups, whose elements start at `slot0`.
+//
+// The records stream past a table in LDS. A thread that finds an empty slot
+// writes its record to a free place of the list of distinct records and then
+// publishes the place in the slot; if another thread was faster it keeps the
+// place for its next new record. A group is named by q0 plus its place (no
+// more places are taken than there are elements), so an element's pair is
+// written at once. When the list is full, the records are cut into shares by
+// their hash and every share takes a round of its own: an element is looked
+// up in the round of its share alone, whose list then holds its record. (With
+// elements that found the list full left to the next round, which looks all
+// of them up again in a full table, 26M distinct 12-byte records of which few
+// are used took 3.38 ms a call.)
+//
+// A part names its groups likewise and lists their elements (record, name) in
+// the upper half of the bucket's slots of `uelems`; the last part to end has
+// the names of equal records led to one of them (merge_parts), and no pair is
+// written again. Where the records' hashes are too much alike for the table,
+// or the groups too many for the list, the bucket goes through
+// group_big_bucket.
+template <int K, bool MESH, int BLOCK, int DCAP, bool PART>
+__device__ __forceinline__ bool group_elements(const GroupArgs& a, const LargeBuckets& large,
+                                           GroupTable<K, BLOCK, DCAP>& t, int64_t b0, int64_t b1, int64_t q0,
+                                           int64_t q1, int64_t slot0, uint32_t* used_out) {
+  using T = GroupTable<K, BLOCK, DCAP>;
+  constexpr int S = K + 1, TB = T::TB, TS = T::TS;
+  constexpr int PER = (DCAP + BLOCK - 1) / BLOCK;
+  constexpr uint32_t kEmpty = 0xFFFFFFFFu, kUsedBit = 0x80000000u, kHard = 0x40000000u;
+  const int tid = threadIdx.x;
+  const uint32_t cnt = uint32_t(q1 - q0), last = cnt - 1u;
+  const uint32_t half = uint32_t(b1 - b0) / 2;  // slots of the list
+  uint32_t* const list = a.uelems + (b1 - half) * S;
+  const uint32_t* const elems = a.elems + q0 * S;
+  uint2* const pairs = a.pairs + q0;
+  uint32_t names = uint32_t(q0), used_all = 0;
+  bool hard = false;
+  for (uint32_t share = 0, shares = 1; share < shares;) {
+    for (int i = tid; i < TS; i += BLOCK) t.tab[i] = kEmpty;
+    for (int i = tid; i < DCAP; i += BLOCK) t.min[i] = kEmpty;
+    for (int i = tid; i < DCAP / 32; i += BLOCK) t.used[i] = 0;
+    if (tid == 0) t.n = t.full = 0;
+    __syncthreads();
+    uint32_t mine = kEmpty;  // a place of this thread's own in the list of records
+    uint32_t next[S];        // the record after the one in hand is on its way
+    load_words<S>(elems + min(uint32_t(tid), last) * S, next);
+    for (uint32_t q = tid; q < cnt; q += BLOCK) {
+      if (cnt > DCAP && __hip_atomic_load(&t.full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) break;
+      uint32_t e[S];
+#pragma unroll
+      for (int w = 0; w < S; ++w) e[w] = next[w];
+      load_words<S>(elems + min(q + BLOCK, last) * S, next);
+      const uint32_t h = hash_words<K>(e);
+      if (shares > 1 && hash_share(h, shares) != share) continue;
+      uint32_t sl = (h * 0x9E3779B1u) >> (32 - TB);
+      uint32_t at = kEmpty;
+      while (true) {
+        uint32_t cur = __hip_atomic_load(&t.tab[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (cur == kEmpty) {
+          if (mine == kEmpty) mine = atomicAdd(&t.n, 1u);
+          if (mine >= uint32_t(DCAP)) break;
+#pragma unroll
+          for (int w = 0; w < K; ++w) t.key[w * DCAP + mine] = e[w];
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+          cur = atomicCAS(&t.tab[sl], kEmpty, mine);
+          if (cur == kEmpty) {
+            at = mine;
+            mine = kEmpty;
+            break;
+          }
+        }
+        bool eq = true;
+#pragma unroll
+        for (int w = 0; w < K; ++w) eq = eq && t.key[w * DCAP + cur] == e[w];
+        if (eq) {
+          at = cur;
+          break;
+        }
+        sl = (sl + 1) & (TS - 1);
+      }
+      if (at == kEmpty) {
+        t.full = q + 1;
+        break;
+      }
+      const uint32_t id = e[K] & ~kUsedBit;
+      pairs[q] = make_uint2(names + at, id);
+      if (id < __hip_atomic_load(&t.min[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+        atomicMin(&t.min[at], id);
+      if ((e[K] & kUsedBit) && !(__hip_atomic_load(&t.used[at >> 5], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP) >> (at & 31) & 1u))
+        atomicOr(&t.used[at >> 5], 1u << (at & 31));
+    }
+    __syncthreads();
+    const uint32_t full = uniform(t.full);
+    if (full != 0) {
+      const uint32_t more = shares == 1 ? uniform(group_shares(full, cnt, float(DCAP))) : 2;
+      shares *= more;
+      share *= more;
+      hard = shares > kMostShares + kMostShares * (cnt / uint32_t(DCAP));
+      __syncthreads();
+      if (hard) break;
+      continue;
+    }
+    // slots of the used groups, of all of them for the list; places nobody
+    // published are skipped
+    uint32_t x[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int d = tid * PER + j;
+      x[j] = d >= DCAP || t.min[d] == kEmpty ? 0u : 1u | (t.used[d >> 5] >> (d & 31) & 1u) << 16;
+      sum += x[j];
+    }
+    uint32_t all;
+    uint32_t at = block_exclusive_scan<BLOCK>(sum, t.wave, &all);
+    uint32_t listed = 0;  // groups listed before these
+    if constexpr (PART) {
+      if (tid == 0) t.x[0] = atomicAdd(large.listed(b0), all & 0xFFFFu);
+      __syncthreads();
+      listed = uniform(t.x[0]);
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int d = tid * PER + j;
+      if (x[j] == 0) continue;
+      const bool used = x[j] >> 16;
+      const uint32_t name = names + uint32_t(d), rank = listed + (at & 0xFFFFu);
+      if (PART || used) a.rep[name] = t.min[d];
+      if (PART || !used) a.cmap[name] = used ? kUsedMark : -1;
+      if (PART ? rank < half : used) {
+        uint32_t e[S];
+#pragma unroll
+        for (int w = 0; w < K; ++w) e[w] = t.key[w * DCAP + d];
+        e[K] = name;
+        store_words<S>(PART ? list + int64_t(rank) * S : a.uelems + (slot0 + used_all + (at >> 16)) * S, e);
+      }
+      at += x[j];
+    }
+    used_all += uniform(all >> 16);
+    names += uniform(min(t.n, uint32_t(DCAP)));
+    if (++share < shares) __syncthreads();
+  }
+  if constexpr (PART) {
+    // whoever ends last has the groups of all parts in view
+    stores_in_l2();
+    __syncthreads();
+    if (tid == 0) {
+      if (hard) atomicOr(large.listed(b0), kHard);
+      __threadfence();  // for all of the workgroup's stores
+      t.x[0] = atomicAdd(large.listed(b0) - 1, 1u) + 1u;
+    }
+    __syncthreads();
+    const uint32_t parts = uint32_t(b1 - 1) / uint32_t(large.part) - uint32_t(b0) / uint32_t(large.part) + 1;
+    if (uniform(t.x[0]) != parts) return false;
+    __threadfence();
+    const uint32_t listed = uniform(lb_load(large.listed(b0)));
+    __syncthreads();  // t.x is used again
+    hard = listed > half;
+    if (!hard) used_all = merge_parts<K, BLOCK>(a, list, listed, b0, slot0, t.x);
+  }
+  if (hard) used_all = group_big_bucket<K, MESH, BLOCK>(a, b0, b1, slot0, t.x);
+  *used_out = used_all;
+  return true;
+}
+
+// The whole bucket is kept apart from the parts, whose listing in its loop
+// cost the other 3 us of 60 (5.2M 8-byte vertices).
+template <int K, bool MESH, int BLOCK, int DCAP>
+__device__ __forceinline__ bool group_span(const GroupArgs& a, const LargeBuckets& large,
+                                           GroupTable<K, BLOCK, DCAP>& t, int64_t b0, int64_t b1, int64_t q0,
+                                           int64_t q1, int64_t slot0, uint32_t* used) {
+  if (q1 - q0 < b1 - b0)
+    return group_elements<K, MESH, BLOCK, DCAP, true>(a, large, t, b0, b1, q0, q1, slot0, used);
+  return group_elements<K, MESH, BLOCK, DCAP, false>(a, large, t, b0, b1, b0, b1, slot0, used);
+}
+
+// Groups of one bucket, or of a part of one.
 template <int K, bool MESH, int BLOCK, int DCAP>
 __global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBucketArgs b) {
-  constexpr int S = K + 1;
-  constexpr int TB = DCAP > 3072 ? 13 : DCAP > 1536 ? 12 : DCAP > 768 ? 11 : 10, TS = 1 << TB;
-  static_assert(TS * 3 >= DCAP * 4, "table load");
-  constexpr int PER = (DCAP + BLOCK - 1) / BLOCK;
-  constexpr uint32_t kEmpty = 0xFFFFFFFFu, kUsedBit = 0x80000000u, kOpen = 0xFFFFFFFFu;
-  __shared__ uint32_t s_key[K * DCAP];     // distinct records, word-major
-  __shared__ uint32_t s_tab[TS];           // place in that list; later dense names
-  __shared__ uint32_t s_min[DCAP];         // smallest id
-  __shared__ uint32_t s_used[DCAP / 32];
-  __shared__ uint32_t s_wave[BLOCK / kWave];
-  __shared__ uint32_t s_n, s_full;
-  __shared__ uint32_t s_big[4];
+  __shared__ GroupTable<K, BLOCK, DCAP> s_table;
   const GroupArgs& a = b.g;
-  const int tid = threadIdx.x;
-  const int64_t f = blockIdx.x;
-  const int64_t b0 = b.starts[f], b1 = b.starts[f + 1];
-  uint32_t used_all = 0;
-  bool big = false;
-  if (b1 > b0) {
-    const uint32_t cnt = uint32_t(b1 - b0), last = cnt - 1u;
-    const uint32_t* const elems = a.elems + b0 * S;
-    uint2* const pairs = a.pairs + b0;
-    uint32_t names = uint32_t(b0);  // first name of the round
-    for (int round = 0;; ++round) {
-      for (int i = tid; i < TS; i += BLOCK) s_tab[i] = kEmpty;
-      for (int i = tid; i < DCAP; i += BLOCK) s_min[i] = kEmpty;
-      for (int i = tid; i < DCAP / 32; i += BLOCK) s_used[i] = 0;
-      if (tid == 0) s_n = s_full = 0;
-      __syncthreads();
-      uint32_t mine = kEmpty;  // a place of this thread's own in the list
-      // sweep 0 adds records; sweep 1, after the list has filled up, only looks
-      for (int sweep = 0; sweep < 2; ++sweep) {
-        bool open = false;
-        uint32_t next[S];  // the record after the one in hand is on its way
-        load_words<S>(elems + min(uint32_t(tid), last) * S, next);
-        for (uint32_t q = tid; q < cnt; q += BLOCK) {
-          uint32_t e[S];
-#pragma unroll
-          for (int w = 0; w < S; ++w) e[w] = next[w];
-          load_words<S>(elems + min(q + BLOCK, last) * S, next);
-          // found in an earlier round, or by this round's first sweep
-          if ((round > 0 || sweep > 0) && pairs[q].x != kOpen) continue;
-          const uint32_t v = e[K];
-          uint32_t sl = (hash_words<K>(e) * 0x9E3779B1u) >> (32 - TB);
-          uint32_t at = kOpen;
-          while (true) {
-            uint32_t cur = __hip_atomic_load(&s_tab[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (cur == kEmpty) {
-              if (sweep != 0) break;
-              if (mine == kEmpty) mine = atomicAdd(&s_n, 1u);
-              if (mine >= uint32_t(DCAP)) break;
-#pragma unroll
-              for (int w = 0; w < K; ++w) s_key[w * DCAP + mine] = e[w];
-              __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-              cur = atomicCAS(&s_tab[sl], kEmpty, mine);
-              if (cur == kEmpty) {
-                at = mine;
-                mine = kEmpty;
-                break;
-              }
-            }
-            bool eq = true;
-#pragma unroll
-            for (int w = 0; w < K; ++w) eq = eq && s_key[w * DCAP + cur] == e[w];
-            if (eq) {
-              at = cur;
-              break;
-            }
-            sl = (sl + 1) & (TS - 1);
-          }
-          const uint32_t id = v & ~kUsedBit;
-          pairs[q] = make_uint2(at == kOpen ? kOpen : names + at, id);
-          if (at == kOpen) {
-            open = true;
-            continue;
-          }
-          if (id < __hip_atomic_load(&s_min[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
-            atomicMin(&s_min[at], id);
-          if ((v & kUsedBit) && !(__hip_atomic_load(&s_used[at >> 5], __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP) >> (at & 31) & 1u))
-            atomicOr(&s_used[at >> 5], 1u << (at & 31));
-        }
-        if (open) s_full = 1;
-        __syncthreads();
-        if (s_full == 0) break;
-      }
-      const bool again = s_full != 0;
-      big = again && round == 0 && b1 - b0 > kGroupSlots;
-      if (big) break;  // nothing is kept but pairs, which are written again
-      const bool dense = again || round > 0;
-      const uint32_t places = min(s_n, uint32_t(DCAP));
-      // slots of the used groups, and dense names where there are several
-      // rounds; places nobody published are skipped
-      uint32_t x[PER], sum = 0;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int d = tid * PER + j;
-        x[j] = d >= DCAP || s_min[d] == kEmpty ? 0u : 1u | (s_used[d >> 5] >> (d & 31) & 1u) << 16;
-        sum += x[j];
-      }
-      uint32_t all;
-      uint32_t at = block_exclusive_scan<BLOCK>(sum, s_wave, &all);
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int d = tid * PER + j;
-        if (x[j] == 0) continue;
-        const uint32_t name = names + (dense ? at & 0xFFFFu : uint32_t(d));
-        s_tab[d] = name;
-        if (x[j] >> 16) {
-          uint32_t e[S];
-#pragma unroll
-          for (int w = 0; w < K; ++w) e[w] = s_key[w * DCAP + d];
-          e[K] = name;
-          store_words<S>(a.uelems + (b0 + used_all + (at >> 16)) * S, e);
-          a.rep[name] = s_min[d];
-        } else {
-          a.cmap[name] = -1;
-        }
-        at += x[j];
-      }
-      static_assert(TS >= DCAP, "names fit the table");
-      used_all += all >> 16;
-      if (!dense) break;
-      __syncthreads();
-      for (uint32_t q = tid; q < cnt; q += BLOCK) {
-        const uint32_t was = pairs[q].x - names;  // earlier rounds' names are smaller, open ones larger
-        if (was < places) pairs[q].x = s_tab[was];
-      }
-      names += all & 0xFFFFu;
-      if (!again) break;
-      __syncthreads();
+  const int64_t part = b.large.part;
+  int64_t f = blockIdx.x, q0 = 0;
+  if (f >= b.buckets) {
+    if (*b.large.any == 0) return;
+    q0 = (f - b.buckets + 1) * part;
+    int lo = 0, hi = b.buckets - 1;  // last bucket that starts at or before q0
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (int64_t(b.starts[mid]) <= q0) lo = mid; else hi = mid - 1;
     }
+    f = lo;
   }
-  if (big) used_all = group_big_bucket<K, MESH, BLOCK>(a, b0, b1, b0, s_big);
-  if (tid == 0) {
-    a.chunks[f] = make_uint2(uint32_t(b0), used_all);
-    if (used_all) atomicAdd(&a.range_sums[group_run_of(f, gridDim.x, a.ranges)], used_all);
+  const int64_t b0 = b.starts[f], b1 = b.starts[f + 1];
+  const bool large = b1 - b0 > 2 * part;
+  if (q0 > 0 && (!large || q0 == b0 || q0 >= b1)) return;  // nothing for a helper
+  if (q0 == 0) q0 = b0;
+  const int64_t q1 = large ? b.large.end(q0, b1) : b1;
+  uint32_t used = 0;
+  if (q1 > q0 && !group_span<K, MESH, BLOCK, DCAP>(a, b.large, s_table, b0, b1, q0, q1, b0, &used)) return;
+  if (threadIdx.x == 0) {
+    a.chunks[f] = make_uint2(uint32_t(b0), used);
+    if (used) atomicAdd(&a.range_sums[group_run_of(f, b.buckets, a.ranges)], used);
+  }
+}
+
+// Buckets that k_group left: few workgroups that take one after the other,
+// then the parts of large ones.
+constexpr int kOverGrid = 1024;
+template <int K, bool MESH>
+__global__ __launch_bounds__(kGroupBlock, K <= 9 ? 8 : 4) void k_group_over(GroupArgs a, LargeBuckets large,
+                                                                            int64_t tiles) {
+  constexpr int DCAP = BucketShape<K>::DCAP;
+  __shared__ GroupTable<K, kGroupBlock, DCAP> s_table;
+  const int64_t part = large.part;
+  const uint32_t count = uniform(*a.over_count);
+  const bool any = uniform(*a.over_any) != 0;
+  uint32_t i = blockIdx.x;
+  for (bool helper = false; !helper;) {
+    uint32_t tile;
+    if (i < count) {
+      tile = uniform(a.over_list[i]);
+      i += gridDim.x;
+    } else {
+      helper = true;
+      if (!any || int(blockIdx.x) >= large.helpers) return;
+      tile = uniform(a.over_at[blockIdx.x + 1]);
+      if (tile == 0) return;
+      --tile;
+    }
+    const int64_t b0 = uniform(a.over[tile].x), b1 = uniform(a.over[tile].y), q0 = helper ? int64_t(blockIdx.x + 1) * part : b0;
+    const int64_t q1 = b1 - b0 > 2 * part ? large.end(q0, b1) : b1;
+    const uint32_t c = uniform(a.chunks[tile].y), slot0 = uniform(a.chunks[tile].x) + c;
+    uint32_t used = 0;
+    if (group_span<K, MESH, kGroupBlock, DCAP>(a, large, s_table, b0, b1, q0, q1, slot0, &used) &&
+        threadIdx.x == 0) {
+      a.chunks[tile].y = c + used;
+      if (used) atomicAdd(&a.range_sums[group_run_of(tile, tiles, a.ranges)], used);
+    }
+    __syncthreads();
   }
 }
 

@@ -30,6 +30,9 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   return v;
 }
 
+// A value that is the same in every lane, where the compiler cannot see it.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Exclusive scan over all threads of a block (BLOCK threads, BLOCK % 64 == 0).
 // `s_wave` must hold BLOCK/64 words of LDS. Returns the exclusive prefix and
 // the block total in *total. Contains __syncthreads().
@@ -322,6 +325,24 @@ __device__ __forceinline__ uint32_t lookback_exclusive(const uint64_t* base, int
     }
   }
   return excl;
+}
+
+// ---------------------------------------------------------------- group names
+//
+// Names of one record that the parts of a large bucket gave it: cmap leads
+// from all but one of them to that one, as a value below -1 (which no unused
+// group has after hash grouping). A used group may be marked in cmap until
+// its new id is known.
+constexpr int32_t kUsedMark = INT32_MIN;
+__device__ __forceinline__ int32_t lead_name(uint32_t name) { return -2 - int32_t(name); }
+__device__ __forceinline__ uint32_t led_name(int32_t c) { return uint32_t(-2) - uint32_t(c); }
+
+// Every store of this wave so far has reached the die's L2, ordered before
+// what follows for the threads of the workgroup (a fence for the whole device
+// would write the L2's dirty lines back, 15 us and more).
+__device__ __forceinline__ void stores_in_l2() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
 }
 
 // Tile of this workgroup in a launch whose tiles wait on their predecessors

@@ -29,8 +29,8 @@
 // lies in that range (the name tells the group's mesh).
 //
 // A bucket that does not fit the LDS window (many copies of one value, or an
-// unlucky hash) is grouped by the same workgroup through a table of chains in
-// global memory (group_big_bucket), whatever its size.
+// unlucky hash) is left to k_group_over (bucket_kernels.hpp), which groups it
+// by a hash table as those of the one partition pass.
 #pragma once
 
 #include "device_common.hpp"
@@ -83,6 +83,14 @@ struct GroupArgs {
   const int32_t* mesh_tab;
   const uint2* mesh_buckets;  // each mesh's hash buckets (mesh_bucket)
   int32_t nmesh;
+  // k_group: buckets that run past their chunk's window, left to
+  // k_group_over: [chunks] (first position, end), and the chunks that have one
+  uint2* over;
+  uint32_t* over_list;
+  uint32_t* over_count;    // zeroed
+  int32_t part;            // of a larger one than two parts the chunk (+ 1), by multiples of `part` inside it
+  uint32_t* over_any;      // zeroed; set where there is a larger one
+  uint32_t* over_at;       // zeroed
 };
 
 // Runs of consecutive chunks, one per workgroup of k_group_compact_hist: few
@@ -131,17 +139,16 @@ constexpr int group_min_waves() {
 }
 
 // End of the bucket that starts at position b0 (of the last one of a chunk of
-// k_group that runs past its window): the first position after it whose
-// element hashes elsewhere.
+// k_group that runs past its window): the elements are in bucket order, so
+// every step takes BLOCK probes between the last position known to be in the
+// bucket and the first known not to be, three for 10M copies (a walk over
+// them took 10 ms).
 template <int K, bool MESH, int BLOCK>
 __device__ int64_t end_of_bucket(const GroupArgs& a, int64_t b0, uint32_t* s_x) {
   constexpr int S = K + 1;
-  constexpr int U = 4;  // elements in flight per thread
-  constexpr uint32_t kNone = 0xFFFFFFFFu;
   const int tid = threadIdx.x;
   uint32_t mesh = 0;
   if constexpr (MESH) mesh = mesh_of(a.mesh_off, a.nmesh, b0, a.mesh_tab);
-  const int64_t lim = MESH ? min(a.n, a.mesh_off[mesh + 1]) : a.n;  // buckets belong to meshes
   auto bucket_at = [&](int64_t p) {
     uint32_t e[S];
     load_words<S>(a.elems + p * S, e);
@@ -149,48 +156,78 @@ __device__ int64_t end_of_bucket(const GroupArgs& a, int64_t b0, uint32_t* s_x) 
     else return hash_words<K>(e) & a.bucket_mask;
   };
   const uint32_t bucket = bucket_at(b0);
-  if (tid == 0) s_x[0] = kNone;
-  __syncthreads();
-  for (int64_t base = b0 + 1; base < lim; base += BLOCK * U) {
-    uint32_t first = kNone;
-#pragma unroll
-    for (int r = 0; r < U; ++r) {
-      const int64_t p = base + r * BLOCK + tid;
-      if (p < lim && bucket_at(p) != bucket) first = min(first, uint32_t(p));
+  int64_t in = b0, out = MESH ? min(a.n, a.mesh_off[mesh + 1]) : a.n;  // buckets belong to meshes
+  while (out - in > 1) {
+    const int64_t step = (out - in + BLOCK) / (BLOCK + 1);
+    if (tid == 0) {
+      s_x[0] = uint32_t(in);
+      s_x[1] = uint32_t(out);
     }
-    if (first != kNone) atomicMin(&s_x[0], first);
     __syncthreads();
-    const uint32_t end = s_x[0];
+    const int64_t p = in + (tid + 1) * step;
+    if (p < out) {
+      if (bucket_at(p) == bucket) atomicMax(&s_x[0], uint32_t(p));
+      else atomicMin(&s_x[1], uint32_t(p));
+    }
     __syncthreads();
-    if (end != kNone) return end;
+    in = s_x[0];
+    out = max(int64_t(s_x[1]), in + 1);
+    __syncthreads();
   }
-  return lim;
+  return out;
 }
 
-// Groups one bucket of any size, [b0, b1). The distinct records of the bucket hang
-// in chains off a table in `uelems`, of which the bucket's positions own two
-// words each (head of a chain, next of a node) until its elements are written
-// there; a node is the position of some copy and names its group. The record
+// Node of record e (element i of `recs`) among chains that hang off a table in
+// memory, of which every element owns two words, [i * S] the head of chain i
+// and [i * S + 1] the next of node i: the node that holds an equal record, or
+// i itself, after `publish`. Everything the workgroup's waves tell each other
+// through memory goes by agent-scope atomics (L2), in order. Chains
+// are only ever prepended to, so a failed insertion re-reads what was added
+// and retries.
+template <int K, class Publish>
+__device__ __forceinline__ uint32_t chain_node(uint32_t* table, const uint32_t* recs, uint32_t heads, uint32_t i,
+                                               const uint32_t (&e)[K + 1], Publish publish) {
+  constexpr int S = K + 1;
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
+  uint32_t* const head = table + int64_t(__umulhi(hash_words<K>(e) * 0x9E3779B1u, heads)) * S;
+  uint32_t seen = kNone;  // nodes from here on are known not to match
+  uint32_t cur = lb_load(head);
+  while (true) {
+    for (uint32_t q = cur; q != seen && q != kNone; q = lb_load(table + int64_t(q) * S + 1)) {
+      bool eq = true;
+#pragma unroll
+      for (int w = 0; w < K; ++w) eq = eq && recs[int64_t(q) * S + w] == e[w];
+      if (eq) return q;
+    }
+    seen = cur;
+    lb_store(table + int64_t(i) * S + 1, cur);
+    publish();
+    stores_in_l2();  // one workgroup builds the chains
+    const uint32_t was = atomicCAS(head, cur, i);
+    if (was == cur) return i;
+    cur = was;
+  }
+}
+
+// Groups one bucket of any size, [b0, b1), through chains whose table lies in
+// the bucket's slots of `uelems` until its elements are written there; a node
+// is the position of some copy and names its group. The record
 // at b0 is the likeliest one to have thousands of copies: its copies are told
-// by a comparison in registers and touch no table. Everything the
-// workgroup's waves tell each other through memory goes by agent-scope
-// atomics (L2), ordered by fences. Chains are only ever prepended to, so a
-// failed insertion re-reads what was added and retries. Bound: the round trips
+// by a comparison in registers and touch no table. Bound: the round trips
 // of one workgroup's atomics, some 30 elements a microsecond where copies of
-// several values meet; k_group_bucket comes here only when LDS rounds would
-// take longer. Returns
+// several values meet; only buckets whose records group_span cannot cut by
+// their hash come here. Returns
 // the number of used groups; their elements start at slot `upre`.
 template <int K, bool MESH, int BLOCK>
 __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t b1, int64_t upre, uint32_t* s_x) {
   constexpr int S = K + 1;
-  constexpr int U = 4;  // elements in flight per thread
+  constexpr int U = S <= 5 ? 4 : 2;  // elements in flight per thread
   constexpr uint32_t kNone = 0xFFFFFFFFu, kUsedBit = 0x80000000u;
-  constexpr int32_t kUsedMark = -2;
   const int tid = threadIdx.x;
   uint32_t hot[S];
   load_words<S>(a.elems + b0 * S, hot);
   const uint32_t cnt = uint32_t(b1 - b0);
-  uint32_t* const table = a.uelems + b0 * S;  // head of chain h: [h * S], next of node b0 + i: [i * S + 1]
+  uint32_t* const table = a.uelems + b0 * S;
   for (uint32_t i = tid; i < cnt; i += BLOCK) lb_store(table + int64_t(i) * S, kNone);
   if (tid == 0) {
     lb_store(reinterpret_cast<uint32_t*>(a.cmap) + b0, uint32_t(-1));
@@ -198,7 +235,7 @@ __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t b1,
     s_x[2] = hot[K] & 0x7FFFFFFFu;   // its smallest id
     s_x[3] = 0;                      // used groups
   }
-  __threadfence();
+  stores_in_l2();
   __syncthreads();
   uint32_t* const rep = a.rep;
   uint32_t* const cm = reinterpret_cast<uint32_t*>(a.cmap);
@@ -223,43 +260,22 @@ __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t b1,
         if ((e[r][K] & kUsedBit) && s_x[1] == 0u) s_x[1] = 1u;
         if (id < s_x[2]) atomicMin(&s_x[2], id);
       } else {
-        const uint32_t h = __umulhi(hash_words<K>(e[r]) * 0x9E3779B1u, cnt);
-        uint32_t* const head = table + int64_t(h) * S;
-        uint32_t seen = kNone;  // nodes from here on are known not to match
-        uint32_t cur = lb_load(head);
-        node = kNone;
-        while (node == kNone) {
-          for (uint32_t q = cur; q != seen && q != kNone; q = lb_load(table + (int64_t(q) - b0) * S + 1)) {
-            bool eq = true;
-#pragma unroll
-            for (int w = 0; w < K; ++w) eq = eq && a.elems[int64_t(q) * S + w] == e[r][w];
-            if (eq) {
-              node = q;
-              break;
-            }
-          }
-          if (node != kNone) break;
-          seen = cur;
-          lb_store(table + (p - b0) * S + 1, cur);
+        node += chain_node<K>(table, a.elems + b0 * S, cnt, uint32_t(p - b0), e[r], [&] {
           lb_store(rep + p, id);
           lb_store(cm + p, uint32_t(-1));
-          __threadfence();
-          const uint32_t was = atomicCAS(head, cur, uint32_t(p));
-          if (was == cur) node = uint32_t(p);
-          else cur = was;
-        }
+        });
         if (lb_load(rep + node) > id) atomicMin(rep + node, id);
         if ((e[r][K] & kUsedBit) && lb_load(cm + node) != uint32_t(kUsedMark)) lb_store(cm + node, uint32_t(kUsedMark));
       }
       a.pairs[p] = make_uint2(node, id);
     }
   }
-  __threadfence();
+  stores_in_l2();
   __syncthreads();
   if (tid == 0) {
     lb_store(rep + b0, s_x[2]);
     if (s_x[1]) lb_store(cm + b0, uint32_t(kUsedMark));
-    __threadfence();
+    stores_in_l2();
   }
   __syncthreads();
   // ---- one element per used group (the table is no longer needed)
@@ -270,6 +286,46 @@ __device__ uint32_t group_big_bucket(const GroupArgs& a, int64_t b0, int64_t b1,
     load_words<S>(a.elems + p * S, e);
     e[K] = uint32_t(p);
     store_words<S>(a.uelems + u * S, e);
+  }
+  __syncthreads();
+  return s_x[3];
+}
+
+// Merges the `listed` groups (record, name) of a large bucket's parts: of the
+// names of one record one stays, with the smallest of their ids and the used
+// mark if any is used, and cmap leads from the others to it. The chains'
+// table lies in the bucket's elements, whose parts are all done. The elements
+// of the used groups, whose number is returned, go to slots from `upre` on,
+// at most to half of the bucket's, below the list.
+template <int K, int BLOCK>
+__device__ uint32_t merge_parts(const GroupArgs& a, const uint32_t* list, uint32_t listed, int64_t b0, int64_t upre,
+                                uint32_t* s_x) {
+  constexpr int S = K + 1;
+  const int tid = threadIdx.x;
+  uint32_t* const table = const_cast<uint32_t*>(a.elems) + b0 * S;
+  uint32_t* const rep = a.rep;
+  uint32_t* const cm = reinterpret_cast<uint32_t*>(a.cmap);
+  for (uint32_t j = tid; j < listed; j += BLOCK) lb_store(table + int64_t(j) * S, 0xFFFFFFFFu);
+  if (tid == 0) s_x[3] = 0;
+  stores_in_l2();
+  __syncthreads();
+  for (uint32_t j = tid; j < listed; j += BLOCK) {
+    uint32_t e[S];
+    load_words<S>(list + int64_t(j) * S, e);
+    const uint32_t node = chain_node<K>(table, list, listed, j, e, [] {});
+    if (node == j) continue;
+    const uint32_t name = list[int64_t(node) * S + K], id = lb_load(rep + e[K]);
+    if (lb_load(rep + name) > id) atomicMin(rep + name, id);
+    if (lb_load(cm + e[K]) == uint32_t(kUsedMark)) lb_store(cm + name, uint32_t(kUsedMark));
+    lb_store(cm + e[K], uint32_t(lead_name(name)));
+  }
+  stores_in_l2();
+  __syncthreads();
+  for (uint32_t j = tid; j < listed; j += BLOCK) {
+    uint32_t e[S];
+    load_words<S>(list + int64_t(j) * S, e);
+    if (lb_load(cm + e[K]) != uint32_t(kUsedMark)) continue;
+    store_words<S>(a.uelems + (upre + atomicAdd(&s_x[3], 1u)) * S, e);
   }
   __syncthreads();
   return s_x[3];
@@ -293,7 +349,7 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
   __shared__ uint32_t s_scratch[kScratch];  // buckets of the window, then the table
   __shared__ uint32_t s_cnt[2][IPT][WAVES];
   __shared__ uint32_t s_sq, s_eq, s_lq;
-  __shared__ uint32_t s_big[4];
+  __shared__ uint32_t s_big[2];
 
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int64_t n = a.n;
@@ -376,7 +432,7 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
   __syncthreads();
   const int sq = int(s_sq);
   const bool active = sq < qc1;
-  // the chunk's last bucket runs past the window: it is grouped by itself below
+  // the chunk's last bucket runs past the window: it is left to k_group_over
   const bool over = active && int(s_eq) >= WIN;
   const int eq = over ? int(s_lq) : int(s_eq);
   for (int i = tid; i < TS; i += BLOCK) s_scratch[i] = kEmpty;  // buckets are no longer needed
@@ -497,11 +553,17 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
       a.cmap[g] = -1;
     }
   }
-  uint32_t u_own = active ? ut : 0u;
+  const uint32_t u_own = active ? ut : 0u;
   if (over) {
-    const int64_t big = c0 - 1 + int(s_lq);
-    const int64_t big_end = end_of_bucket<K, MESH, BLOCK>(a, big, s_big);
-    u_own += group_big_bucket<K, MESH, BLOCK>(a, big, big_end, int64_t(upre) + ut, s_big);
+    const int64_t b0 = c0 - 1 + int(s_lq), b1 = end_of_bucket<K, MESH, BLOCK>(a, b0, s_big);
+    const bool large = b1 - b0 > 2 * int64_t(a.part);
+    if (tid == 0) {
+      a.over[tile] = make_uint2(uint32_t(b0), uint32_t(b1));
+      a.over_list[atomicAdd(a.over_count, 1u)] = tile;
+      if (large) *a.over_any = 1;
+    }
+    if (large)
+      for (int64_t w = b0 / a.part + 1 + tid; w * a.part < b1; w += BLOCK) a.over_at[w] = tile + 1;
   }
   // ---- the chunk's record and its share of its run's sum
   if (tid == 0) {

@@ -23,7 +23,7 @@ __host__ __device__ inline uint32_t cut_offset(const int64_t* off, int64_t b, in
 // bring the vertices per bucket down to `target`; for passes by hash digits
 // (mesh_bucket) the smallest power of two that does.
 __host__ __device__ inline uint32_t mesh_bucket_count(uint32_t nb, int32_t target, bool digits) {
-  if (!digits) return uint32_t((int64_t(nb) + target - 1) / target);
+  if (!digits) return (nb + uint32_t(target) - 1u) / uint32_t(target);  // nb < 2^30
   int k = 0;
   while (k < 30 && int64_t(nb >> k) > target) ++k;
   return 1u << k;
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kMeshBucketBlock) void k_mesh_buckets(const int64_t
                                                                    int64_t n, int32_t target,
                                                                    int64_t* __restrict__ ordered,
                                                                    uint2* __restrict__ mb) {
-  constexpr int WAVES = kMeshBucketBlock / kWave, PER = 8;
+  constexpr int WAVES = kMeshBucketBlock / kWave, PER = 6;
   __shared__ uint32_t s_wave[WAVES];
   const int lane = lane_id(), wave = threadIdx.x / kWave;
   uint32_t buckets = 0, reached = 0;  // of the meshes before this round's

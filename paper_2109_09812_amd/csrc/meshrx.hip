@@ -376,7 +376,8 @@ Layout make_layout(int64_t n, int64_t num_idx, int K, int32_t nmesh, const SortV
     L.hist_hash = off; off = align_up(off + sizeof(uint32_t) * size_t(L.P_hash) * size_t(v.radix()));
     L.plan_hash = off; off = align_up(off + sizeof(uint32_t) * size_t(2 * L.P_hash + 1));
     L.dead_hash = off; off = align_up(off + sizeof(uint32_t) * size_t(L.P_hash));
-    L.group_chunks = off; off = align_up(off + sizeof(uint32_t) * 4 * size_t(L.tiles_group));
+    // a record of each chunk and the bucket it left to k_group_over
+    L.group_chunks = off; off = align_up(off + sizeof(uint2) * 2 * size_t(L.tiles_group));
     L.group_ranges = off; off = align_up(off + sizeof(uint32_t) * 3 * size_t(group_compact_ranges(L.tiles_group)));
   }
   // last, so that a call whose Step 1 writes every flag (by bands) can leave
@@ -691,6 +692,20 @@ struct BucketState {
   int64_t ranges = 0;
 };
 
+// What the grouping of large buckets keeps in the zeroed flags of the sort of
+// all vertices (n bytes, at least 256, which hash grouping leaves alone): a
+// word that says whether there are any, two words of state per part and, on
+// the digit path, one more and the list of the chunks that left a bucket.
+LargeBuckets large_buckets(int64_t n, uint32_t* words, GroupArgs* g) {
+  const LargeBuckets l{large_part(n), large_helpers(n), words, words + 2};
+  g->part = l.part;
+  g->over_any = words;
+  g->over_count = words + 1;
+  g->over_at = l.state + 2 * (l.helpers + 1);
+  g->over_list = g->over_at + l.helpers + 1;
+  return l;
+}
+
 BucketState bucket_state(const SortVariant& v, Layout L, int64_t n, int K, int32_t nmesh, uint32_t* lookback,
                          uint32_t* matrix) {
   BucketState b;
@@ -720,8 +735,10 @@ BucketState bucket_state(const SortVariant& v, Layout L, int64_t n, int K, int32
 }
 
 // Elements into their buckets (in args.elems) and the buckets grouped.
-void group_buckets(const BucketState& b, const BucketGroup& g, const MarkArgs* mark, const BandArgs* band,
-                   GroupArgs ga, hipStream_t s) {
+void group_buckets(BucketState& b, const BucketGroup& g, const MarkArgs* mark, const BandArgs* band, GroupArgs ga,
+                   const LargeBuckets& large, hipStream_t s) {
+  b.args.most = 2 * uint32_t(large.part);
+  b.args.large = ga.over_any;
   prof_mark(mark || band ? "mark_bucket_count" : "bucket_count", s);
   g.count(b.args, mark, band, s);
   prof_mark("bucket_offsets", s);
@@ -736,7 +753,7 @@ void group_buckets(const BucketState& b, const BucketGroup& g, const MarkArgs* m
   ga.chunks = b.chunks;
   ga.range_sums = b.range_sums;
   ga.ranges = b.ranges;
-  const GroupBucketArgs a{ga, b.args.starts, b.args.buckets, b.plan.target};
+  const GroupBucketArgs a{ga, b.args.starts, b.args.buckets, b.plan.target, large};
   prof_mark("group", s);
   g.group(a, s);
 }
@@ -850,6 +867,7 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
     g.cmap = cmap;
     g.uelems = buf[2];
     g.status = status;
+    const LargeBuckets large = large_buckets(n, reinterpret_cast<uint32_t*>(ws + L.used_g), &g);
     if (bucketed) {
       bs.args.vtx = static_cast<const uint32_t*>(vtx);
       bs.args.used = used_v;
@@ -857,7 +875,7 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
       g.pairs = reinterpret_cast<uint2*>(Y);
       group_chunks = bs.chunks;
       group_range_sums = bs.range_sums;
-      group_buckets(bs, v.bucket, scatter_mark ? &mark : nullptr, band_mark ? &ba : nullptr, g, s);
+      group_buckets(bs, v.bucket, scatter_mark ? &mark : nullptr, band_mark ? &ba : nullptr, g, large, s);
     } else {
       // stable sort by the hash digits; every hash pass runs (dead flags go to
       // a word nobody reads), so the elements end in X = buf[(ph - 1) & 1]
@@ -892,8 +910,11 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
       g.chunks = group_chunks;
       g.range_sums = group_range_sums;
       g.ranges = group_ranges;
+      g.over = group_chunks + L.tiles_group;
       prof_mark("group", s);
       v.group(g, L.tiles_group, s);
+      prof_mark("group_over", s);
+      v.group_over(g, large, L.tiles_group, s);
     }
     uint2* pairs = reinterpret_cast<uint2*>(Y);
     OrderArgs o{};
@@ -921,8 +942,8 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
       // of the index entries
       const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
                             reinterpret_cast<uint2*>(X), ptable, status,
-                            reinterpret_cast<const uint32_t*>(rep), new2old, SortBuffers{}, 0, nullptr,
-                            nullptr, nullptr, 0};
+                            reinterpret_cast<const uint32_t*>(rep), new2old, g.over_any, SortBuffers{}, 0,
+                            nullptr, nullptr, nullptr, 0};
       prof_mark("pair_partition", s);
       launch_pair_partition(pa, bp.fine, s);
       const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,
@@ -1264,6 +1285,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   g.mesh_tab = vtab;
   g.mesh_buckets = mbk;
   g.nmesh = num_meshes;
+  const LargeBuckets large = large_buckets(n, reinterpret_cast<uint32_t*>(ws + L.used_g), &g);
   if (bucketed) {
     bs.args.vtx = static_cast<const uint32_t*>(vtx);
     bs.args.used = used_v;
@@ -1275,7 +1297,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
     g.pairs = reinterpret_cast<uint2*>(Y);
     group_chunks = bs.chunks;
     group_range_sums = bs.range_sums;
-    group_buckets(bs, v.bucket_mesh, scatter_mark ? &mark : nullptr, bands ? &ba : nullptr, g, s);
+    group_buckets(bs, v.bucket_mesh, scatter_mark ? &mark : nullptr, bands ? &ba : nullptr, g, large, s);
   } else {
     if (bands) {
       prof_mark("band_mark", s);
@@ -1318,8 +1340,11 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
     g.chunks = group_chunks;
     g.range_sums = group_range_sums;
     g.ranges = group_ranges;
+    g.over = group_chunks + L.tiles_group;
     prof_mark("group", s);
     v.group_mesh(g, L.tiles_group, s);
+    prof_mark("group_over", s);
+    v.group_over_mesh(g, large, L.tiles_group, s);
   }
   uint2* pairs = reinterpret_cast<uint2*>(Y);
 
@@ -1350,8 +1375,8 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   if (bands) {
     const PairPartArgs pa{static_cast<const uint2*>(pairs), cmap, n, bp.shift, bp.nb, bp.ptiles,
                           reinterpret_cast<uint2*>(X), ptable, status,
-                          reinterpret_cast<const uint32_t*>(rep), new2old, SortBuffers{}, 0, vtx_offsets,
-                          out_vtx_offsets, vtab, num_meshes};
+                          reinterpret_cast<const uint32_t*>(rep), new2old, g.over_any, SortBuffers{}, 0,
+                          vtx_offsets, out_vtx_offsets, vtab, num_meshes};
     prof_mark("pair_partition", s);
     launch_pair_partition(pa, true, s);
     const BandMapArgs ma{reinterpret_cast<const uint2*>(X), ptable, bp.ptiles, ipart, itable, bp.itiles, n,

@@ -102,6 +102,8 @@ struct SortVariant {
   void (*band_mark_hash_hist)(const BandArgs& ba, const uint32_t* vtx, int64_t n, int ph, uint32_t* hist,
                               hipStream_t) = nullptr;
   void (*group)(const GroupArgs&, int64_t grid, hipStream_t) = nullptr;
+  // the buckets that it left, by `large`
+  void (*group_over)(const GroupArgs&, const LargeBuckets&, int64_t chunks, hipStream_t) = nullptr;
   // dense copy of the used groups' elements + their key-digit histograms
   // (for the LSD key sort)
   void (*group_compact_hist)(const GroupCompactArgs&, hipStream_t) = nullptr;
@@ -124,6 +126,7 @@ struct SortVariant {
                          const int32_t* tab, const uint2* mesh_buckets, int ph, uint32_t* hist,
                          hipStream_t) = nullptr;
   void (*group_mesh)(const GroupArgs&, int64_t grid, hipStream_t) = nullptr;
+  void (*group_over_mesh)(const GroupArgs&, const LargeBuckets&, int64_t chunks, hipStream_t) = nullptr;
   int group_mesh_chunk = 0;
   int group_mesh_target_bucket = 0;
 

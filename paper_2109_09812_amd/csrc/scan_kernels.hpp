@@ -306,8 +306,9 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
 // [vtx_off[b], vtx_off[b+1]) (sorted by (mesh id, record), or hash-ordered
 // with per-mesh bucket ranges), so the mesh of an element is that of its
 // position: one lookup for a tile inside one mesh. `new2old` (nullable, after
-// hash grouping) receives the representatives `rep`, given by group name, at
-// their groups' new ids: the pair that holds one is found by comparison.
+// hash grouping) receives the representatives `rep` (null after sort-all),
+// given by group name, at their groups' new ids: the pair that holds one is
+// found by comparison.
 template <bool BATCHED, int kItems>
 __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs, const uint2* pairs_in,
                                                                 const int32_t* __restrict__ cmap, int64_t n,
@@ -360,6 +361,11 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
     const int64_t off = int64_t(p[it].x) - int64_t(g0);
     if (int64_t(p[it].x) >= n) c[it] = -1;
     else c[it] = (off >= 0 && off < span) ? s_stage[off] : cmap[p[it].x];  // outside: only after a failed wait
+    if (rep && c[it] < -1 && int64_t(p[it].x) < n) {
+      // a name that leads to another of its group (of a large hash bucket)
+      p[it].x = led_name(c[it]);
+      c[it] = int64_t(p[it].x) < n ? cmap[p[it].x] : -1;
+    }
   }
   // which pairs hold their group's representative: staged in the same LDS where
   // many groups of the tile are used (with room for both, half as many

@@ -220,6 +220,12 @@ void launch_group_mesh(const GroupArgs& a, int64_t grid, hipStream_t s) {
   if (grid > 0) hipLaunchKernelGGL((k_group<K, true>), dim3(grid), dim3(GroupShape<K + 1>::BLOCK), 0, s, a);
 }
 
+template <bool MESH>
+void launch_group_over(const GroupArgs& a, const LargeBuckets& large, int64_t chunks, hipStream_t s) {
+  hipLaunchKernelGGL((k_group_over<K, MESH>), dim3(std::max<int64_t>(large.helpers, std::min<int64_t>(chunks, kOverGrid))),
+                     dim3(kGroupBlock), 0, s, a, large, chunks);
+}
+
 // The sample sort of the used groups, grids sized for n of them.
 template <bool MESH>
 SplitSort make_split() {
@@ -343,11 +349,11 @@ BucketGroup make_bucket() {
   g.group = [](const GroupBucketArgs& a, hipStream_t s) {
     using SH = BucketShape<K>;
     if (a.target <= SH::DCAP_SMALL * 4 / 5)
-      hipLaunchKernelGGL((k_group_bucket<K, MESH, kGroupBlockSmall, SH::DCAP_SMALL>), dim3(a.buckets),
-                         dim3(kGroupBlockSmall), 0, s, a);
+      hipLaunchKernelGGL((k_group_bucket<K, MESH, kGroupBlockSmall, SH::DCAP_SMALL>),
+                         dim3(a.buckets + a.large.helpers), dim3(kGroupBlockSmall), 0, s, a);
     else
-      hipLaunchKernelGGL((k_group_bucket<K, MESH, kGroupBlock, SH::DCAP>), dim3(a.buckets), dim3(kGroupBlock), 0, s,
-                         a);
+      hipLaunchKernelGGL((k_group_bucket<K, MESH, kGroupBlock, SH::DCAP>), dim3(a.buckets + a.large.helpers),
+                         dim3(kGroupBlock), 0, s, a);
   };
   return g;
 }
@@ -373,6 +379,7 @@ SortVariant make() {
   v.hash_hist = &launch_hash_hist<D>;
   v.band_mark_hash_hist = &launch_band_mark_hash_hist<D>;
   v.group = &launch_group;
+  v.group_over = &launch_group_over<false>;
   v.group_compact_hist = &launch_group_compact_hist<D>;
   v.finalize = &launch_finalize;
   v.group_chunk = GroupShape<K>::CHUNK;
@@ -386,6 +393,7 @@ SortVariant make() {
   v.split = make_split<false>();
   v.split_mesh = make_split<true>();
   v.group_mesh = &launch_group_mesh;
+  v.group_over_mesh = &launch_group_over<true>;
   v.group_mesh_chunk = GroupShape<K + 1>::CHUNK;
   v.group_mesh_target_bucket = GroupShape<K + 1>::TARGET_BUCKET;
   return v;

@@ -1,0 +1,276 @@
+"""GPU parity of hash buckets that do not fit one round of their workgroup's
+table, against the oracle: more distinct records than the list holds (shares),
+records of one hash, a value with so many copies that several workgroups group
+its bucket in parts, and the same on the digit path, where k_group leaves such
+buckets to k_group_over. The kernels that ran are read from the profile."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+HASH, SORT_ALL = 8, 4
+U32 = np.uint32
+
+
+def _say(*a):
+    print("[case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+def _rotl(x, r):
+    return (x << U32(r)) | (x >> U32(32 - r))
+
+
+def _mixed(w):
+    return _rotl(w * U32(0xCC9E2D51), 15) * U32(0x1B873593)
+
+
+def record_hash(v):
+    """The record hash (MurmurHash3 x86_32 of the words)."""
+    with np.errstate(over="ignore"):
+        h = np.full(v.shape[0], 0x21090981, U32)
+        for w in range(v.shape[1]):
+            h = _rotl(h ^ _mixed(v[:, w]), 13) * U32(5) + U32(0xE6546B64)
+        h ^= U32(4 * v.shape[1])
+        h ^= h >> U32(16)
+        h *= U32(0x85EBCA6B)
+        h ^= h >> U32(13)
+        h *= U32(0xC2B2AE35)
+        h ^= h >> U32(16)
+    return h
+
+
+def _inverse(a):
+    return U32(pow(int(a), -1, 1 << 32))
+
+
+def records_of_hash(rng, u, k, h):
+    """u distinct records of k >= 2 words whose hash is h (an array or one
+    value): random words, and the last one solved for."""
+    v = rng.integers(0, 2**32, size=(u, k), dtype=np.uint64).astype(U32)
+    v[:, 0] = rng.permutation(u).astype(U32)
+    with np.errstate(over="ignore"):
+        x = np.broadcast_to(np.asarray(h, U32), (u,)).copy()
+        x ^= x >> U32(16)
+        x *= _inverse(0xC2B2AE35)
+        x = x ^ (x >> U32(13)) ^ (x >> U32(26))
+        x *= _inverse(0x85EBCA6B)
+        x ^= x >> U32(16)
+        x ^= U32(4 * k)
+        x = _rotl((x - U32(0xE6546B64)) * _inverse(5), 19)
+        s = np.full(u, 0x21090981, U32)
+        for w in range(k - 1):
+            s = _rotl(s ^ _mixed(v[:, w]), 13) * U32(5) + U32(0xE6546B64)
+        v[:, k - 1] = _rotl((x ^ s) * _inverse(0x1B873593), 17) * _inverse(0xCC9E2D51)
+    assert np.array_equal(record_hash(v), np.broadcast_to(np.asarray(h, U32), (u,)))
+    return v
+
+
+def dev(a):
+    a = np.ascontiguousarray(a)
+    return torch.from_numpy(a.view(np.int32) if a.dtype == U32 else a).to(DEV)
+
+
+def ran(mrx, call):
+    mrx._lib.profile_enable(True)
+    r = call()
+    mrx._lib.profile_enable(False)
+    return r, {name for name, _ in mrx._lib.profile_records()}
+
+
+def check(vtx, idx, name, kernel=None):
+    import paper_2109_09812_amd as mrx
+    _say(name, vtx.shape, idx.shape)
+    r, kernels = ran(mrx, lambda: mrx.reindex_mesh(dev(vtx), dev(idx), tuning=(0, 0, 0, HASH)))
+    assert kernel is None or kernel in kernels, (name, kernels)
+    got = (r.out_vtx.cpu().numpy().view(U32), r.out_idx.cpu().numpy(), r.old2new.cpu().numpy(), r.new2old.cpu().numpy())
+    for label, g, e in zip(("out_vtx", "out_idx", "old2new", "new2old"), got, oracle.reindex(vtx, idx)):
+        assert np.array_equal(g, e), (name, label)
+
+
+def check_batch(vs, es, name, kernel=None):
+    import paper_2109_09812_amd as mrx
+    vo = np.concatenate([[0], np.cumsum([v.shape[0] for v in vs])]).astype(np.int64)
+    eo = np.concatenate([[0], np.cumsum([e.shape[0] for e in es])]).astype(np.int64)
+    vtx, idx = np.concatenate(vs), np.concatenate(es)
+    _say(name, len(vs), "meshes", vtx.shape)
+    r, kernels = ran(mrx, lambda: mrx.reindex_mesh_batched(dev(vtx), dev(vo), dev(idx), dev(eo),
+                                                           tuning=(0, 0, 0, HASH)))
+    assert kernel is None or kernel in kernels, (name, kernels)
+    want = oracle.reindex_batched(vtx, idx, vo, eo)
+    for label, e in zip(("out_vtx", "out_vtx_offsets", "out_idx", "old2new", "new2old"), want):
+        g = getattr(r, label).cpu().numpy()
+        assert np.array_equal(g.view(U32) if label == "out_vtx" else g, e), (name, label)
+
+
+def some_used(rng, n, share):
+    return rng.permutation(n)[: int(share * n)].astype(np.int32).reshape(-1, 1)
+
+
+def random_records(rng, n, k, distinct):
+    pool = rng.integers(0, 2**32, size=(max(1, distinct), k), dtype=np.uint64).astype(U32)
+    return pool[rng.integers(0, pool.shape[0], n)]
+
+
+# K with lists of 4,096 (1,024 for small buckets) down to 1,024 (512) records
+@pytest.mark.parametrize("k", [2, 3, 5, 6, 9, 16])
+@pytest.mark.parametrize("used", [1.0, 0.2, 0.0])
+def test_more_distinct_records_than_the_list_holds(k, used):
+    """Distinct records, some copied, of hashes in the interval of one bucket
+    (a hundredth of a percent of all), among others."""
+    rng = np.random.default_rng(31 * k + int(10 * used))
+    h = (0x12340000 + rng.integers(0, 1 << 18, 7000)).astype(U32)
+    one = records_of_hash(rng, 7000, k, h)
+    vtx = np.concatenate([one, one[rng.integers(0, 7000, 900)], random_records(rng, 60_000, k, 40_000)])
+    vtx = vtx[rng.permutation(vtx.shape[0])]
+    check(vtx, some_used(rng, vtx.shape[0], used), f"shares k={k} used={used}", "bucket_scatter")
+
+
+@pytest.mark.parametrize("k", [2, 3, 8, 16])
+@pytest.mark.parametrize("copies", [1, 4])
+def test_records_of_one_hash(k, copies):
+    """The table cannot tell them apart by shares: chains in memory do, for a
+    bucket of one workgroup and (copies = 4) for one in parts."""
+    rng = np.random.default_rng(57 + k)
+    one = np.repeat(records_of_hash(rng, 6000, k, 0xDEADBEEF), copies, axis=0)  # copies = 4: in parts
+    vtx = np.concatenate([one, random_records(rng, 20_000, k, 9000)])
+    vtx = vtx[rng.permutation(vtx.shape[0])]
+    check(vtx, some_used(rng, vtx.shape[0], 0.4), f"one hash k={k} x{copies}", "bucket_scatter")
+
+
+# parts hold 4,096 elements here: a bucket is cut above 8,192
+@pytest.mark.parametrize("k", [2, 3, 7, 16])
+@pytest.mark.parametrize("n,hot", [(8192, 8192), (8193, 8193), (12_288, 12_288), (50_000, 8190), (50_000, 8300),
+                                   (50_000, 20_480), (50_000, 50_000), (300_000, 150_000)])
+def test_value_with_many_copies(k, n, hot):
+    rng = np.random.default_rng(n + hot + k)
+    vtx = random_records(rng, n, k, n // 3)
+    vtx[rng.permutation(n)[:hot]] = rng.integers(0, 2**32, size=(1, k), dtype=np.uint64).astype(U32)
+    for used in (0.5, 0.0001):
+        check(vtx, some_used(rng, n, used), f"hot k={k} n={n} hot={hot}", "bucket_scatter")
+
+
+@pytest.mark.parametrize("values", [2, 3, 40, 5000])
+def test_many_copies_of_several_values_in_one_bucket(values):
+    """Values that share a bucket, so that its parts list many groups each;
+    the smallest id of every one may lie in any part."""
+    rng = np.random.default_rng(values)
+    pool = records_of_hash(rng, values, 3, (0x70000000 + rng.integers(0, 1 << 12, values)).astype(U32))
+    vtx = np.concatenate([pool[rng.integers(0, values, 90_000)], random_records(rng, 30_000, 3, 10_000)])
+    if values == 40:
+        vtx = vtx[rng.permutation(vtx.shape[0])]
+    elif values == 3:
+        vtx = vtx[::-1]
+    for used in (1.0, 0.3, 0.0):
+        check(vtx, some_used(rng, vtx.shape[0], used), f"{values} hot values used {used}", "bucket_scatter")
+
+
+@pytest.mark.parametrize("bands", [False, True])
+def test_batch_with_large_buckets(bands):
+    """Meshes of one value, of one value and others, of records of one hash,
+    and of more distinct records than a list holds, next to ordinary and empty
+    ones; `bands`: large enough for Steps 1 and 4 by vertex bands."""
+    rng = np.random.default_rng(3)
+    grow = 40 if bands else 1
+    vs = [random_records(rng, 5000, 3, 2000), np.repeat(random_records(rng, 1, 3, 1), 30_000, axis=0),
+          np.zeros((0, 3), U32), random_records(rng, 40_000, 3, 12_000), random_records(rng, 70, 3, 9),
+          records_of_hash(rng, 6000, 3, 77), np.repeat(records_of_hash(rng, 5000, 3, 99), 4, axis=0),
+          records_of_hash(rng, 9000, 3, (0x5000 + rng.integers(0, 1 << 10, 9000)).astype(U32)),
+          random_records(rng, 30_000 * grow, 3, 10_000 * grow)]
+    vs[3][rng.random(40_000) < 0.6] = (1, 2, 3)
+    vs[1][::997] = (1, 2, 3)
+    vs = [v[rng.permutation(v.shape[0])] for v in vs]
+    es = [some_used(rng, v.shape[0], u) for v, u in zip(vs, (0.9, 0.9, 0, 0.5, 1.0, 0.5, 0.3, 0.7, 0.95))]
+    check_batch(vs, es, "batch", "bucket_scatter")
+
+
+@pytest.mark.parametrize("n,hot", [(62_000, 3000), (62_000, 8100), (62_000, 17_000), (62_000, 31_000), (62_000, 62_000),
+                                   (700_000, 2100)])
+def test_digit_path_of_one_mesh(n, hot):
+    """4-byte records leave no room for the sample sort's tables at these
+    sizes, so the digit path serves them: buckets past k_group's window, in
+    one part and in several."""
+    rng = np.random.default_rng(n + hot)
+    vtx = random_records(rng, n, 1, n // 2)
+    for c in range(1 if n < 100_000 else 200):
+        vtx[rng.permutation(n)[:hot]] = 77 + 1000 * c
+    for used in (0.5, 0.001):
+        check(vtx, some_used(rng, n, used), f"digits n={n} hot={hot}", "group_over" if n < 100_000 else None)
+
+
+@pytest.mark.parametrize("k", [3, 16])
+def test_digit_path_of_a_batch(k):
+    """More meshes than the buckets have columns for."""
+    rng = np.random.default_rng(k)
+    vs = [random_records(rng, 12 + b % 4, k, 6) for b in range(6000)]
+    vs[7] = random_records(rng, 9000, k, 3000)
+    vs[7][rng.random(9000) < 0.7] = 5
+    vs[2000] = np.repeat(random_records(rng, 1, k, 1), 20_000, axis=0)
+    vs[2000][::501, 0] += U32(1)
+    vs[5999] = np.repeat(random_records(rng, 2, k, 2), 10_000, axis=0)[rng.permutation(20_000)]
+    es = [some_used(rng, v.shape[0], 0.7) for v in vs]
+    check_batch(vs, es, "digits, batch", "group_over")
+
+
+def test_large_buckets_replayed_from_a_graph():
+    """The parts' counters start at zero in every replay."""
+    import paper_2109_09812_amd as mrx
+    rng = np.random.default_rng(12)
+    a, b = random_records(rng, 200_000, 3, 60_000), random_records(rng, 200_000, 3, 60_000)
+    a[rng.random(200_000) < 0.5] = 9
+    idx = some_used(rng, 200_000, 0.6)
+    r = mrx.Reindexer(dev(a), dev(idx), tuning=(0, 0, 0, HASH))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        r.launch()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            r.launch()
+    torch.cuda.synchronize()
+    for vtx in (a, b, a, a):
+        _say("replay")
+        r.vtx.copy_(dev(vtx))
+        g.replay()
+        torch.cuda.synchronize()
+        res = mrx.Reindexed(r.out_vtx, r.out_idx, r.old2new, r.new2old, r.meta).trim()
+        want = oracle.reindex(vtx, idx)
+        assert np.array_equal(res.out_idx.cpu().numpy(), want[1]) and np.array_equal(res.new2old.cpu().numpy(), want[3])
+
+
+def _ms(r):
+    for _ in range(3):
+        r.launch()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        r.launch()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
+# a third of the vertices one value; all of them
+@pytest.mark.parametrize("n,form", [(4_000_000, 0.3), (4_000_000, 1.0), (31_000_000, 0.3)])
+def test_no_slower_than_sorting_all(n, form):
+    """One workgroup alone on a large bucket took hash grouping past the time of
+    sorting all (4M vertices of one value: six times). It should take less than two thirds of it, or
+    three times where all records are one and no pass of the sort has anything
+    to do."""
+    import paper_2109_09812_amd as mrx
+    g = torch.Generator(device="cuda").manual_seed(n)
+    v = torch.randint(-2**31, 2**31 - 1, (n, 3), generator=g, device=DEV, dtype=torch.int32)
+    v = v[torch.randint(0, n // 6, (n,), generator=g, device=DEV)]
+    v[torch.rand(n, generator=g, device=DEV) < form] = 5
+    idx = torch.randint(0, n, (n // 3, 3), generator=g, device=DEV, dtype=torch.int32)
+    _say("times", n, form)
+    hashed = _ms(mrx.Reindexer(v, idx, tuning=(0, 0, 0, HASH)))
+    sorted_ = _ms(mrx.Reindexer(v, idx, tuning=(0, 0, 0, SORT_ALL)))
+    print(f"[time] {n} {form}: {hashed:.3f} ms, sort-all {sorted_:.3f} ms", flush=True)
+    assert hashed < sorted_ * (3.0 if form == 1.0 else 2.0 / 3.0)
