@@ -58,8 +58,8 @@ struct BucketShape {
   static constexpr int TARGET = DCAP * 3 / 4;
 };
 
-// Buckets and tiles for n vertices in nmesh meshes; buckets = 0: too many
-// vertices or meshes.
+// Buckets and tiles for n vertices in nmesh meshes with m index entries;
+// buckets = 0: too many vertices or meshes, or too few entries.
 struct BucketPlan {
   int32_t buckets = 0;   // columns (a batch may use fewer)
   int32_t target = 0;    // vertices per bucket aimed at
@@ -70,7 +70,7 @@ struct BucketPlan {
 };
 
 template <int K>
-inline BucketPlan bucket_plan(int64_t n, int32_t nmesh, int64_t words) {
+inline BucketPlan bucket_plan(int64_t n, int64_t m, int32_t nmesh, int64_t words) {
   using SH = BucketShape<K>;
   BucketPlan p;
   const int64_t most = nmesh > 1 ? int64_t(kBucketMaxMesh) - nmesh : int64_t(kBucketMax);
@@ -80,6 +80,13 @@ inline BucketPlan bucket_plan(int64_t n, int32_t nmesh, int64_t words) {
   int64_t t = std::max<int64_t>(256, std::min<int64_t>(nmesh > 1 ? n / 2048 : n / 1024, SH::TARGET));
   t = std::max(t, (n + most - 1) / most);
   if (t > kBucketMostPer) return p;
+  // Where few entries name few values, the grouping is nearly all there is to
+  // do. Were the records distinct, such buckets would take four rounds and
+  // more, each over all of a bucket, where the digit path groups in one: 26M
+  // distinct 12-byte records 1.95 ms by buckets and 1.54 by digits, six copies
+  // of each 1.27 and 1.41. Few used of many is a part cut out of a mesh that is
+  // indexed already far more often than one out of a soup.
+  if (t > 3 * SH::DCAP && m < n / 8) return p;
   p.target = int32_t(t);
   p.buckets = int32_t((n + t - 1) / t + (nmesh > 1 ? nmesh : 0));
   // small tiles while the large ones would not fill the GPU twice

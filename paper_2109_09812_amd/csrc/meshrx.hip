@@ -706,11 +706,11 @@ LargeBuckets large_buckets(int64_t n, uint32_t* words, GroupArgs* g) {
   return l;
 }
 
-BucketState bucket_state(const SortVariant& v, Layout L, int64_t n, int K, int32_t nmesh, uint32_t* lookback,
-                         uint32_t* matrix) {
+BucketState bucket_state(const SortVariant& v, Layout L, int64_t n, int64_t m, int K, int32_t nmesh,
+                         uint32_t* lookback, uint32_t* matrix) {
   BucketState b;
   const BucketGroup& g = nmesh > 1 ? v.bucket_mesh : v.bucket;
-  const BucketPlan p = g.plan(n, nmesh, n * int64_t(K + 1));
+  const BucketPlan p = g.plan(n, m, nmesh, n * int64_t(K + 1));
   const int64_t F = p.buckets;
   const int64_t ranges = group_compact_ranges(F);
   if (F == 0 || F > (nmesh > 1 ? kBucketMaxMesh : kBucketMax) ||
@@ -808,7 +808,7 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
 
   // one partition pass where the buckets suffice, else two or three stable
   // passes by hash digits; the order of the used groups takes either's chunks
-  BucketState bs = bucket_state(v, L, n, K, 1, reinterpret_cast<uint32_t*>(lookback), buf[1]);
+  BucketState bs = bucket_state(v, L, n, m, K, 1, reinterpret_cast<uint32_t*>(lookback), buf[1]);
   const bool bucketed = bs.plan.buckets > 0;
   if (bucketed) L.tiles_group = bs.plan.buckets;
   const int64_t group_ranges = group_compact_ranges(L.tiles_group);
@@ -1214,7 +1214,7 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
   int counter = 0;  // next tile counter (claimed tiles)
   auto next_counter = [&]() { return claimed ? counters + counter++ : nullptr; };
 
-  BucketState bs = bucket_state(v, L, n, K, num_meshes, reinterpret_cast<uint32_t*>(lookback), buf[1]);
+  BucketState bs = bucket_state(v, L, n, m, K, num_meshes, reinterpret_cast<uint32_t*>(lookback), buf[1]);
   const bool bucketed = bs.plan.buckets > 0;
   if (bucketed) L.tiles_group = bs.plan.buckets;
   const int64_t group_ranges = group_compact_ranges(L.tiles_group);

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(BLOCK) void k_mark_histogram(MarkArgs ma, const uin
 // One partition pass into hash buckets and their grouping
 // (bucket_kernels.hpp).
 struct BucketGroup {
-  BucketPlan (*plan)(int64_t n, int32_t nmesh, int64_t words) = nullptr;
+  BucketPlan (*plan)(int64_t n, int64_t m, int32_t nmesh, int64_t words) = nullptr;
   // bucket counts, with Step 1's marking by scattered stores (`mark`) or by
   // bands (`band`) in the same launch when given
   void (*count)(const BucketArgs&, const MarkArgs* mark, const BandArgs* band, hipStream_t) = nullptr;

@@ -257,18 +257,21 @@ def _ms(r):
 
 
 # a third of the vertices one value; all of them
-@pytest.mark.parametrize("n,form", [(4_000_000, 0.3), (4_000_000, 1.0), (31_000_000, 0.3)])
+@pytest.mark.parametrize("n,form", [(4_000_000, 0.3), (4_000_000, 1.0), (31_000_000, 0.3), (26_000_000, "distinct")])
 def test_no_slower_than_sorting_all(n, form):
-    """One workgroup alone on a large bucket took hash grouping past the time of
-    sorting all (4M vertices of one value: six times). It should take less than two thirds of it, or
+    """One workgroup alone on a large bucket, or looking records up in a table
+    that is full, took hash grouping past the time of sorting all (4M vertices
+    of one value: six times). It should take less than two thirds of it, or
     three times where all records are one and no pass of the sort has anything
     to do."""
     import paper_2109_09812_amd as mrx
     g = torch.Generator(device="cuda").manual_seed(n)
     v = torch.randint(-2**31, 2**31 - 1, (n, 3), generator=g, device=DEV, dtype=torch.int32)
-    v = v[torch.randint(0, n // 6, (n,), generator=g, device=DEV)]
-    v[torch.rand(n, generator=g, device=DEV) < form] = 5
-    idx = torch.randint(0, n, (n // 3, 3), generator=g, device=DEV, dtype=torch.int32)
+    if form != "distinct":
+        v = v[torch.randint(0, n // 6, (n,), generator=g, device=DEV)]
+        v[torch.rand(n, generator=g, device=DEV) < form] = 5
+    idx = torch.randint(0, n, (n // 3 if form != "distinct" else n // 300, 3), generator=g, device=DEV,
+                        dtype=torch.int32)
     _say("times", n, form)
     hashed = _ms(mrx.Reindexer(v, idx, tuning=(0, 0, 0, HASH)))
     sorted_ = _ms(mrx.Reindexer(v, idx, tuning=(0, 0, 0, SORT_ALL)))

@@ -29,7 +29,7 @@ static int fail(const char* what, int form, long long n, int nmesh) {
 }
 template <int K>
 static int check(int form, int64_t n, int32_t nmesh, const std::vector<int64_t>& off) {
-  const BucketPlan p = bucket_plan<K>(n, nmesh, n * (K + 1));
+  const BucketPlan p = bucket_plan<K>(n, n, nmesh, n * (K + 1));  // as many entries as vertices
   std::vector<int64_t> ordered(nmesh + 1);
   uint32_t reached = 0;
   int64_t buckets = 0, digits = 0;
