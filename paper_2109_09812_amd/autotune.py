@@ -1,7 +1,8 @@
 """Autotuner for the radix-sort kernel shape (digit width, workgroup size,
 items per thread) and the way duplicates are found (sort all vertices by
 their full record, or hash grouping; for a batch the key is (mesh id,
-record) either way).
+record) either way), and for small meshes the library's default, which alone
+may re-index a whole mesh in one workgroup.
 
 Every compiled variant and either strategy compute the identical result, so
 tuning is purely a speed choice. Which strategy wins depends on the data (how
@@ -28,7 +29,7 @@ import torch
 from . import _lib
 from .api import BatchedReindexer, Reindexer
 
-SCHEMA = 3
+SCHEMA = 4
 
 
 def cache_path() -> str:
@@ -76,11 +77,21 @@ def save_cache(entries: dict, path: str | None = None):
 _STRATEGY_FLAGS = (_lib.MRX_TUNING_SORT_ALL, _lib.MRX_TUNING_HASH_GROUPS)
 
 
+# The most vertices one workgroup takes at any record width.
+_SMALL = 4096
+# A shape has to be this much faster than the default of a small mesh: where
+# the mesh is a little too large for one workgroup the two differ by noise,
+# and the cached choice serves smaller meshes of its size bucket too.
+_MARGIN = 0.95
+
+
 def candidates(vtx_bytes: int, num_vtx: int, batched: bool):
     """Every compiled kernel shape, with each strategy a call of this shape
-    can take (meshes and batches of 2^30 or more vertices always sort all)."""
+    can take (meshes and batches of 2^30 or more vertices always sort all);
+    for meshes that may fit one workgroup the all-zero default first, since
+    any shape or strategy asks for the general launch sequence."""
     flags = (0,) if num_vtx >= (1 << 30) else _STRATEGY_FLAGS
-    out = []
+    out = [_lib.Tuning(0, 0, 0, 0)] if not batched and num_vtx <= _SMALL else []
     for t in _lib.tunings(vtx_bytes):
         for fl in flags:
             out.append(_lib.Tuning(t.digit_bits, t.block_threads, t.items_per_thread, fl))
@@ -89,11 +100,14 @@ def candidates(vtx_bytes: int, num_vtx: int, batched: bool):
 
 def cached_tuning(entries: dict, key: str, vtx_bytes: int):
     """The cached candidate for `key` if the loaded library still has its
-    shape and its flags are a strategy choice, else None."""
+    shape and its flags are a strategy choice (or it is the default), else
+    None."""
     e = entries.get(key)
     if not isinstance(e, dict) or not isinstance(e.get("tuning"), list) or len(e["tuning"]) != 4:
         return None
     want = tuple(int(x) for x in e["tuning"])
+    if want == (0, 0, 0, 0):
+        return _lib.Tuning(*want)
     if want[3] not in (0,) + _STRATEGY_FLAGS:
         return None
     for t in _lib.tunings(vtx_bytes):
@@ -161,7 +175,7 @@ def autotune(vtx: torch.Tensor, idx: torch.Tensor, vtx_offsets: torch.Tensor | N
         report[t.as_key()] = ms
         if verbose:
             print(f"[autotune] {key} {t.as_key()}: {ms:.4f} ms", flush=True)
-        if best is None or ms < best[1]:
+        if best is None or ms < best[1] * (_MARGIN if best[0].digit_bits == 0 else 1.0):
             best = (t, ms)
         del r
     if use_cache:
