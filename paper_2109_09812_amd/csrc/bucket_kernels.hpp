@@ -35,7 +35,15 @@ constexpr int kBucketBlock = 512;
 // stage, leave room for two workgroups on a CU.
 constexpr int kBucketMax = 2560;      // one mesh
 constexpr int kBucketMaxMesh = 6144;  // batches: at least one per mesh
-constexpr int kBucketMostPer = 10400; // vertices per bucket
+// Vertices per bucket, beyond which the digit path takes over. Buckets win
+// where the records have copies and lose, the more the larger they are (a
+// share of a bucket's distinct records is read with all the others), where
+// they do not. 12-byte records, ms by buckets and by digits with six, two and
+// one copy of each: 26M (10,156 a bucket) 1.40 and 1.64, 2.34 and 2.20, 3.38
+// and 2.88; 31M (12,110) 1.65 and 1.90, 2.78 and 2.56, 4.16 and 3.44; 16M
+// (6,250) 0.88 and 1.02, 1.18 and 1.26, 1.98 and 1.77. The line lies where the
+// loss without copies reaches a sixth, about the gain of six.
+constexpr int kBucketMostPer = 10400;
 constexpr int kGroupBlock = 1024;     // k_group_bucket
 constexpr int kGroupBlockSmall = 256; // where buckets are aimed to be small
 
