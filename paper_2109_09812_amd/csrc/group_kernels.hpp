@@ -414,20 +414,22 @@ __global__ __launch_bounds__(GroupShape<MESH ? K + 1 : K>::BLOCK, (group_min_wav
   __syncthreads();
 
   // ---- bucket starts: the first (sq) and last (lq) in the chunk and the first
-  // at or after position c1 (eq; position n counts as one)
+  // at or after position c1 (eq; position n counts as one). A wave's slots are
+  // neighbours, so its first and its last lane with one tell it (buckets of two
+  // elements, every lane for itself: 0.74 ms instead of 0.52 for 36M vertices).
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const int q = i * BLOCK + tid;
     const int64_t pos = c0 - 1 + q;
-    if (q == 0 || pos > n) continue;
-    const bool start = pos == 0 || pos == n || s_scratch[q] != s_scratch[q - 1];
-    if (!start) continue;
-    if (q < qc1) {
-      atomicMin(&s_sq, uint32_t(q));
-      atomicMax(&s_lq, uint32_t(q));
-    } else {
-      atomicMin(&s_eq, uint32_t(q));
+    const bool start =
+        q > 0 && pos <= n && (pos == 0 || pos == n || s_scratch[q] != s_scratch[max(q, 1) - 1]);
+    const uint64_t in = ballot(start && q < qc1), after = ballot(start && q >= qc1);
+    if (in) {
+      const int first = __ffsll((unsigned long long)in) - 1, last = 63 - __clzll((long long)in);
+      if (lane == first) atomicMin(&s_sq, uint32_t(q));
+      if (lane == last) atomicMax(&s_lq, uint32_t(q));
     }
+    if (after && lane == __ffsll((unsigned long long)after) - 1) atomicMin(&s_eq, uint32_t(q));
   }
   __syncthreads();
   const int sq = int(s_sq);
