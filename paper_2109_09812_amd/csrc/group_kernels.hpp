@@ -700,11 +700,15 @@ static __global__ void k_group_sort_plan(SortBuffers b) {
 
 // After an LSD key sort of the used groups: sorted position c is output
 // vertex c (Section 2, Step 3 compacts the sorted array). Writes the record,
-// cmap[group] = c, and U.
+// cmap[group] = c, U, and for one mesh the representative: gathered here it
+// takes 0.18 ms for the 13.3M used values of an 80M-vertex mesh, where finding
+// them among the pairs takes 0.72 longer in the scatter of the map.
 struct FinalizeArgs {
   SortBuffers bufs;        // sorted(): [U][K+1] (record, group name)
   int32_t* cmap;           // [n]
   uint32_t* out_vtx;       // [U][K]
+  const uint32_t* rep;     // [n]
+  int32_t* new2old;        // [U], nullable
   int64_t* out_num;        // nullable
   int64_t cap;             // n
   Control* ctl;
@@ -729,6 +733,7 @@ __global__ __launch_bounds__(256) void k_group_finalize(FinalizeArgs a) {
       continue;
     }
     a.cmap[g] = int32_t(c);
+    if (a.new2old) a.new2old[c] = int32_t(a.rep[g]);
   }
 }
 

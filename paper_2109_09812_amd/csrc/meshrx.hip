@@ -192,7 +192,7 @@ int bits_for(int64_t x) {  // bits needed to represent values 0..x
 
 // Hash grouping for a single mesh of n vertices? Its look-back words hold
 // counts below 2^30. By default from the smallest meshes that do not fit one
-// workgroup (use_small) on: 21,905 12-byte vertices take 86 us in 11 launches,
+// workgroup (use_small) on: 21,905 12-byte vertices take 60 us in 11 launches,
 // 199 us in the 19 of the sort of all vertices.
 constexpr int64_t kHashMinDefault = int64_t(1) << 10;
 // For batches, and where the workspace was sized for the sort of all vertices
@@ -455,18 +455,25 @@ int64_t rand_grid(int64_t work, int items = kRandItems) {
   return std::max<int64_t>(1, (work + kRandBlock * items - 1) / (kRandBlock * items));
 }
 
+// Few entries, so few used values among many (also bucket_plan)?
+bool few_used(int64_t n, int64_t m) { return m < n / 8; }
+
 // The scatter's items per thread: with 16 a mesh of 429,165 vertices has 105
 // workgroups on 256 CUs (17.9 us; 9.4 us with 4), 4,096 parts of 1.05 million
-// 256 (27.4 and 14.3 us).
+// 256 (27.4 and 14.3 us). `stage_rep`: representatives of most vertices'
+// groups are wanted.
 template <bool BATCHED, typename... A>
-void launch_scatter_old2new(hipStream_t s, SortBuffers sb, const uint2* pairs, const int32_t* cmap, int64_t n,
-                            const A&... rest) {
+void launch_scatter_old2new(hipStream_t s, bool stage_rep, SortBuffers sb, const uint2* pairs, const int32_t* cmap,
+                            int64_t n, const A&... rest) {
+  const dim3 block(kRandBlock), few(rand_grid(n, kScatterFew)), many(rand_grid(n, kScatterItems));
   if (rand_grid(n, kScatterItems) < 4 * 256)
-    hipLaunchKernelGGL((k_scatter_old2new<BATCHED, kScatterFew>), dim3(rand_grid(n, kScatterFew)), dim3(kRandBlock), 0,
-                       s, sb, pairs, cmap, n, rest...);
+    hipLaunchKernelGGL((k_scatter_old2new<BATCHED, kScatterFew, false>), few, block, 0, s, sb, pairs, cmap, n, rest...);
+  else if (stage_rep)
+    hipLaunchKernelGGL((k_scatter_old2new<BATCHED, kScatterItems, true>), many, block, 0, s, sb, pairs, cmap, n,
+                       rest...);
   else
-    hipLaunchKernelGGL((k_scatter_old2new<BATCHED, kScatterItems>), dim3(rand_grid(n, kScatterItems)),
-                       dim3(kRandBlock), 0, s, sb, pairs, cmap, n, rest...);
+    hipLaunchKernelGGL((k_scatter_old2new<BATCHED, kScatterItems, false>), many, block, 0, s, sb, pairs, cmap, n,
+                       rest...);
 }
 
 mrx_status check_launch() {
@@ -559,6 +566,8 @@ struct OrderArgs {
   bool wide;
   uint32_t* counter;         // nullable
   int gp;                    // passes of the call so far
+  const uint32_t* rep;       // one mesh: representatives and, nullable, new2old for the LSD sort to write
+  int32_t* new2old;
   const int64_t* vtx_off;    // batches
   const int32_t* mesh_tab;
   int32_t nmesh;
@@ -673,6 +682,8 @@ void order_used_groups(const SortVariant& v, const Layout& L, int64_t n, int K, 
   fa.bufs = sb;
   fa.cmap = o.cmap;
   fa.out_vtx = o.out_vtx;
+  fa.rep = o.rep;
+  fa.new2old = o.new2old;
   fa.out_num = o.out_num;
   fa.cap = n;
   fa.ctl = o.ctl;
@@ -935,7 +946,10 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
     o.counter = claimed ? counters + counter : nullptr;
     o.gp = gp;
     o.out_num = out_num_vtx;
+    o.rep = reinterpret_cast<const uint32_t*>(rep);
+    o.new2old = new2old;
     order_used_groups(v, L, n, K, o, s);
+    if (!split_applies(v, L, n, K)) new2old = nullptr;  // written
     // Step 4's map (and, by bands, the remap)
     if (bp.mode == kMarkAndMap) {
       // X and C are free again: X takes the partitioned pairs, C the new ids
@@ -958,9 +972,10 @@ mrx_status launch_hash(const SortVariant& v, const Layout& layout, const void* v
       return check_launch();
     }
     prof_mark("old2new", s);
-    launch_scatter_old2new<false>(s, SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs),
-                                  cmap, n, nullptr, nullptr, 0, nullptr, old2new,
-                                  reinterpret_cast<const uint32_t*>(rep), new2old);
+    launch_scatter_old2new<false>(s, new2old && !few_used(n, m), SortBuffers{{nullptr, nullptr}, nullptr, 0},
+                                  static_cast<const uint2*>(pairs), cmap, n, nullptr, nullptr, 0, nullptr, old2new,
+                                  reinterpret_cast<const uint32_t*>(rep), new2old,
+                                  static_cast<const uint32_t*>(g.over_any));
   }
   // Step 4: remap the index array
   if (m > 0) {
@@ -1155,8 +1170,9 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
       return check_launch();
     }
     prof_mark("old2new", s);
-    launch_scatter_old2new<false>(s, sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0, nullptr,
-                                  old2new, static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr));
+    launch_scatter_old2new<false>(s, false, sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0, nullptr,
+                                  old2new, static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
+                                  static_cast<const uint32_t*>(nullptr));
   }
   // Step 4: remap the index array
   if (m > 0) {
@@ -1391,10 +1407,11 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
     return check_launch();
   }
   prof_mark("old2new", s);
-  launch_scatter_old2new<true>(s, SortBuffers{{nullptr, nullptr}, nullptr, 0}, static_cast<const uint2*>(pairs), cmap,
+  launch_scatter_old2new<true>(s, new2old && !few_used(n, m), SortBuffers{{nullptr, nullptr}, nullptr, 0},
+                               static_cast<const uint2*>(pairs), cmap,
                                n, vtx_offsets, static_cast<const int64_t*>(out_vtx_offsets), num_meshes,
                                static_cast<const int32_t*>(vtab), old2new, reinterpret_cast<const uint32_t*>(rep),
-                               new2old);
+                               new2old, static_cast<const uint32_t*>(g.over_any));
   if (m > 0) {
     prof_mark("remap", s);
     hipLaunchKernelGGL((k_remap<true>), dim3(rand_grid(m)), dim3(kRandBlock), 0, s, idx, m, arity, n, vtx_offsets,
@@ -1720,9 +1737,10 @@ mrx_status mrx_reindex_mesh_batched(const void* vtx, const int64_t* vtx_offsets,
                        num_meshes, sb, static_cast<const int32_t*>(cmap), static_cast<const Control*>(ctl),
                        static_cast<const int64_t*>(&ctl->num_used), n, out_vtx_offsets);
     prof_mark("old2new", s);
-    launch_scatter_old2new<true>(s, sb, static_cast<const uint2*>(nullptr), cmap, n, vtx_offsets, out_vtx_offsets,
+    launch_scatter_old2new<true>(s, false, sb, static_cast<const uint2*>(nullptr), cmap, n, vtx_offsets, out_vtx_offsets,
                                  num_meshes, static_cast<const int32_t*>(vtab), old2new,
-                                 static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr));
+                                 static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
+                                  static_cast<const uint32_t*>(nullptr));
     if (new2old) {
       prof_mark("localize_new2old", s);
       hipLaunchKernelGGL(k_localize_new2old, dim3(grid_for(n, 256)), dim3(256), 0, s, new2old,

@@ -300,16 +300,24 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
 // Step 4's map: old2new[org] = new id of the group of each sorted element
 // (-1 if the group is unused), a scatter from the (group id, original id)
 // pairs that the flag scan left in the spare sort buffer (or that the hash
-// grouping left in `pairs_in`); the cmap reads follow the non-decreasing
-// group ids. For a batch the new id is made mesh-local with the mesh's
-// output offset. A batch's pairs are in mesh order, mesh b's at positions
-// [vtx_off[b], vtx_off[b+1]) (sorted by (mesh id, record), or hash-ordered
-// with per-mesh bucket ranges), so the mesh of an element is that of its
-// position: one lookup for a tile inside one mesh. `new2old` (nullable, after
-// hash grouping) receives the representatives `rep` (null after sort-all),
-// given by group name, at their groups' new ids: the pair that holds one is
-// found by comparison.
-template <bool BATCHED, int kItems>
+// grouping left in `pairs_in`). After sorting, and after k_group for one mesh,
+// a tile's group ids do not decrease and grow by at most one per position, so
+// the new ids between its first and its last are staged in LDS with coalesced
+// loads. In a hash bucket, and in a batch after k_group, the names come in no
+// order: what the stage between those two misses is gathered, from lines that
+// the bucket's other pairs read too. For a batch the new id is made mesh-local
+// with the mesh's output offset. A batch's pairs are in mesh order, mesh b's
+// at positions [vtx_off[b], vtx_off[b+1]) (sorted by (mesh id, record), or
+// hash-ordered with per-mesh bucket ranges), so the mesh of an element is that
+// of its position: one lookup for a tile inside one mesh. `new2old` (nullable,
+// after hash grouping) receives the representatives `rep`, given by group name,
+// at their groups' new ids: the pair that holds one is found by comparison.
+// `large` (null after sort-all): not 0 if there were large buckets (led_name). With kStageRep they are staged like the
+// new ids, with both loads in flight: for calls that use most of their values
+// (batch4096 5.5 ms; 5.9 where the same LDS took first the one and then the
+// other). Where few are used only theirs are read, and the LDS goes to more
+// workgroups (26M vertices, 1% used: 0.69 ms staged, 0.45 not).
+template <bool BATCHED, int kItems, bool kStageRep>
 __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs, const uint2* pairs_in,
                                                                 const int32_t* __restrict__ cmap, int64_t n,
                                                                 const int64_t* __restrict__ vtx_off,
@@ -317,19 +325,17 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
                                                                 int32_t nmesh, const int32_t* __restrict__ vtx_tab,
                                                                 int32_t* __restrict__ old2new,
                                                                 const uint32_t* __restrict__ rep,
-                                                                int32_t* __restrict__ new2old) {
+                                                                int32_t* __restrict__ new2old,
+                                                                const uint32_t* __restrict__ large) {
   constexpr int TILE = kRandBlock * kItems;
   const uint2* __restrict__ pairs = pairs_in ? pairs_in : reinterpret_cast<const uint2*>(bufs.spare());
-  __shared__ int32_t s_stage[TILE];  // cmap, then (large tiles) the representatives
-  constexpr bool kStageRep = kItems == kScatterItems;
+  __shared__ int32_t s_cmap[TILE];
+  __shared__ uint32_t s_rep[kStageRep ? TILE : 1];
   __shared__ uint32_t s_g[2];
   __shared__ uint32_t s_mesh[2];
   const int64_t t0 = int64_t(blockIdx.x) * TILE;
   const int64_t base = t0 + threadIdx.x;
   const int64_t t1 = min(t0 + TILE, n) - 1;  // last position of the tile
-  // A tile's group ids are non-decreasing and grow by at most one per
-  // position, so cmap[g_first .. g_last] (at most TILE entries) is staged in
-  // LDS with coalesced loads instead of one gather per element.
   if (threadIdx.x == 0) {
     s_g[0] = pairs[t0].x;
     s_g[1] = pairs[t1].x;
@@ -353,45 +359,33 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   const uint32_t g0 = s_g[0];
   const int64_t span = min(int64_t(TILE), int64_t(s_g[1]) - int64_t(g0) + 1);
   for (int64_t i = threadIdx.x; i < span; i += kRandBlock) {
-    s_stage[i] = (int64_t(g0) + i < n) ? cmap[int64_t(g0) + i] : -1;
+    s_cmap[i] = (int64_t(g0) + i < n) ? cmap[int64_t(g0) + i] : -1;
+    if (kStageRep && new2old) s_rep[i] = (int64_t(g0) + i < n) ? rep[int64_t(g0) + i] : 0xFFFFFFFFu;
   }
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < kItems; ++it) {
     const int64_t off = int64_t(p[it].x) - int64_t(g0);
     if (int64_t(p[it].x) >= n) c[it] = -1;
-    else c[it] = (off >= 0 && off < span) ? s_stage[off] : cmap[p[it].x];  // outside: only after a failed wait
-    if (rep && c[it] < -1 && int64_t(p[it].x) < n) {
-      // a name that leads to another of its group (of a large hash bucket)
+    else c[it] = (off >= 0 && off < span) ? s_cmap[off] : cmap[p[it].x];
+  }
+  if (large && *large != 0) {
+    // names that lead to another of their group (of a large hash bucket)
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+      if (c[it] >= -1 || int64_t(p[it].x) >= n) continue;
       p[it].x = led_name(c[it]);
       c[it] = int64_t(p[it].x) < n ? cmap[p[it].x] : -1;
     }
   }
-  // which pairs hold their group's representative: staged in the same LDS where
-  // many groups of the tile are used (with room for both, half as many
-  // workgroups on a CU took 0.69 ms for 26M vertices of which few were used,
-  // 0.57 with the stage in every tile, and 0.46 as it is)
-  uint32_t reps = 0;
-  if (new2old) {
-    int used = 0;
+  uint32_t reps = 0;  // pairs that hold their group's representative
+  if (!kStageRep && new2old) {
+    uint32_t r[kItems];  // all loads in flight
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) used += c[it] >= 0 ? 1 : 0;
-    const bool staged = kStageRep && __syncthreads_or(used > kItems / 2);
-    if (staged) {
-      for (int64_t i = threadIdx.x; i < span; i += kRandBlock)
-        s_stage[i] = (int64_t(g0) + i < n) ? int32_t(rep[int64_t(g0) + i]) : -1;
-      __syncthreads();
-    }
-    uint32_t r[kItems];
-#pragma unroll
-    for (int it = 0; it < kItems; ++it) {
-      const int64_t off = int64_t(p[it].x) - int64_t(g0);
-      r[it] = 0xFFFFFFFFu;
-      if (c[it] < 0 || c[it] >= n) continue;
-      r[it] = staged && off >= 0 && off < span ? uint32_t(s_stage[off]) : rep[p[it].x];
-    }
+    for (int it = 0; it < kItems; ++it) r[it] = c[it] >= 0 && c[it] < n ? rep[p[it].x] : 0xFFFFFFFFu;
 #pragma unroll
     for (int it = 0; it < kItems; ++it) reps |= r[it] == p[it].y ? 1u << it : 0u;
+    if constexpr (kItems == kScatterItems) __syncthreads();  // loads before stores: 0.48 -> 0.45 ms for 26M vertices
   }
   int64_t tile_off = 0, tile_vtx = 0;  // output and vertex offsets of the tile's mesh, if it has one
   const bool one_mesh = BATCHED && s_mesh[0] == s_mesh[1];
@@ -405,7 +399,11 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   for (int it = 0; it < kItems; ++it) {
     if (int64_t(p[it].x) >= n || int64_t(p[it].y) >= n) continue;  // past the end (or a failed wait)
     int32_t cc = c[it] < 0 ? -1 : c[it];
-    const bool is_rep = reps >> it & 1u;
+    bool is_rep = reps >> it & 1u;
+    if constexpr (kStageRep) {
+      const int64_t off = int64_t(p[it].x) - int64_t(g0);
+      is_rep = new2old && cc >= 0 && cc < n && (off >= 0 && off < span ? s_rep[off] : rep[p[it].x]) == p[it].y;
+    }
     if constexpr (BATCHED) {
       if (cc >= 0) {
         int64_t out0 = tile_off, first = tile_vtx;

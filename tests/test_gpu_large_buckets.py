@@ -277,3 +277,28 @@ def test_no_slower_than_sorting_all(n, form):
     sorted_ = _ms(mrx.Reindexer(v, idx, tuning=(0, 0, 0, SORT_ALL)))
     print(f"[time] {n} {form}: {hashed:.3f} ms, sort-all {sorted_:.3f} ms", flush=True)
     assert hashed < sorted_ * (3.0 if form == 1.0 else 2.0 / 3.0)
+
+
+def test_order_by_passes_beyond_the_sample_sort():
+    """More vertices than the sample sort takes: an LSD sort orders the used
+    values and its finalisation writes new2old; one value's bucket is in
+    parts. Against sorting all."""
+    import paper_2109_09812_amd as mrx
+    n = (1 << 26) + 777
+    g = torch.Generator(device="cuda").manual_seed(6)
+    v = torch.randint(-2**31, 2**31 - 1, (n // 4, 2), generator=g, device=DEV, dtype=torch.int32)
+    v = v[torch.randint(0, n // 4, (n,), generator=g, device=DEV)]
+    v[torch.rand(n, generator=g, device=DEV) < 0.02] = 5
+    idx = torch.randint(0, n, (n // 3, 2), generator=g, device=DEV, dtype=torch.int32)
+    _say("LSD order", n)
+    a, kernels = ran(mrx, lambda: mrx.reindex_mesh(v, idx, tuning=(0, 0, 0, HASH)))
+    assert "finalize" in kernels and "group_over" in kernels, kernels
+    b = mrx.reindex_mesh(v, idx, tuning=(0, 0, 0, SORT_ALL))
+    for name in ("out_vtx", "out_idx", "old2new", "new2old"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    # without new2old the rest is the same
+    c = mrx.Reindexer(v, idx, tuning=(0, 0, 0, HASH))
+    c.new2old = None
+    c.launch()
+    torch.cuda.synchronize()
+    assert torch.equal(c.old2new, b.old2new) and torch.equal(c.out_idx, b.out_idx)
