@@ -80,9 +80,10 @@ _STRATEGY_FLAGS = (_lib.MRX_TUNING_SORT_ALL, _lib.MRX_TUNING_HASH_GROUPS)
 # The most vertices one workgroup takes at any record width.
 _SMALL = 4096
 # A shape has to be this much faster than the default of a small mesh: where
-# the mesh is a little too large for one workgroup the two differ by noise,
-# and the cached choice serves smaller meshes of its size bucket too.
-_MARGIN = 0.95
+# the mesh is a little too large for one workgroup, 3,073 to 4,096 12-byte
+# vertices, the two differ by noise (60 us in a dozen launches), and the cached
+# choice serves smaller meshes of its size bucket too (20 us in one).
+_MARGIN = 0.85
 
 
 def candidates(vtx_bytes: int, num_vtx: int, batched: bool):
