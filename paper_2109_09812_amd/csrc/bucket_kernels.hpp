@@ -11,15 +11,17 @@
 //    tiles) and the elements per bucket;
 //  * k_bucket_scatter: elements (record, id | used << 31) to their buckets,
 //    put in bucket order in LDS first so that runs are written together;
-//  * k_group_bucket: equal records of a bucket by a hash table in LDS.
+//  * k_group_bucket: equal records of a bucket by a hash table in LDS;
+//  * k_group_over: the same for buckets that k_group leaves (digit path).
 // Measured (MI355X), 26.4M 12-byte vertices of a soup: offsets 0.035, scatter
 // 0.235 (3.3 TB/s, bound by runs of three elements per tile and bucket) and
-// grouping 0.242 ms (3.0 TB/s, phases of memory and LDS work of two workgroups
+// grouping 0.239 ms (3.0 TB/s, phases of memory and LDS work of two workgroups
 // a CU), where two stable passes and k_group took 0.21 + 0.24 and 0.27 ms; 15M
 // in 256 meshes 0.010 + 0.196 + 0.185 ms, the whole call 1.65 -> 1.23 ms.
 // The order inside a bucket is that of atomics, so a group's representative is
-// the minimum of its ids. Only a bucket's distinct records take LDS, and where
-// they do not fit, the rest of the bucket takes another round.
+// the minimum of its ids. Only a bucket's distinct records take LDS; where they
+// do not fit, they take rounds by shares of their hash, and a bucket of many
+// copies is grouped in parts by several workgroups.
 #pragma once
 
 #include <algorithm>
@@ -710,9 +712,9 @@ __global__ __launch_bounds__(BLOCK, K <= 9 ? 8 : 4) void k_group_bucket(GroupBuc
   }
 }
 
-// Buckets that k_group left: few workgroups that take one after the other,
-// then the parts of large ones.
-constexpr int kOverGrid = 1024;
+// Buckets that k_group left: two workgroups a CU that take one after the
+// other, then the parts of large ones.
+constexpr int kOverGrid = 512;
 template <int K, bool MESH>
 __global__ __launch_bounds__(kGroupBlock, K <= 9 ? 8 : 4) void k_group_over(GroupArgs a, LargeBuckets large,
                                                                             int64_t tiles) {
@@ -722,6 +724,7 @@ __global__ __launch_bounds__(kGroupBlock, K <= 9 ? 8 : 4) void k_group_over(Grou
   const uint32_t count = uniform(*a.over_count);
   const bool any = uniform(*a.over_any) != 0;
   uint32_t i = blockIdx.x;
+  if (i >= count && !any) return;
   for (bool helper = false; !helper;) {
     uint32_t tile;
     if (i < count) {
@@ -734,7 +737,8 @@ __global__ __launch_bounds__(kGroupBlock, K <= 9 ? 8 : 4) void k_group_over(Grou
       if (tile == 0) return;
       --tile;
     }
-    const int64_t b0 = uniform(a.over[tile].x), b1 = uniform(a.over[tile].y), q0 = helper ? int64_t(blockIdx.x + 1) * part : b0;
+    const int64_t b0 = uniform(a.over[tile].x), b1 = uniform(a.over[tile].y);
+    const int64_t q0 = helper ? int64_t(blockIdx.x + 1) * part : b0;
     const int64_t q1 = b1 - b0 > 2 * part ? large.end(q0, b1) : b1;
     const uint32_t c = uniform(a.chunks[tile].y), slot0 = uniform(a.chunks[tile].x) + c;
     uint32_t used = 0;

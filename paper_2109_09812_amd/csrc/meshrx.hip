@@ -1170,8 +1170,8 @@ mrx_status launch_single(const SortVariant& v, const Layout& L, const void* vtx,
       return check_launch();
     }
     prof_mark("old2new", s);
-    launch_scatter_old2new<false>(s, false, sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0, nullptr,
-                                  old2new, static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
+    launch_scatter_old2new<false>(s, false, sb, static_cast<const uint2*>(nullptr), cmap, n, nullptr, nullptr, 0,
+                                  nullptr, old2new, static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
                                   static_cast<const uint32_t*>(nullptr));
   }
   // Step 4: remap the index array
@@ -1737,10 +1737,10 @@ mrx_status mrx_reindex_mesh_batched(const void* vtx, const int64_t* vtx_offsets,
                        num_meshes, sb, static_cast<const int32_t*>(cmap), static_cast<const Control*>(ctl),
                        static_cast<const int64_t*>(&ctl->num_used), n, out_vtx_offsets);
     prof_mark("old2new", s);
-    launch_scatter_old2new<true>(s, false, sb, static_cast<const uint2*>(nullptr), cmap, n, vtx_offsets, out_vtx_offsets,
-                                 num_meshes, static_cast<const int32_t*>(vtab), old2new,
+    launch_scatter_old2new<true>(s, false, sb, static_cast<const uint2*>(nullptr), cmap, n, vtx_offsets,
+                                 out_vtx_offsets, num_meshes, static_cast<const int32_t*>(vtab), old2new,
                                  static_cast<const uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
-                                  static_cast<const uint32_t*>(nullptr));
+                                 static_cast<const uint32_t*>(nullptr));
     if (new2old) {
       prof_mark("localize_new2old", s);
       hipLaunchKernelGGL(k_localize_new2old, dim3(grid_for(n, 256)), dim3(256), 0, s, new2old,

@@ -222,8 +222,8 @@ void launch_group_mesh(const GroupArgs& a, int64_t grid, hipStream_t s) {
 
 template <bool MESH>
 void launch_group_over(const GroupArgs& a, const LargeBuckets& large, int64_t chunks, hipStream_t s) {
-  hipLaunchKernelGGL((k_group_over<K, MESH>), dim3(std::max<int64_t>(large.helpers, std::min<int64_t>(chunks, kOverGrid))),
-                     dim3(kGroupBlock), 0, s, a, large, chunks);
+  const int64_t grid = std::max<int64_t>(large.helpers, std::min<int64_t>(chunks, kOverGrid));
+  hipLaunchKernelGGL((k_group_over<K, MESH>), dim3(grid), dim3(kGroupBlock), 0, s, a, large, chunks);
 }
 
 // The sample sort of the used groups, grids sized for n of them.
