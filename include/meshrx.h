@@ -206,7 +206,9 @@ mrx_status mrx_reindex_mesh_noalloc(const void* vtx, int64_t num_vtx, int32_t vt
  *   vtx           [total_vtx records], mesh b at records
  *                 [vtx_offsets[b], vtx_offsets[b+1]).
  *   vtx_offsets   device int64 [num_meshes + 1], non-decreasing, [0] == 0,
- *                 [num_meshes] == total_vtx (not checked on the host).
+ *                 [num_meshes] == total_vtx (not checked on the host; the
+ *                 outputs for others are unspecified, but every kernel stays
+ *                 in bounds).
  *   idx           [total_elems * arity] int32, MESH-LOCAL vertex ids; mesh b
  *                 owns elements [elem_offsets[b], elem_offsets[b+1]).
  *   elem_offsets  device int64 [num_meshes + 1], same rules, ends at

@@ -7,8 +7,9 @@
 // one pass (bucket_kernels.hpp); beyond that, and with k_group below, the N
 // pairs are first sorted by a few hash digits of the record (stable, so within
 // a bucket of equal hash digits ids stay ascending). Equal records share
-// their hash, so every group of duplicates lies inside one bucket, and buckets are small enough (a few hundred
-// records) to be grouped in LDS: k_group numbers the groups of each bucket in
+// their hash, so every group of duplicates lies inside one bucket, and buckets
+// are small enough (a few hundred records) to be grouped in LDS: k_group
+// numbers the groups of each bucket in
 // order of their first copy, which is the smallest original id (Step 2's
 // representative rule), and emits one element per *used* group. Only those U
 // elements are then sorted by their full key (Step 3's output order), a

@@ -314,9 +314,9 @@ __global__ __launch_bounds__(BLOCK) void k_compact(CompactArgs a) {
 // at their groups' new ids: the pair that holds one is found by comparison.
 // `large` (null after sort-all): not 0 if there were large buckets (led_name). With kStageRep they are staged like the
 // new ids, with both loads in flight: for calls that use most of their values
-// (batch4096 5.5 ms; 5.9 where the same LDS took first the one and then the
-// other). Where few are used only theirs are read, and the LDS goes to more
-// workgroups (26M vertices, 1% used: 0.69 ms staged, 0.45 not).
+// (328M vertices in 4,096 meshes 5.8 ms; 6.0 where the same LDS took first the
+// one and then the other). Where few are used only theirs are read, and the LDS goes to more
+// workgroups (26M vertices, 1% used: 0.69 ms staged, 0.43 not).
 template <bool BATCHED, int kItems, bool kStageRep>
 __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs, const uint2* pairs_in,
                                                                 const int32_t* __restrict__ cmap, int64_t n,
