@@ -84,13 +84,22 @@ __global__ void k_localize_new2old(int32_t* __restrict__ new2old, const int64_t*
 }
 
 // tab[q] = mesh of packed id min(q << kMeshTabShift, total - 1), q in [0, nq),
-// the bucket table that lets mesh_of search a handful of meshes.
-__global__ void k_mesh_table(const int64_t* __restrict__ off, int32_t nmesh, int64_t total, int32_t* tab,
-                             int64_t nq) {
-  const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (q >= nq) return;
-  const int64_t x = min(q << kMeshTabShift, total - 1);
-  tab[q] = int32_t(mesh_of(off, nmesh, x));
+// the bucket table that lets mesh_of search a handful of meshes. `more`: a
+// second table in the same launch (nq = 0: none).
+struct MeshTable {
+  const int64_t* off;
+  int64_t total;
+  int32_t* tab;
+  int64_t nq;
+};
+__global__ void k_mesh_table(MeshTable t, MeshTable more, int32_t nmesh) {
+  int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (q >= t.nq) {
+    q -= t.nq;
+    t = more;
+  }
+  if (q >= t.nq) return;
+  t.tab[q] = int32_t(mesh_of(t.off, nmesh, min(q << kMeshTabShift, t.total - 1)));
 }
 
 // Workspace of mrx_reindex_mesh_noalloc: a fixed array in the library's code
@@ -474,6 +483,15 @@ void launch_scatter_old2new(hipStream_t s, bool stage_rep, SortBuffers sb, const
   else
     hipLaunchKernelGGL((k_scatter_old2new<BATCHED, kScatterItems, false>), many, block, 0, s, sb, pairs, cmap, n,
                        rest...);
+}
+
+// Entries of the bucket table of `total` ids (0: none), as laid out by
+// make_layout or fewer.
+int64_t mesh_table_size(int64_t total) { return total > 0 ? (total - 1) / (int64_t(1) << kMeshTabShift) + 2 : 0; }
+
+void launch_mesh_tables(const MeshTable& t, const MeshTable& more, int32_t nmesh, hipStream_t s) {
+  const int64_t nq = t.nq + more.nq;
+  if (nq > 0) hipLaunchKernelGGL(k_mesh_table, dim3((nq + 255) / 256), dim3(256), 0, s, t, more, nmesh);
 }
 
 mrx_status check_launch() {
@@ -1252,16 +1270,9 @@ mrx_status launch_batched_hash(const SortVariant& v, const Layout& layout, const
     hipLaunchKernelGGL(k_mesh_buckets<true>, dim3(1), dim3(kMeshBucketBlock), 0, s, vtx_offsets, num_meshes, n,
                        int32_t(v.group_mesh_target_bucket), out_vtx_offsets, mbk);
   prof_mark("mesh_tables", s);
-  hipLaunchKernelGGL(k_mesh_table, dim3((L.vtx_tab_n + 255) / 256), dim3(256), 0, s, ordered, num_meshes, n,
-                     vtab, L.vtx_tab_n);
-  const int64_t num_e = total_elems;
-  if (etab && num_e > 0) {
-    const int64_t nq = (num_e - 1) / (int64_t(1) << kMeshTabShift) + 2;  // <= L.elem_tab_n
-    hipLaunchKernelGGL(k_mesh_table, dim3((nq + 255) / 256), dim3(256), 0, s, elem_offsets, num_meshes, num_e,
-                       etab, nq);
-  } else {
-    etab = nullptr;
-  }
+  if (total_elems <= 0) etab = nullptr;
+  launch_mesh_tables({ordered, n, vtab, L.vtx_tab_n}, {elem_offsets, total_elems, etab, mesh_table_size(total_elems)},
+                     num_meshes, s);
   // Step 1 by vertex bands, or by scattered byte stores beside the
   // bucket-digit histograms of the stable sort of (record, id | used << 31)
   // by the buckets of (mesh id, record)
@@ -1637,21 +1648,11 @@ mrx_status mrx_reindex_mesh_batched(const void* vtx, const int64_t* vtx_offsets,
   hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(int64_t(L.zero_end / 16), 256, 4096)), dim3(256), 0, s,
                      reinterpret_cast<uint4*>(ws), int64_t(L.zero_end / 16), dev_status,
                      static_cast<int64_t*>(nullptr), static_cast<int64_t*>(nullptr));
-  const int64_t num_e = total_elems;
-  if (vtab && n > 0) {
-    prof_mark("mesh_tables", s);
-    hipLaunchKernelGGL(k_mesh_table, dim3((L.vtx_tab_n + 255) / 256), dim3(256), 0, s, vtx_offsets, num_meshes,
-                       n, vtab, L.vtx_tab_n);
-  } else {
-    vtab = nullptr;
-  }
-  if (etab && num_e > 0) {
-    const int64_t nq = (num_e - 1) / (int64_t(1) << kMeshTabShift) + 2;  // <= L.elem_tab_n
-    hipLaunchKernelGGL(k_mesh_table, dim3((nq + 255) / 256), dim3(256), 0, s, elem_offsets, num_meshes, num_e,
-                       etab, nq);
-  } else {
-    etab = nullptr;
-  }
+  if (n <= 0) vtab = nullptr;
+  if (total_elems <= 0) etab = nullptr;
+  if (vtab || etab) prof_mark("mesh_tables", s);
+  launch_mesh_tables({vtx_offsets, n, vtab, vtab ? L.vtx_tab_n : 0},
+                     {elem_offsets, total_elems, etab, mesh_table_size(total_elems)}, num_meshes, s);
   const MarkArgs mark{idx, m, arity, n, vtx_offsets, elem_offsets, num_meshes, etab, nullptr, used_v, status};
   const bool fused = v.mark_hist_applies(n, m);
   if (fused) {
@@ -1785,10 +1786,8 @@ mrx_status mrx_merge_meshes(const void* vtx, const int64_t* vtx_offsets, int64_t
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (m > 0) {
     int32_t* etab = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + L.elem_tab);
-    const int64_t nq = (total_elems - 1) / (int64_t(1) << kMeshTabShift) + 2;  // <= L.elem_tab_n
     prof_mark("mesh_tables", s);
-    hipLaunchKernelGGL(k_mesh_table, dim3((nq + 255) / 256), dim3(256), 0, s, elem_offsets, num_meshes,
-                       total_elems, etab, nq);
+    launch_mesh_tables({elem_offsets, total_elems, etab, mesh_table_size(total_elems)}, {}, num_meshes, s);
     prof_mark("offset_indices", s);
     hipLaunchKernelGGL(k_offset_indices, dim3((m + 255) / 256), dim3(256), 0, s, idx, m, arity, vtx_offsets,
                        elem_offsets, num_meshes, static_cast<const int32_t*>(etab), out_idx);
