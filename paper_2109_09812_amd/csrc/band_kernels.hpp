@@ -332,6 +332,7 @@ __global__ __launch_bounds__(BLOCK) void k_pair_partition(PairPartArgs a) {
   const int tid = threadIdx.x;
   for (int b = tid; b < kMaxBands; b += BLOCK) s_cnt[b] = 0;
   __syncthreads();
+  const bool led = a.large && *a.large != 0;  // requested before the pairs
   const uint2* pairs = a.from_sort ? reinterpret_cast<const uint2*>(a.sort.spare()) : a.pairs;
   uint2* out = a.from_sort ? reinterpret_cast<uint2*>(a.sort.sorted()) : a.part;
   const int64_t tile = blockIdx.x;
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(BLOCK) void k_pair_partition(PairPartArgs a) {
     at[i] = 0xFFFFFFFFu;
     if (a.new2old) at[i] = a.rep[min(p[i].x, last)];
   }
-  if (a.large && *a.large != 0) {
+  if (led) {
     // names that lead to another of their group
 #pragma unroll
     for (int i = 0; i < kPairItems; ++i) {

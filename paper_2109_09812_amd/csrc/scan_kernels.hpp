@@ -333,6 +333,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
   __shared__ uint32_t s_rep[kStageRep ? TILE : 1];
   __shared__ uint32_t s_g[2];
   __shared__ uint32_t s_mesh[2];
+  const bool led = large && *large != 0;  // requested before the pairs
   const int64_t t0 = int64_t(blockIdx.x) * TILE;
   const int64_t base = t0 + threadIdx.x;
   const int64_t t1 = min(t0 + TILE, n) - 1;  // last position of the tile
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(kRandBlock) void k_scatter_old2new(SortBuffers bufs
     if (int64_t(p[it].x) >= n) c[it] = -1;
     else c[it] = (off >= 0 && off < span) ? s_cmap[off] : cmap[p[it].x];
   }
-  if (large && *large != 0) {
+  if (led) {
     // names that lead to another of their group (of a large hash bucket)
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
